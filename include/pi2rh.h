@@ -318,8 +318,8 @@ pi_status pi_rollout_adjoint(const pi_problem *p, const pi_lwpr *m, const void *
  * [T_b][n_u], iter[b] (one uint32), cost[b] [K_b][T_b].  All problems must be
  * PI_F32 and PI_DYN_QUAD12 with matrix-core models (PI_ERR_UNSUPPORTED
  * otherwise).  A problem's tile_samples (<= 32, or <= 128 when the batch
- * runs the bf16x3 or f16x2 form; 0 = 16, or 128 in the f16x2 form) sets
- * its tile; the variant and tile_waves of problem 0 apply to the batch (8
+ * runs the bf16x3 or f16x2 form; 0 = 16, or 128 in the f16x2 form of a batch
+ * of at least 16384 rollouts) sets its tile; the variant and tile_waves of problem 0 apply to the batch (8
  * waves need every tile <= 16, or the largest above 32 in the pieces forms).
  * Models given pre-folded (pi_lwpr.folded) are read in place; the others are
  * folded into the workspace on every call.  The launch plan (descriptors and

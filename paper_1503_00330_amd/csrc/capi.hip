@@ -479,8 +479,17 @@ struct BatchLayout {
   std::vector<int64_t> n_tiles, item_off;
 };
 
-int batch_spw(const pi_problem &p) {
-  return p.tile_samples > 0 ? p.tile_samples : p.variant == PI_VARIANT_MFMA_F16X2 ? 128 : 16;
+// Tile of the fp16 form's problems that leave it to the library: the shared
+// tile once its 128-row workgroups cover about half of a 256-unit device, else
+// the 16-row tiles, whose workgroups are eight times as many (single problems
+// of 6 x 256 models and 40 steps, shared tile on 8 waves against 16 rows on 4
+// or 8: 2.07 against 1.12 or 1.30 ms at 8192 rollouts, 2.07 against 1.99 or
+// 2.39 ms at 16384, 2.08 against 2.87 or 3.59 ms at 24576).
+constexpr int64_t kBatchSharedMinSamples = 16384;
+
+int batch_spw(const pi_problem &p, int64_t n_total) {
+  if (p.tile_samples > 0) return p.tile_samples;
+  return p.variant == PI_VARIANT_MFMA_F16X2 && n_total >= kBatchSharedMinSamples ? 128 : 16;
 }
 
 pi_status batch_layout(int32_t B, const pi_problem *p, const pi_lwpr *m, BatchLayout *out) {
@@ -499,10 +508,12 @@ pi_status batch_layout(int32_t B, const pi_problem *p, const pi_lwpr *m, BatchLa
   BatchLayout L;
   L.waves = p[0].tile_waves > 0 ? p[0].tile_waves : 4;
   L.max_spw = 0;
+  int64_t n_total = 0;   // rollouts of the whole batch
+  for (int b = 0; b < B; ++b) n_total += (int64_t)p[b].K * (p[b].M > 0 ? p[b].M : 1);
   L.spw.resize(B);
   L.n_tiles.resize(B);
   for (int b = 0; b < B; ++b) {
-    L.spw[b] = batch_spw(p[b]);
+    L.spw[b] = batch_spw(p[b], n_total);
     L.max_spw = std::max(L.max_spw, L.spw[b]);
     L.n_tiles[b] = ((int64_t)p[b].K * (p[b].M > 0 ? p[b].M : 1) + L.spw[b] - 1) / L.spw[b];
   }

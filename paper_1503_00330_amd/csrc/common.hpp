@@ -173,6 +173,43 @@ __device__ __forceinline__ void euler_step(int dyn, Real dt, const Real *x, cons
   }
 }
 
+// The same step with the state carried as x + lo: each sum's rounding error
+// goes into lo and back into the next step's increment (Kahan), so a float32
+// state does not pick up half an ulp per step over the horizon -- without it,
+// the largest part of a float32 rollout's error.  (Where the increment exceeds
+// the state the captured error is itself rounded, below an ulp of the sum.)
+template <typename Real>
+__device__ __forceinline__ void euler_step_comp(int dyn, Real dt, const Real *x, const Real *acc, const Real *u,
+                                                Real *xn, Real *lo) {
+  auto add = [&](int a, Real rate) {
+    const Real y = dt * rate + lo[a];
+    xn[a] = x[a] + y;
+    lo[a] = y - (xn[a] - x[a]);
+  };
+  if (dyn == kDynPointMass2D) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      add(a, x[2 + a]);
+      add(2 + a, acc[a]);
+    }
+  } else if (dyn == kDynQuadHybrid) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      add(a, x[3 + a]);
+      add(3 + a, acc[a]);
+      add(6 + a, (Real)kRateGain * (u[a] - x[6 + a]));
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      add(a, x[3 + a]);
+      add(3 + a, acc[a]);
+      add(6 + a, x[9 + a]);
+      add(9 + a, acc[3 + a]);
+    }
+  }
+}
+
 // State cost q(x) (Sec. 5): weighted squared goal error, |euler|^2 and |v|^2
 // penalties, plus the obstacle term over obstacles in `obs` (LDS or global).
 template <typename Real>

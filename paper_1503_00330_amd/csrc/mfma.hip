@@ -326,38 +326,52 @@ __device__ __forceinline__ Acc acc_sum(const Acc &a, const Acc &b) {
 // tile, 32-feature block and piece, 64 lanes x 8 bf16 (16 bytes per lane,
 // kept in the float4 slots), sample lane%16, features 8 (lane/16) .. +7.
 //
-// SH (a pieces form with MT > 2 row tiles, MT / NW = 1 or 2 per wave): the
-// shared-tile form.  Each wave owns its row tiles and runs every model tile;
-// the workgroup stages each model tile once in LDS (ring, three tiles deep)
-// instead of every wave streaming its own range, and each wave's sums are
-// final (NPART = 1).  The samples' pieces are built in registers by their
-// wave (no A).
+// SH (a pieces form with MT > 2 row tiles): the shared-tile form.  The
+// workgroup stages each model tile once in LDS (ring) instead of every wave
+// streaming its own range; each wave holds RT row tiles, and the TS waves of a
+// row group share the model tiles (NPART = TS sets of sums).  The samples'
+// pieces are built in registers by their waves (no A).
 template <int D, int MT, int NW, int PF = 0>
 struct MixSmem {
   static constexpr bool BF = PF != kPfF32;
   static constexpr bool SH = BF && MT > 2;
-  static_assert(!BF || (D == kBfD && (MT <= 2 || (MT % NW == 0 && MT / NW <= 2))),
-                "the pieces forms cover d = 16, one or two row tiles per wave");
+  static_assert(!BF || (D == kBfD && (MT <= 2 || MT == 8)), "the pieces forms cover d = 16, one or two row tiles per wave");
   static constexpr int NPC = PF == kPfF16x2 ? 2 : 3;   // pieces per value
   static constexpr int ROWS = 16 * MT;
   static constexpr int NFRAG = BF ? kBfNKB * NPC : Geo<D>::KB4;   // 16-byte fragments per lane and row tile
   static constexpr int NSRC = BF ? kBfNKB * 32 : Geo<D>::NE;
-  static constexpr int NPART = SH ? 1 : NW;
-  // ring slot: the tile's piece chunks (1 KiB each, lane-major), then one of
-  // its per-model values (the 16 sigma^2; fp16 form: sigma^2 and scales)
-  static constexpr int kRingChunks = kBfNKB * NPC + 1;
-  static constexpr int kRingSlots = 4;   // two stages of two tiles
+  // row tiles per wave and waves per row group of the shared-tile form: the
+  // bf16 pieces of two row tiles would not fit an eight-wave workgroup's
+  // registers beside the rest
+  static constexpr int RT = PF == kPfBf16x3 && NW == 8 ? 1 : 2;
+  static constexpr int TS = SH ? NW * RT / MT : 1;
+  static constexpr int NPART = SH ? TS : NW;
+  // outputs held per row: the shared-tile form runs the quadrotor's six
+  static constexpr int NOUT = SH ? 6 : kMaxOut;
+  static constexpr int XIS = SH ? 6 : 8;   // next-state draws held per row
+  // ring of stages of two tiles' piece chunks (1 KiB each, lane-major)
+  static constexpr int kChunks = kBfNKB * NPC;
+  static constexpr int kRingStages = 3;
   std::conditional_t<SH, char[16], float4[MT][NFRAG][64]> A;   // sample fragments, lane-major (anchor slots 0)
-  std::conditional_t<SH, u32x4[kRingSlots][kRingChunks][64], char[16]> ring;
-  Acc part[NPART][kMaxOut][ROWS];        // per-wave partial sums
+  std::conditional_t<SH, u32x4[kRingStages][2 * kChunks][64], char[16]> ring;
+  Acc part[NPART][NOUT][ROWS];           // per-wave partial sums
   float z[ROWS][D + 2];                  // [z, 1, 0]: fragment entries are products of two
-  float mref[ROWS][kMaxOut], yref[ROWS][kMaxOut];
-  float mprev[ROWS][kMaxOut];            // previous step's largest activation
-  float mean[ROWS][kMaxOut], var[ROWS][kMaxOut];
-  float acc[ROWS][kMaxOut];              // sampled accelerations (rollouts)
+  float mref[ROWS][NOUT], yref[ROWS][NOUT];
+  float mprev[ROWS][NOUT];               // previous step's largest activation
+  float mean[SH ? 1 : ROWS][NOUT], var[SH ? 1 : ROWS][NOUT];   // moments (read by the prediction kernel)
+  // sampled accelerations (rollouts); the shared-tile form, whose LDS is full,
+  // leaves them in the Z slots of the sums they come from
+  float acc[SH ? 1 : ROWS][NOUT];
+  __device__ __forceinline__ float &accel(int row, int o) {
+    if constexpr (SH)
+      return part[0][o][row].Z;
+    else
+      return acc[row][o];
+  }
   unsigned short fsrc[NSRC];             // entry (BF: feature slot) -> (ia << 8) | ib into z[row][]
   int redo[2];                           // second-pass requests, by evaluation parity
   int pair_fail;                         // a partner wait ran out (results invalid)
+  int model_scaled;                      // SH, fp16 form: some tile's scales are not all 1
 };
 
 // fp16 form: the exponent e >= 0 of the power of two 2^-e that scales every
@@ -373,7 +387,8 @@ __device__ __forceinline__ int row_scale_exp(const MixSmem<D, MT, NW, PF> &sm, i
     mx = fmaxf(mx, fmaxf(za, za * za));
   }
 #pragma unroll
-  for (int o = 0; o < kMaxOut; ++o) mx = fmaxf(mx, fmaxf(fabsf(sm.mref[row][o]), fabsf(sm.yref[row][o])));
+  for (int o = 0; o < MixSmem<D, MT, NW, PF>::NOUT; ++o)
+    mx = fmaxf(mx, fmaxf(fabsf(sm.mref[row][o]), fabsf(sm.yref[row][o])));
   int ex = 0;
   frexpf(mx, &ex);   // mx < 2^ex
   return ex > 14 ? ex - 14 : 0;
@@ -495,9 +510,8 @@ __device__ __forceinline__ void build_fragments(MixSmem<D, MT, NW, PF> &sm) {
 template <int D, int MT, int NW, int PF>
 __device__ __forceinline__ void clear_parts(MixSmem<D, MT, NW, PF> &sm) {
   Acc *pp = &sm.part[0][0][0];
-  for (int i = threadIdx.x; i < MixSmem<D, MT, NW, PF>::NPART * kMaxOut * MixSmem<D, MT, NW, PF>::ROWS;
-       i += NW * 64)
-    pp[i] = acc_empty();
+  using SM = MixSmem<D, MT, NW, PF>;
+  for (int i = threadIdx.x; i < SM::NPART * SM::NOUT * SM::ROWS; i += NW * 64) pp[i] = acc_empty();
 }
 
 // Stage 2 (each wave): its contiguous range of model tiles, one MFMA chain per
@@ -969,64 +983,80 @@ __device__ __forceinline__ void static_for(F &f) {
   }
 }
 
-// The shared-tile form of the bf16 stage (MixSmem::SH: RT = MT / NW row tiles
-// per wave, one or two).  Every wave runs all model tiles [T0, T1) for its own
-// 16 RT rows, so the workgroup reads each model tile from L2 once per step
-// instead of once per wave: the tile's 18 piece chunks and its sigma^2 go
-// straight from memory into a four-slot LDS ring (buffer loads to LDS, each
-// wave issuing every NW-th chunk), and each wave reads the chunks of the tile
-// in hand from LDS.  The tiles go in stages of two: a stage's loads are issued
-// one stage ahead, and the waves meet once per stage, so the two waves of a
-// SIMD (8 waves, one row tile each) can drift apart within it and one's
-// vector work runs under the other's products.  Per stage a wave waits for
-// its own loads of that stage and then for the other waves at a barrier: past
-// it the stage is complete in LDS and every wave is done with the slots the
-// next loads overwrite (the previous stage's).  The per-tile arithmetic is
-// mixture_tiles_bf's for the wave's row tiles, in tile order.
+// The shared-tile form of the pieces stage (MixSmem::SH): 128 rows in groups of
+// 16 RT, every wave holding the pieces of one group.  With two row tiles per
+// wave each model piece read from LDS serves two products; the workgroup reads
+// each model tile from L2 once per step: the tile's piece chunks go straight
+// from memory into an LDS ring (buffer loads to LDS, each wave issuing every
+// NW-th chunk).  The tiles go in stages of two.  Four waves (and eight with
+// one row tile each, the bf16 form) run both tiles of a stage; eight waves of
+// two row tiles take one tile of the stage each, waves w and w + 4 (one SIMD)
+// holding the same rows, their sums meeting in the merge.  Three stages fit the
+// ring: a stage's loads are issued two stages ahead, spread over the products
+// of the stage in hand (all at once after the barrier they held every wave up
+// for about 400 cycles), and are complete one stage before their use, so a
+// wave reads its next tile's first blocks before the barrier.  Per stage a wave
+// waits for its own loads of the next stage and then for the other waves at a
+// barrier: past it every wave is done with the slots the next loads overwrite.
+//
+// Bound: the matrix pipe (36 fp16 products of 16 cycles per wave and tile) and,
+// with it, the card's power: its clock falls as the pipe fills.  A product
+// leaves room for two vector instructions beside it, so the softmax epilogue of
+// the wave's previous tile (52 vector operations and 8 exponentials) is issued
+// between the products of the tile in hand, from a second accumulator set, as
+// in mixture_tiles_bf: a pending set with activation -inf, prediction 0 and
+// sigma^2 0 adds exact zeros.  At 65536 rollouts x 200 steps x 6 x 1024 models
+// (fp16 pieces, 8 waves) a stage of two tiles takes 1833 cycles at 2.06 GHz,
+// the pipe 64 % busy, 68.9 ms in all (1350 TFLOP/s of executed fp16 products);
+// one row tile per wave, every piece read for one product and the epilogue
+// behind the products: 2540 cycles at 2.35 GHz, 83.7 ms on the same card.  bf16
+// pieces, 40 steps: 25.8 against 26.5 ms.
 template <int D, int MT, int NW, int PF>
 __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D, MT, NW, PF> &sm, int T0, int T1) {
   using SM = MixSmem<D, MT, NW, PF>;
-  static_assert(SM::SH && (NW == 4 || NW == 8), "shared-tile form: four or eight waves");
+  static_assert(SM::SH && MT == 8 && (NW == 4 || NW == 8), "shared-tile form: 128 rows on four or eight waves");
   using G = Geo<D>;
   constexpr bool HF = PF == kPfF16x2;   // two fp16 pieces (else three bf16 pieces)
   constexpr int NPC = SM::NPC;
-  constexpr int RT = MT / NW;   // row tiles per wave
-  constexpr int RW = 16 * RT;   // rows per wave
+  constexpr int RT = SM::RT;     // row tiles per wave
+  constexpr int RG = MT / RT;    // row groups
+  constexpr int TS = SM::TS;     // waves per row group: each takes every TS-th tile
+  static_assert(RG * TS == NW && (TS == 1 || TS == 2), "shared-tile form: the waves cover the rows");
   constexpr int FQ = G::NP + D + 1, KQA = FQ / 32, GQA = (FQ % 32) / 8, IQA = FQ % 8;
   constexpr int FY = D + 1, KYA = kBfNKQ + FY / 32, GYA = (FY % 32) / 8, IYA = FY % 8;
   constexpr int kTileBytes = kBfNKB * NPC * 1024;
-  constexpr int kSig = SM::kRingChunks - 1;   // ring chunk of the per-model values
   // bytes of per-model values per tile: sigma^2, or (fp16 form) sigma^2 and the two scales
   constexpr int kMetaBytes = HF ? kHfMeta * 4 : 16 * 4;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int half = TS == 2 ? wave / RG : 0;
+  const int row0 = 16 * RT * (wave % RG) + (lane & 15);   // the lane's row of row tile 0
   const int n = T1 - T0;
   const __amdgpu_buffer_rsrc_t wrs = buffer_rsrc(HF ? (const void *)md.Wh : (const void *)md.Wb,
                                                  md.n_tiles * kTileBytes);
   const __amdgpu_buffer_rsrc_t srs = buffer_rsrc(HF ? md.hmeta : md.sig2, md.n_tiles * kMetaBytes);
-  // this wave's loads of one tile: chunks wave, wave + NW, ... up to kSig (the
-  // chunk of per-model values)
-  constexpr int kJobs = SM::kRingChunks, kMaxJob = (kJobs + NW - 1) / NW;
-  auto issue = [&](int tile, int slot) {
-#pragma unroll
-    for (int q = 0; q < kMaxJob; ++q) {
-      const int c = wave + NW * q;
-      if (c < kSig)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (__attribute__((address_space(3))) void *)&sm.ring[slot][c][0],
-                                                 16, lane * 16, tile * kTileBytes + c * 1024, 0, 0);
-      else if (c == kSig)
-        // 64 lanes x 4 bytes from the tile's 16 (or 48) values on (the lanes
-        // past them read the next tiles', or zeros past the last: unused)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, (__attribute__((address_space(3))) void *)&sm.ring[slot][c][0],
-                                                 4, lane * 4, tile * kMetaBytes, 0, 0);
-    }
+  // Stage st_i: tiles 2 st_i and 2 st_i + 1, their chunks (contiguous in memory)
+  // in ring stage st_i % NSTG.  Load q of this wave is chunk wave + NW q of the
+  // stage.  The loads are unconditional: past the stage's last chunk they
+  // repeat it, past the range's last tile they re-read that tile's end into
+  // slots that nobody reads (no branch in the tile loop).
+  constexpr int NSTG = SM::kRingStages;
+  constexpr int kLoads = (2 * SM::kChunks + NW - 1) / NW;
+  const int n_st = (n + 1) / 2;
+  const int src_end = T1 * kTileBytes - 1024;
+  auto issue = [&](int st_i, int ring, int q) {
+    const int j = min(wave + NW * q, 2 * SM::kChunks - 1);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (__attribute__((address_space(3))) void *)&sm.ring[ring][j][0], 16,
+                                             lane * 16, min((T0 + 2 * st_i) * kTileBytes + j * 1024, src_end), 0, 0);
   };
-  // stage st_i: tiles 2 st_i and 2 st_i + 1 in slots 2 (st_i & 1) and + 1
   auto issue_stage = [&](int st_i) {
-    issue(T0 + 2 * st_i, 2 * (st_i & 1));
-    if (2 * st_i + 1 < n) issue(T0 + 2 * st_i + 1, 2 * (st_i & 1) + 1);
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) issue(st_i, st_i % NSTG, q);
   };
-  if (n > 0) issue_stage(0);
+  if (n > 0) {
+    issue_stage(0);
+    issue_stage(1);
+  }
   // fp16 form: each row's features (and its anchors) scaled by a power of two
   // 2^-e (e >= 0) that keeps them below 2^14 in magnitude; rsc[mt] = 2^e
   // undoes it in the epilogue
@@ -1036,7 +1066,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     rsc[mt] = 1.0f;
     rsi[mt] = 1.0f;
     if constexpr (HF) {
-      const int e = row_scale_exp(sm, RW * wave + 16 * mt + (lane & 15));
+      const int e = row_scale_exp(sm, row0 + 16 * mt);
       rsc[mt] = ldexpf(1.0f, e);
       rsi[mt] = ldexpf(1.0f, -e);
     }
@@ -1048,23 +1078,25 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     else
       bf16_split3(x, pc);
   };
-  // the wave's sample pieces, built in registers (rows RW wave + 16 mt + lane%16,
-  // features 32 kb + 8 (lane/16) .. +7 of block kb)
+  // the wave's sample pieces, built in registers (rows row0 + 16 mt, features
+  // 32 kb + 8 (lane/16) .. +7 of block kb)
   u32x4 Bs[RT][kBfNKB][NPC];
   {
-    const int r16 = lane & 15, grp = lane >> 4;
+    const int grp = lane >> 4;
 #pragma unroll
-    for (int mt = 0; mt < RT; ++mt) {
-      const int row = RW * wave + 16 * mt + r16;
+    for (int kb = 0; kb < kBfNKB; ++kb) {
+      unsigned src[8];
 #pragma unroll
-      for (int kb = 0; kb < kBfNKB; ++kb) {
+      for (int i = 0; i < 8; ++i) src[i] = sm.fsrc[32 * kb + 8 * grp + i];
+#pragma unroll
+      for (int mt = 0; mt < RT; ++mt) {
+        const int row = row0 + 16 * mt;
         uint32_t pk[NPC][4];
 #pragma unroll
         for (int i = 0; i < 8; i += 2) {
           uint16_t lo[3], hi[3];
-          const unsigned s0 = sm.fsrc[32 * kb + 8 * grp + i], s1 = sm.fsrc[32 * kb + 8 * grp + i + 1];
-          split(sm.z[row][s0 >> 8] * sm.z[row][s0 & 0xFF], mt, lo);
-          split(sm.z[row][s1 >> 8] * sm.z[row][s1 & 0xFF], mt, hi);
+          split(sm.z[row][src[i] >> 8] * sm.z[row][src[i] & 0xFF], mt, lo);
+          split(sm.z[row][src[i + 1] >> 8] * sm.z[row][src[i + 1] & 0xFF], mt, hi);
 #pragma unroll
           for (int p = 0; p < NPC; ++p) pk[p][i / 2] = (uint32_t)lo[p] | ((uint32_t)hi[p] << 16);
         }
@@ -1102,20 +1134,27 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   auto set_anchor = [&](int oo) {
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
-      const int row = RW * wave + 16 * mt + (lane & 15);
+      const int row = row0 + 16 * mt;
       if ((lane >> 4) == GQA) put(Bs[mt][KQA], std::integral_constant<int, IQA>{}, -sm.mref[row][oo], mt);
       if ((lane >> 4) == GYA) put(Bs[mt][KYA], std::integral_constant<int, IYA>{}, -sm.yref[row][oo], mt);
     }
   };
-  Acc st[RT][4];
+  // sums over the lane's models 4 (lane/16) + i: one per i, or (eight waves,
+  // whose registers are all taken) i even and odd apart
+  constexpr int NS = TS == 1 ? 4 : 2;
+  Acc st[RT][NS];
+  auto clear_sums = [&]() {
 #pragma unroll
-  for (int mt = 0; mt < RT; ++mt)
+    for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) st[mt][i] = acc_empty();
+      for (int i = 0; i < NS; ++i) st[mt][i] = acc_empty();
+  };
+  clear_sums();
   auto flush = [&](int oo) {
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
-      Acc s = acc_sum(acc_sum(st[mt][0], st[mt][1]), acc_sum(st[mt][2], st[mt][3]));
+      Acc s = acc_sum(st[mt][0], st[mt][1]);
+      if constexpr (NS == 4) s = acc_sum(s, acc_sum(st[mt][2], st[mt][3]));
 #pragma unroll
       for (int m = 16; m <= 32; m <<= 1) {
         s.Z += __shfl_xor(s.Z, m);
@@ -1124,10 +1163,9 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
         s.S3 += __shfl_xor(s.S3, m);
         s.mx = fmaxf(s.mx, __shfl_xor(s.mx, m));
       }
-      if (lane < 16) sm.part[0][oo][RW * wave + 16 * mt + lane] = s;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) st[mt][i] = acc_empty();
+      if (lane < 16) sm.part[half][oo][row0 + 16 * mt] = s;
     }
+    clear_sums();
   };
   auto mm = [&](const u32x4 &a, const u32x4 &b, f32x4 c) {
     if constexpr (HF)
@@ -1137,143 +1175,198 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
                                                      0, 0, 0);
   };
-  int o = output_of(T0);
-  int nb = next_boundary(T0);
-  set_anchor(o);
-  const int n_st = (n + 1) / 2;
-  // RS: the wave's rows carry powers of two (fp16 form); without, as for
-  // nearly every state, the epilogue skips their products
-  auto stages = [&](auto RS) {
-    constexpr bool kRowScale = decltype(RS)::value;
-    for (int st_i = 0; st_i < n_st; ++st_i) {
-      // this wave's loads of the stage (issued one stage ago) are complete; no
-      // memory access moves across the barrier (compiler fences on both sides)
-      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), expcnt and lgkmcnt untouched
-      __asm__ __volatile__("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      __asm__ __volatile__("" ::: "memory");
-      if (st_i + 1 < n_st) issue_stage(st_i + 1);
-      const bool two = 2 * st_i + 1 < n;   // the stage holds a second tile
-      // the stage's 12 (or 6) blocks of model pieces go through a ring of three
-      // blocks in registers, each read from LDS two blocks before its products:
-      // with 8 waves reading, an LDS round trip outlasts one block's products
-      u32x4 wb[3][NPC];
-      auto ldb = [&](auto Q) {
-        constexpr int q = decltype(Q)::value, u = q / kBfNKB, kb = q % kBfNKB;
-        const u32x4(*W)[64] = sm.ring[2 * (st_i & 1) + u];
+  // two accumulator sets: one takes the tile in hand, the other waits for its
+  // epilogue, with sigma^2 and (fp16 form) the scales of its tile's models
+  f32x4 qa[2][RT], ya[2][RT], s2[2], qs[2], ys[2];
+  auto clear_pending = [&](auto PI) {
+    constexpr int p = decltype(PI)::value;
 #pragma unroll
-        for (int p = 0; p < NPC; ++p) wb[q % 3][p] = W[kb * NPC + p][lane];
-      };
-      ldb(std::integral_constant<int, 0>{});
-      ldb(std::integral_constant<int, 1>{});
-      f32x4 qa[RT], ya[RT], s2, qs, ys;
-      bool plain[2] = {false, false};
-      auto step = [&](auto Q) {
-        constexpr int q = decltype(Q)::value, u = q / kBfNKB, kb = q % kBfNKB;
-        if constexpr (q + 2 < 2 * kBfNKB) {
-          if (q + 2 < kBfNKB || two) ldb(std::integral_constant<int, q + 2>{});
-        }
-        __builtin_amdgcn_sched_barrier(0);   // the reads go out ahead of this block's products
-        if constexpr (kb == 0) {
-          // the two waves of a SIMD (w and w + 4 of 8) take turns leading the
-          // matrix pipe, one tile each per stage: left to age order, the older
-          // wave would finish the stage first and the younger run alone (the
-          // bf16 form; the fp16 form, half the products per tile, runs faster
-          // in age order)
-          if constexpr (NW == 8 && !HF) {
-            if ((wave >= 4) == (u == 0))
-              __builtin_amdgcn_s_setprio(1);
-            else
-              __builtin_amdgcn_s_setprio(0);
-          }
-          const int tile = T0 + 2 * st_i + u;
-          if (tile >= nb) {
-            flush(o);
-            o = output_of(tile);
-            nb = next_boundary(tile);
-            set_anchor(o);
-          }
-          const f32x4 *meta = (const f32x4 *)&sm.ring[2 * (st_i & 1) + u][kSig][0];
-          s2 = meta[lane >> 4];
-          if constexpr (HF) {   // the models' scales 2^eq, 2^ey, and whether all are 1
-            qs = meta[4 + (lane >> 4)];
-            ys = meta[8 + (lane >> 4)];
-            plain[u] = __builtin_amdgcn_readfirstlane(__float_as_int(((const float *)meta)[kHfPlain])) != 0;
-          }
+    for (int mt = 0; mt < RT; ++mt) {
+      qa[p][mt] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      ya[p][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    s2[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    qs[p] = f32x4{1.f, 1.f, 1.f, 1.f};
+    ys[p] = qs[p];
+  };
+  // The epilogue of element (row tile el % RT, model el / RT of the lane's four)
+  // in three steps, placed in consecutive slots so that none waits for the one
+  // before: A the exponential (and the models' and rows' powers of two undone,
+  // exactly, when SC), B and C the sums.
+  float ea[4 * RT], ee[4 * RT], ed[4 * RT];   // activation, weight, prediction difference (live for two slots)
+  auto epi_a = [&](auto PI, auto SC, int el) {
+    constexpr int p = decltype(PI)::value;
+    constexpr bool sc = decltype(SC)::value;
+    const int mt = el % RT, i = el / RT;
+    ea[el] = sc ? qa[p][mt][i] * (qs[p][i] * rsc[mt]) : qa[p][mt][i];
+    ed[el] = sc ? ya[p][mt][i] * (ys[p][i] * rsc[mt]) : ya[p][mt][i];
+    // bare v_exp_f32: arguments below -126 (weights under 2^-126 next to a
+    // largest term of at least 2^-100) need none of exp2f's denormal scaling
+    ee[el] = __builtin_amdgcn_exp2f(ea[el]);
+  };
+  float et[4 * RT];
+  auto epi_b = [&](int el) {
+    const int mt = el % RT, i = el / RT;
+    et[el] = ee[el] * ed[el];
+    st[mt][i % NS].Z += ee[el];
+    st[mt][0].mx = fmaxf(st[mt][0].mx, ea[el]);   // one running max per row
+  };
+  auto epi_c = [&](auto PI, int el) {
+    constexpr int p = decltype(PI)::value;
+    const int mt = el % RT, i = el / RT;
+    Acc &t = st[mt][i % NS];
+    t.S1 += et[el];
+    t.S2 = fmaf(et[el], ed[el], t.S2);
+    t.S3 = fmaf(ee[el], s2[p][i], t.S3);
+  };
+  auto epi_all = [&](auto PI, auto SC) {
 #pragma unroll
-          for (int mt = 0; mt < RT; ++mt) {
-            qa[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            ya[mt] = qa[mt];
-          }
-        }
-        const u32x4 *w = wb[q % 3];
-        // the piece pairs (model, sample) into one accumulator per row tile and
-        // sum (the pipe takes a dependent product at full rate; with two row
-        // tiles the chains alternate): bf16 hh, hm, mh, hl, mm, lh; fp16 hh, hl, lh
-        constexpr int NPR = HF ? 3 : 6;
-        constexpr int PA[6] = {0, 0, 1, 0, 1, 2}, PB[6] = {0, 1, 0, 2, 1, 0};
-#pragma unroll
-        for (int r = 0; r < NPR; ++r)
-#pragma unroll
-          for (int mt = 0; mt < RT; ++mt) {
-            f32x4 &x = kb < kBfNKQ ? qa[mt] : ya[mt];
-            x = mm(w[PA[r]], Bs[mt][kb][PB[r]], x);
-          }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kb == kBfNKB - 1) {
-          // SC: which powers of two the fp16 form undoes here (exact): none
-          // (bf16 pieces, or a tile whose models' scales are all 1 and rows
-          // without scale), the models', or the models' and the rows'
-          auto epilogue = [&](auto SC) {
-            constexpr int sc = decltype(SC)::value;
-#pragma unroll
-            for (int mt = 0; mt < RT; ++mt)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float a = sc == 0 ? qa[mt][i] : sc == 1 ? qa[mt][i] * qs[i] : qa[mt][i] * (qs[i] * rsc[mt]);
-                const float dd = sc == 0 ? ya[mt][i] : sc == 1 ? ya[mt][i] * ys[i] : ya[mt][i] * (ys[i] * rsc[mt]);
-                // bare v_exp_f32: arguments below -126 (weights under 2^-126 next to a
-                // largest term of at least 2^-100) need none of exp2f's denormal scaling
-                const float e = __builtin_amdgcn_exp2f(a);
-                const float te = e * dd;
-                st[mt][i].Z += e;
-                st[mt][i].S1 += te;
-                st[mt][i].S2 = fmaf(te, dd, st[mt][i].S2);
-                st[mt][i].S3 = fmaf(e, s2[i], st[mt][i].S3);
-                st[mt][0].mx = fmaxf(st[mt][0].mx, a);   // one running max per row
-              }
-          };
-          if constexpr (!HF)
-            epilogue(std::integral_constant<int, 0>{});
-          else if constexpr (kRowScale)
-            epilogue(std::integral_constant<int, 2>{});
-          else if (plain[u])
-            epilogue(std::integral_constant<int, 0>{});
-          else
-            epilogue(std::integral_constant<int, 1>{});
-        }
-      };
-      static_for<0, kBfNKB>(step);
-      if (two) static_for<kBfNKB, 2 * kBfNKB>(step);
-      if constexpr (NW == 8 && !HF) __builtin_amdgcn_s_setprio(0);
+    for (int el = 0; el < 4 * RT; ++el) {
+      epi_a(PI, SC, el);
+      epi_b(el);
+      epi_c(PI, el);
     }
   };
-  bool scaled = false;
+  // The tile's six blocks of model pieces go through a ring of three blocks in
+  // registers, each read from LDS two blocks (12 products) ahead.
+  u32x4 wb[3][NPC];
+  auto ldb = [&](const u32x4(*W)[64], int kb) {
 #pragma unroll
-  for (int mt = 0; mt < RT; ++mt) scaled = scaled || rsc[mt] != 1.0f;
-  if (HF && __builtin_amdgcn_ballot_w64(scaled) != 0)
-    stages(std::true_type{});
+    for (int p = 0; p < NPC; ++p) wb[kb % 3][p] = W[kb * NPC + p][lane];
+  };
+  int o = 0, nb = 0;
+  // the products of one tile (piece chunks W) into set c, the epilogue of the
+  // tile before from set p, (LD) the loads of stage st_ld into ring stage
+  // `ring_ld`, and the first blocks of the next tile (Wn)
+  auto body = [&](int tile, const u32x4(*W)[64], const u32x4(*Wn)[64], int st_ld, int ring_ld, auto LD, auto CI,
+                  auto PI, auto SC) {
+    constexpr int c = decltype(CI)::value;
+    if (tile >= nb) {
+      epi_all(PI, SC);
+      clear_pending(PI);
+      if (nb > 0) flush(o);
+      o = output_of(tile);
+      nb = next_boundary(tile);
+      set_anchor(o);
+    }
+    constexpr int NPR = HF ? 3 : 6;
+    constexpr int PA[6] = {0, 0, 1, 0, 1, 2}, PB[6] = {0, 1, 0, 2, 1, 0};
+    // slot: one product of each row tile (the chains alternate; piece pairs
+    // (model, sample) bf16 hh, hm, mh, hl, mm, lh; fp16 hh, hl, lh) and about
+    // four vector operations of the pending epilogue
+    auto slot = [&](auto SI) {
+      constexpr int sl = decltype(SI)::value, kb = sl / NPR, r = sl % NPR;
+      // the wave further behind in its tile goes first: left to age order, the
+      // older of the two waves of a SIMD would finish its tile early and leave
+      // the other to run alone
+      constexpr int kQuarter = (kBfNKB * NPR + 3) / 4;
+      if constexpr (NW == 8 && sl % kQuarter == 0) __builtin_amdgcn_s_setprio(3 - sl / kQuarter);
+      if constexpr (r == 0) {
+        if constexpr (kb + 2 < kBfNKB)
+          ldb(W, kb + 2);
+        else
+          ldb(Wn, kb + 2 - kBfNKB);
+      }
+      if constexpr (sl == 0) {   // for the epilogue, one tile later
+        s2[c] = buffer_f32x4(srs, 16 * (lane >> 4), tile * kMetaBytes);
+        if constexpr (decltype(SC)::value) {   // the models' scales 2^eq, 2^ey
+          qs[c] = buffer_f32x4(srs, 16 * (lane >> 4) + 64, tile * kMetaBytes);
+          ys[c] = buffer_f32x4(srs, 16 * (lane >> 4) + 128, tile * kMetaBytes);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int mt = 0; mt < RT; ++mt) {
+        f32x4 &x = kb < kBfNKQ ? qa[c][mt] : ya[c][mt];
+        x = mm(wb[kb % 3][PA[r]], Bs[mt][kb][PB[r]],
+               r == 0 && (kb == 0 || kb == kBfNKQ) ? f32x4{0.f, 0.f, 0.f, 0.f} : x);
+      }
+      if constexpr (sl % 2 == 0) {
+        if constexpr (sl / 2 < 4 * RT) epi_a(PI, SC, sl / 2);
+        if constexpr (sl >= 2 && sl / 2 - 1 < 4 * RT) epi_c(PI, sl / 2 - 1);
+      } else {
+        if constexpr (sl / 2 < 4 * RT) epi_b(sl / 2);
+        // a memory load each: all at once they would hold every wave up
+        if constexpr (decltype(LD)::value && sl / 2 < kLoads) issue(st_ld, ring_ld, sl / 2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<0, kBfNKB * NPR>(slot);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  auto enter = [&]() {
+    // this wave's loads are complete; no memory access moves across the barrier
+    // (compiler fences on both sides)
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), expcnt and lgkmcnt untouched
+    __asm__ __volatile__("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    __asm__ __volatile__("" ::: "memory");
+  };
+  auto run = [&](auto SC) {
+    auto W = [&](int ring, int u) { return (const u32x4(*)[64]) & sm.ring[ring][u * SM::kChunks]; };
+    auto next = [&](int r) { return r + 1 == NSTG ? 0 : r + 1; };
+    clear_pending(I1{});
+    enter();
+    ldb(W(0, half), 0);
+    ldb(W(0, half), 1);
+    int ring = 0, done = 0;   // ring stage of the stage in hand; tiles this wave has run
+    // one stage: the loads go to the stage whose ring slots the last barrier freed
+    auto stage = [&](int st_i, auto CI, auto PI) {
+      const int r1 = next(ring), rl = next(r1), sl = st_i + 2;
+      if constexpr (TS == 2) {
+        if (2 * st_i + half < n) {
+          body(T0 + 2 * st_i + half, W(ring, half), W(r1, half), sl, rl, std::true_type{}, CI, PI, SC);
+          ++done;
+        }
+      } else {
+        body(T0 + 2 * st_i, W(ring, 0), W(ring, 1), sl, rl, std::true_type{}, CI, PI, SC);
+        ++done;
+        if (2 * st_i + 1 < n) {
+          body(T0 + 2 * st_i + 1, W(ring, 1), W(r1, 0), n_st, rl, std::false_type{}, PI, CI, SC);
+          ++done;
+        }
+      }
+      ring = r1;
+    };
+    for (int st_i = 0; st_i < n_st;) {
+      stage(st_i, I0{}, I1{});
+      if (++st_i >= n_st) break;
+      enter();
+      if constexpr (TS == 2) {
+        stage(st_i, I1{}, I0{});
+        if (++st_i >= n_st) break;
+        enter();
+      }
+    }
+    // loads past the last stage must not land in the next evaluation's ring
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    if (done > 0) {
+      if (done & 1)
+        epi_all(I0{}, SC);
+      else
+        epi_all(I1{}, SC);
+      flush(o);
+    }
+  };
+  // Whether any power of two has to be undone: the wave's rows' (rarely) or
+  // some model's (the models' scales are all 1 unless their values are far
+  // from 1); products with a scale of 1 are exact, so both loops agree.
+  bool scaled = false;
+  if constexpr (HF)
+    scaled = sm.model_scaled != 0 || __builtin_amdgcn_ballot_w64(rsc[0] != 1.0f || rsc[RT - 1] != 1.0f) != 0;
+  if (HF && scaled)
+    run(std::true_type{});
   else
-    stages(std::false_type{});
-  flush(o);
+    run(std::false_type{});
 }
 
 // Sampling of the next-state draw inside the mixture's last stage: with xi
 // set, acc = mu + sqrt(var) xi[row][o] (a draw from N(mu, var)); without, mu.
 struct SampleArgs {
-  const float *xi;   // [rows][8] standard normals of this step, or null
+  const float *xi;   // [rows][MixSmem::XIS] standard normals of this step, or null
   // optional per-step trace of the adjoint: for row r < trace_rows and output
   // o, trace[r * trace_stride + trace_off + 5 o + {0..4}] = (d1, var, log2 Z,
   // m, yref) of the evaluation's final pass: the activation anchor m and the
@@ -1296,8 +1389,10 @@ __device__ __forceinline__ void finish_sums(MixSmem<D, MT, NW, PF> &sm, int row,
   const float d1 = s.S1 / s.Z;
   const float mu = sm.yref[row][o] + d1;
   const float var = (fmaxf(s.S2 - s.S1 * d1, 0.f) + s.S3) / s.Z;
-  sm.mean[row][o] = mu;
-  sm.var[row][o] = var;
+  if constexpr (!MixSmem<D, MT, NW, PF>::SH) {
+    sm.mean[row][o] = mu;
+    sm.var[row][o] = var;
+  }
   // the anchor in use is m (base-2 units): sum_j exp(-q_j/2) = 2^m Z.  A
   // redo pass rewrites the trace, so it ends with the final pass's values.
   if (sa.trace && row < sa.trace_rows) {
@@ -1308,7 +1403,7 @@ __device__ __forceinline__ void finish_sums(MixSmem<D, MT, NW, PF> &sm, int row,
     dst[3] = sm.mref[row][o];
     dst[4] = sm.yref[row][o];
   }
-  sm.acc[row][o] = sa.xi ? mu + sqrtf(var) * sa.xi[row * 8 + o] : mu;
+  sm.accel(row, o) = sa.xi ? mu + sqrtf(var) * sa.xi[row * MixSmem<D, MT, NW, PF>::XIS + o] : mu;
   const bool valid = isfinite(s.Z) && isfinite(s.S1) && isfinite(s.S2) && isfinite(s.S3) && s.mx >= kAnchorLo;
   if (!valid) sm.redo[ev & 1] = 1;
   sm.mref[row][o] += s.mx;
@@ -1478,7 +1573,7 @@ __device__ __forceinline__ void mixture_step(const MfmaModel &md, MixSmem<D, MT,
 
 template <int D, int MT, int NW, int PF>
 __device__ __forceinline__ void reset_anchors(MixSmem<D, MT, NW, PF> &sm) {
-  for (int i = threadIdx.x; i < MixSmem<D, MT, NW, PF>::ROWS * kMaxOut; i += NW * 64) {
+  for (int i = threadIdx.x; i < MixSmem<D, MT, NW, PF>::ROWS * MixSmem<D, MT, NW, PF>::NOUT; i += NW * 64) {
     (&sm.mref[0][0])[i] = 0.0f;
     (&sm.yref[0][0])[i] = 0.0f;
     (&sm.mprev[0][0])[i] = 0.0f;
@@ -1555,11 +1650,19 @@ struct RollSmem {
   // steps per noise chunk: 1 for the 128-row shared-tile form (its LDS holds the tile ring)
   static constexpr int CH = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH ? 1 : kNoiseChunk;
   MixSmem<Dims<DYN>::D, MT, NW, PF> sm;
-  float xs[ROWS][Dims<DYN>::NX];
+  // the state, and (COMP) its compensation (euler_step_comp): in the shared-tile
+  // form, whose steps are long beside the rows' serial work
+  static constexpr bool COMP = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH;
+  float xs[ROWS][Dims<DYN>::NX], xlo[COMP ? ROWS : 1][Dims<DYN>::NX];
   float us_s[CH][ROWS][4];           // applied controls u_nom + sigma eps of the chunk
-  float xi_s[CH][ROWS][8];
-  float xc[CH][ROWS][Dims<DYN>::NX];   // x_{t+1} of the chunk's steps, for the costs
+  float xi_s[CH][ROWS][MixSmem<Dims<DYN>::D, MT, NW, PF>::XIS];
+  // x_{t+1} of the chunk's steps, for the costs (chunks of one step: xs)
+  std::conditional_t<CH == 1, char[16], float[CH][ROWS][Dims<DYN>::NX]> xc;
   float obs_s[kMaxObs * 3];
+  // the batched kernel's work item: here, so that the kernel has one LDS object
+  // (with two the compiler waits for every load to LDS in flight before each
+  // LDS read: 16 controllers 42.2 against 34.4 ms)
+  int item;
 };
 
 // Rollouts s_base .. s_base + spw - 1 of one problem for its whole horizon.
@@ -1595,6 +1698,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   constexpr int D = DD::D, NX = DD::NX, NU = DD::NU, NO = DD::NO;
   constexpr int ROWS = 16 * MT;
   constexpr int CH = RollSmem<DYN, MT, NW, PF>::CH;
+  constexpr bool COMP = RollSmem<DYN, MT, NW, PF>::COMP;
   MixSmem<D, MT, NW, PF> &sm = rs.sm;
   constexpr int SEGW = NX + 5 * NO;   // trace row: x_t, then 5 values per output (SampleArgs)
   const int tb = sg ? sg->tb : 0, te = sg ? sg->te : p.T;
@@ -1610,6 +1714,13 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   uint32_t seq = 0;
   __syncthreads();  // the previous tile (persistent use) is done with LDS
   reset_anchors(sm);
+  if constexpr (MixSmem<D, MT, NW, PF>::SH && PF == kPfF16x2) {
+    // some model of the problem carries powers of two
+    if (threadIdx.x == 0) sm.model_scaled = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < md.n_tiles; i += NW * 64)
+      if (md.hmeta[(size_t)i * kHfMeta + kHfPlain] == 0.0f) sm.model_scaled = 1;
+  }
   const int row = threadIdx.x;
   const int64_t s = s_base + row;
   const bool active = row < spw && s < (int64_t)p.K * p.Ms;
@@ -1622,6 +1733,8 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
     } else {
       for (int a = 0; a < NX; ++a) rs.xs[row][a] = x0[a];
     }
+    if constexpr (COMP)
+      for (int a = 0; a < NX; ++a) rs.xlo[row][a] = 0.0f;
     sm.z[row][D] = 1.0f;
     sm.z[row][D + 1] = 0.0f;
   }
@@ -1635,7 +1748,12 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
       const int rr = i / n, cc = i - rr * n;
       const int64_t ss = s_base + rr;
       if (rr >= spw || ss >= (int64_t)p.K * p.Ms) continue;
-      float c = p.dt * state_cost<float>(p, rs.obs_s, rs.xc[cc][rr]);
+      const float *xe;
+      if constexpr (CH == 1)
+        xe = rs.xs[rr];
+      else
+        xe = rs.xc[cc][rr];
+      float c = p.dt * state_cost<float>(p, rs.obs_s, xe);
       if constexpr (DYN == kDynQuadHybrid)
         if (p.ctrl_cost) c += rs.xi_s[cc][rr][7];
       cost[ss * p.T + t0 + cc] = failed ? __builtin_nanf("") : c;
@@ -1680,10 +1798,11 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
           sincos_2pi(unit_open<float>(r4.v[1]), &s0, &c0);
           sincos_2pi(unit_open<float>(r4.v[3]), &s1, &c1);
           float *dst = &rs.xi_s[cc][rr][4 * (blk - 1)];
-          dst[0] = rad0 * c0;
-          dst[1] = rad0 * s0;
-          dst[2] = rad1 * c1;
-          dst[3] = rad1 * s1;
+          const float v[4] = {rad0 * c0, rad0 * s0, rad1 * c1, rad1 * s1};
+          constexpr int XIS = MixSmem<D, MT, NW, PF>::XIS;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (XIS == 8 || 4 * (blk - 1) + i < XIS) dst[i] = v[i];
         }
       }
       __syncthreads();
@@ -1726,17 +1845,24 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
     }
     mixture_step(md, sm, t == tb, T0, T1, pc, seq, sa);
     if (active) {
-      float acc[NO], xn[NX], x[NX], u[NU];
+      float acc[NO], xn[NX], x[NX], lo[NX], u[NU];
 #pragma unroll
-      for (int o = 0; o < NO; ++o) acc[o] = sm.acc[row][o];
+      for (int o = 0; o < NO; ++o) acc[o] = sm.accel(row, o);
 #pragma unroll
-      for (int a = 0; a < NX; ++a) x[a] = rs.xs[row][a];
+      for (int a = 0; a < NX; ++a) {
+        x[a] = rs.xs[row][a];
+        if constexpr (COMP) lo[a] = rs.xlo[row][a];
+      }
       applied(u);
-      euler_step<float>(DYN, p.dt, x, acc, u, xn);
+      if constexpr (COMP)
+        euler_step_comp<float>(DYN, p.dt, x, acc, u, xn, lo);
+      else
+        euler_step<float>(DYN, p.dt, x, acc, u, xn);
 #pragma unroll
       for (int a = 0; a < NX; ++a) {
         rs.xs[row][a] = xn[a];
-        rs.xc[tc][row][a] = xn[a];
+        if constexpr (COMP) rs.xlo[row][a] = lo[a];
+        if constexpr (CH > 1) rs.xc[tc][row][a] = xn[a];
       }
     }
   }
@@ -1802,13 +1928,12 @@ __global__ void __launch_bounds__(NW * 64) rollout_batched_kernel(const BatchedP
                                                                   const BatchedItem *__restrict__ items,
                                                                   int n_items, int *__restrict__ queue) {
   __shared__ RollSmem<DYN, MT, NW, PF> rs;
-  __shared__ int item_s;
   mix_setup(rs.sm);
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) item_s = atomicAdd(queue, 1);
+    if (threadIdx.x == 0) rs.item = atomicAdd(queue, 1);
     __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(item_s);   // uniform: the item's descriptors stay scalar
+    const int item = __builtin_amdgcn_readfirstlane(rs.item);   // uniform: the item's descriptors stay scalar
     if (item >= n_items) break;
     const BatchedItem it = items[item];
     const BatchedProblem &bp = probs[it.b];
