@@ -77,25 +77,27 @@ enum { PI_OBS_INDICATOR = 0, PI_OBS_SMOOTH = 1 };
 enum { PI_W_COST_TO_GO = 0, PI_W_TRAJECTORY = 1 };
 /* Kernel variants.  The matrix-core form (PI_VARIANT_MFMA) needs float32,
  * d in {4, 6, 16} and folded tiles under 2 GiB (about 3 M local models at
- * d = 16); PI_VARIANT_AUTO picks it whenever those hold, and requesting it
- * otherwise returns PI_ERR_UNSUPPORTED.  PI_VARIANT_DIRECT is the per-sample
+ * d = 16); PI_VARIANT_AUTO picks it whenever those hold (rollouts of the 12-state
+ * quadrotor with K max(M,1) > 2048 that leave tile_samples, tile_waves and
+ * tile_split to the library too run PI_VARIANT_MFMA_BF16X3 instead, the same
+ * float32 products), and requesting it otherwise returns PI_ERR_UNSUPPORTED.  PI_VARIANT_DIRECT is the per-sample
  * form (any d, float32 or float64).  PI_VARIANT_MFMA_BF16X3 (rollouts of the
  * float32 12-state quadrotor, d = 16; 8 waves need tiles of <= 16) runs the same
  * contraction on the bf16 matrix instructions: every float32 operand is the
  * exact sum of three bf16 pieces and the six piece products of weight at
  * least 2^-24 are summed in float32, which reproduces the float32 products
  * to within float32 rounding.  With it, tiles of 33..128 samples select the
- * shared-tile launch: 128 rows, 16 per wave on 8 waves or 32 on 4, and the
- * workgroup stages every model tile once in LDS (for problems with many
- * rollouts).  PI_VARIANT_MFMA_F16X2 (the same rollouts and launch shapes)
+ * shared-tile launch: 128 rows on 8 or 4 waves (64 rows for tiles of up to 64
+ * on 4 waves), and the workgroup stages every model tile once in LDS (for
+ * problems with many rollouts).  PI_VARIANT_MFMA_F16X2 (the same rollouts and launch shapes)
  * runs it on the fp16 matrix instructions: each model's coefficients and
  * each sample row's features are scaled by powers of two that keep them
  * below 2^14, every scaled value is the sum of two fp16 pieces (hi, lo; lo
  * may be subnormal) and the three piece products hi hi, hi lo, lo hi are
  * summed in float32, half the products of the bf16 form, to about 2^-22
  * relative per product; the scales are undone exactly in float32.  For
- * both, tile_samples 0 means the shared tile (128 samples, 8 waves) when
- * K max(M,1) >= 32768, else the 16-sample tiles.  Neither form has a
+ * both, tile_samples 0 lets the library pick tiles of 16, 32, 64 or 128
+ * samples from K max(M,1) and the number of local models.  Neither form has a
  * prediction entry point (lwpr_predict: PI_ERR_UNSUPPORTED).                */
 enum { PI_VARIANT_AUTO = 0, PI_VARIANT_DIRECT = 1, PI_VARIANT_MFMA = 2, PI_VARIANT_MFMA_BF16X3 = 3,
        PI_VARIANT_MFMA_F16X2 = 4 };
@@ -160,9 +162,8 @@ typedef struct {
                                     * pair of workgroups, on two compute units,
                                     * each runs half and they exchange partial
                                     * sums every step); 0 = library's choice:
-                                    * 2 when the problem has fewer tiles than
-                                    * the device has compute units and the
-                                    * pairs fit on the device at once.  Float32
+                                    * 2 when the device has a compute unit for
+                                    * each workgroup of the pairs.  Float32
                                     * matrix-core rollouts with tile_samples
                                     * <= 16 (4 waves, or 8 for the quadrotor)
                                     * only; otherwise 1.                       */

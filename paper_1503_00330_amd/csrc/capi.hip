@@ -240,24 +240,85 @@ struct RolloutPlan {
 };
 
 constexpr int64_t kMaxPairGroups = 2048;
-constexpr int64_t kSharedTileMinSamples = 128 * 256;
+// Rollouts up to which the float32 16-row pairs of workgroups cover a 256-unit
+// device once.
+constexpr int64_t kPairFullSamples = 16 * 128;
+
+// Whether a problem that leaves the whole launch to the library (contraction,
+// tile, waves, pairing) runs the three-piece bf16 contraction: the float32
+// quadrotor past the pairs' range.  Its products are the float32 ones to
+// float32 rounding and it carries the state's rounding errors, so its costs are
+// the nearer ones (2100..3000 rollouts x 30..100 steps against float64: 0.9e-7..
+// 1.7e-7 of the costs, the float32 products' 1.2e-7..6.3e-7), and it is faster
+// (61 steps, 6 x 256 models, best launch of each: 1.06 against 1.30 ms at 2100
+// rollouts, 3.07 against 4.7 ms at 16384).
+bool auto_pieces(const pi_problem *p, const pi_lwpr *m, int64_t n) {
+  return p->variant == PI_VARIANT_AUTO && p->tile_samples == 0 && p->tile_waves == 0 && p->tile_split == 0 &&
+         p->dyn == PI_DYN_QUAD12 && n > kPairFullSamples && bf_model_ok(m);
+}
+
+// Tile (and waves) of a pieces-form problem that leaves its tile to the
+// library: the launch with the least time per step on 256 compute units, as
+// (passes over the device) x (a + b model tiles), a and b in microseconds
+// fitted to 61-step launches of 6 x 64, 6 x 256 and 6 x 1024 models (24, 96 and
+// 384 tiles; fitted within 15 %):
+//              fp16 pieces          bf16 pieces          rollouts per pass
+//   16 rows    2.6 + 0.105 t        1.0 + 0.164 t        4096 (8192 in halves)
+//   32 rows    7.5 + 0.142 t        5.5 + 0.219 t        8192
+//   64 rows   12.3 + 0.259 t       13.0 + 0.406 t        16384
+//   128 rows  16.8 + 0.344 t (8 waves)   11.6 + 0.627 t (8), 13 + 0.722 t (4)   32768
+// e.g. 16384 rollouts, fp16, 96 tiles: 48 (measured), 40, 37 and 49 us per step.
+struct TileChoice {
+  int spw, waves;
+};
+TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles) {
+  struct Form {
+    int spw, waves;
+    int64_t pass;
+    double a, b;
+  };
+  static const Form kF16[] = {{16, 4, 4096, 2.6, 0.105}, {32, 4, 8192, 7.5, 0.142}, {64, 4, 16384, 12.3, 0.259},
+                              {128, 8, 32768, 16.8, 0.344}};
+  static const Form kB16[] = {{16, 4, 4096, 1.0, 0.164}, {32, 4, 8192, 5.5, 0.219}, {64, 4, 16384, 13.0, 0.406},
+                              {128, 8, 32768, 11.6, 0.627}, {128, 4, 32768, 13.0, 0.722}};
+  const bool hf = pf == kPfF16x2;
+  const Form *f = hf ? kF16 : kB16;
+  const int nf = hf ? 4 : 5;
+  TileChoice best{16, 4};
+  double t_best = 0;
+  for (int i = 0; i < nf; ++i) {
+    // a caller's 8 waves run tiles of 16 or 128 rows; its 4, or the library's
+    // choice for PI_VARIANT_AUTO, no 8-wave launch
+    if (waves == 8 ? (f[i].spw == 32 || f[i].spw == 64 || (f[i].spw == 128 && f[i].waves == 4))
+                   : waves == 4 && f[i].waves == 8 && !hf)
+      continue;
+    const double t = (double)((n + f[i].pass - 1) / f[i].pass) * (f[i].a + f[i].b * n_tiles);
+    if (i == 0 || t < t_best) {
+      t_best = t;
+      best = TileChoice{f[i].spw, waves > 0 ? waves : f[i].waves};
+    }
+  }
+  return best;
+}
 
 RolloutPlan rollout_plan(const pi_problem *p, const pi_lwpr *m) {
   RolloutPlan r;
-  r.pf = variant_pf(p->variant);
+  const int64_t n = (int64_t)p->K * (p->M > 0 ? p->M : 1);
+  const bool auto_bf = auto_pieces(p, m, n);
+  r.pf = auto_bf ? kPfBf16x3 : variant_pf(p->variant);
   r.mfma = p->variant == PI_VARIANT_MFMA || r.pf != kPfF32 || (p->variant == PI_VARIANT_AUTO && mfma_model_ok(m));
   r.bf = r.pf != kPfF32;
-  const int64_t n = (int64_t)p->K * (p->M > 0 ? p->M : 1);
-  // the pieces forms' default for problems that fill a 256-unit device with
-  // 128-sample tiles: the shared-tile launch on 8 waves
-  const bool shared = r.bf && p->tile_samples == 0 && n >= (int64_t)kSharedTileMinSamples;
-  r.waves = p->tile_waves > 0 ? p->tile_waves : shared ? 8 : 4;
+  TileChoice tile{16, 4};
+  if (r.bf && p->tile_samples == 0 && p->dyn == PI_DYN_QUAD12 && bf_model_ok(m))
+    tile = pieces_tile(r.pf, auto_bf ? 4 : p->tile_waves, n, mfma_layout(m->d, m->n_out, m->L_off).n_tiles);
+  const bool large = tile.spw > 16;
+  r.waves = p->tile_waves > 0 ? p->tile_waves : large ? tile.waves : 4;
   const bool split_allowed = r.mfma && (r.waves == 4 || (r.waves == 8 && p->dyn == PI_DYN_QUAD12)) &&
                              p->tile_split != 1 && p->dtype == PI_F32;
   if (p->tile_samples > 0) {
     r.spw = p->tile_samples;
-  } else if (shared) {
-    r.spw = 128;
+  } else if (large) {
+    r.spw = tile.spw;
   } else if (split_allowed) {
     r.spw = 16;   // full 16-row tiles; small problems are spread by pairing
   } else {
@@ -293,8 +354,10 @@ int device_cus(int *dev_out = nullptr) {
   return n_cu;
 }
 
-// Pairing at launch: requested (tile_split 2) or, by default, when the tiles
-// leave compute units idle; in both cases only if the whole grid is resident.
+// Pairing at launch: requested (tile_split 2) or, by default, when the pairs
+// still find a compute unit each (past that the units that hold two workgroups
+// set the pace: 3000 rollouts of 6 x 256 models, 61 steps, 1.46 ms in pairs,
+// 1.31 ms without); in both cases only if the whole grid is resident.
 bool use_pair(const pi_problem *p, const RolloutPlan &pl) {
   if (!pl.pair_ok) return false;
   int dev = 0;
@@ -315,7 +378,7 @@ bool use_pair(const pi_problem *p, const RolloutPlan &pl) {
   }
   const bool resident = (int64_t)pair_grid(pl.groups) <= (int64_t)cap * n_cu;
   if (!resident) return false;
-  return p->tile_split == 2 || pl.groups < n_cu;
+  return p->tile_split == 2 || 2 * pl.groups <= n_cu;
 }
 
 // The rollout launch on the current device: the plan, whether its tiles are

@@ -239,6 +239,48 @@ __device__ __forceinline__ Real state_cost(const ProbDev<Real> &p, const Real *o
   return c;
 }
 
+// The same cost by four consecutive lanes: lane q = 0..3 takes every fourth
+// obstacle; every lane returns the row's cost.  The state is read whole and the
+// obstacles four at a time, so their LDS reads go out together.
+template <typename Real, int DYN>
+__device__ __forceinline__ Real state_cost_quad(const ProbDev<Real> &p, const Real *obs, const Real *x, int q) {
+  constexpr int np = DYN == kDynPointMass2D ? 2 : 3, nr = DYN == kDynPointMass2D ? 4 : 9;
+  Real xx[nr];
+#pragma unroll
+  for (int a = 0; a < nr; ++a) xx[a] = x[a];
+  Real c = 0, ob = 0;
+#pragma unroll
+  for (int a = 0; a < np; ++a) {
+    const Real e = xx[a] - p.goal[a];
+    c += p.w_pos[a] * e * e;
+  }
+#pragma unroll
+  for (int a = 0; a < np; ++a) c += p.w_vel * xx[np + a] * xx[np + a];
+  if constexpr (DYN != kDynPointMass2D)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) c += p.w_ang * xx[6 + a] * xx[6 + a];
+  const bool smooth = p.obs_kind != kObsIndicator;
+  for (int i0 = q; i0 < p.n_obs; i0 += 16) {
+    Real d[4], r[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = min(i0 + 4 * j, p.n_obs - 1);
+      const Real dx = xx[0] - obs[3 * i], dy = xx[1] - obs[3 * i + 1];
+      d[j] = dx * dx + dy * dy;
+      r[j] = obs[3 * i + 2];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i0 + 4 * j >= p.n_obs) continue;
+      ob += smooth ? p.obs_penalty * exp_(-p.obs_decay * d[j]) : (d[j] < r[j] * r[j] ? (Real)1 : (Real)0);
+    }
+  }
+  ob += __shfl_xor(ob, 1);
+  ob += __shfl_xor(ob, 2);
+  if (smooth) return c + ob;
+  return ob > (Real)0 ? c + p.obs_penalty : c;
+}
+
 // Control terms of the cost-to-go S-tilde (Sec. 3.1, below Eq. 2) for one step
 // of the hybrid model, whose commanded rates are its control-affine channel:
 // G_c = kRateGain I and the noise enters through the same channel, B dw =

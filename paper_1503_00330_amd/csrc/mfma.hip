@@ -322,6 +322,26 @@ __device__ __forceinline__ Acc acc_sum(const Acc &a, const Acc &b) {
   return Acc{a.Z + b.Z, a.S1 + b.S1, a.S2 + b.S2, a.S3 + b.S3, fmaxf(a.mx, b.mx)};
 }
 
+// The sums of the four lane groups that hold the same sample (lanes l, l + 16,
+// l + 32, l + 48), in every lane: (g0 + g1) + (g2 + g3).  The row and half-wave
+// swaps stay in the vector ALU, where shuffles are two dependent LDS round trips
+// per sum.
+__device__ __forceinline__ Acc sum_groups(Acc s) {
+  auto fold = [](float v, auto op) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float h = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(h), __float_as_uint(h), false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  };
+  auto add = [](float x, float y) { return x + y; };
+  s.Z = fold(s.Z, add);
+  s.S1 = fold(s.S1, add);
+  s.S2 = fold(s.S2, add);
+  s.S3 = fold(s.S3, add);
+  s.mx = fold(s.mx, [](float x, float y) { return fmaxf(x, y); });
+  return s;
+}
+
 // BF (a pieces form): the samples' fragments as pieces (d = 16): per row
 // tile, 32-feature block and piece, 64 lanes x 8 bf16 (16 bytes per lane,
 // kept in the float4 slots), sample lane%16, features 8 (lane/16) .. +7.
@@ -335,7 +355,7 @@ template <int D, int MT, int NW, int PF = 0>
 struct MixSmem {
   static constexpr bool BF = PF != kPfF32;
   static constexpr bool SH = BF && MT > 2;
-  static_assert(!BF || (D == kBfD && (MT <= 2 || MT == 8)), "the pieces forms cover d = 16, one or two row tiles per wave");
+  static_assert(!BF || (D == kBfD && (MT <= 2 || MT == 4 || MT == 8)), "the pieces forms cover d = 16");
   static constexpr int NPC = PF == kPfF16x2 ? 2 : 3;   // pieces per value
   static constexpr int ROWS = 16 * MT;
   static constexpr int NFRAG = BF ? kBfNKB * NPC : Geo<D>::KB4;   // 16-byte fragments per lane and row tile
@@ -583,14 +603,7 @@ __device__ __forceinline__ void mixture_tiles(const MfmaModel &md, MixSmem<D, MT
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       Acc s = acc_sum(acc_sum(st[mt][0], st[mt][1]), acc_sum(st[mt][2], st[mt][3]));
-#pragma unroll
-      for (int m = 16; m <= 32; m <<= 1) {
-        s.Z += __shfl_xor(s.Z, m);
-        s.S1 += __shfl_xor(s.S1, m);
-        s.S2 += __shfl_xor(s.S2, m);
-        s.S3 += __shfl_xor(s.S3, m);
-        s.mx = fmaxf(s.mx, __shfl_xor(s.mx, m));
-      }
+      s = sum_groups(s);
       if (lane < 16) sm.part[wave][oo][16 * mt + lane] = s;
 #pragma unroll
       for (int i = 0; i < 4; ++i) st[mt][i] = acc_empty();
@@ -793,14 +806,7 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       Acc s = acc_sum(acc_sum(st[mt][0], st[mt][1]), acc_sum(st[mt][2], st[mt][3]));
-#pragma unroll
-      for (int m = 16; m <= 32; m <<= 1) {
-        s.Z += __shfl_xor(s.Z, m);
-        s.S1 += __shfl_xor(s.S1, m);
-        s.S2 += __shfl_xor(s.S2, m);
-        s.S3 += __shfl_xor(s.S3, m);
-        s.mx = fmaxf(s.mx, __shfl_xor(s.mx, m));
-      }
+      s = sum_groups(s);
       if (lane < 16) sm.part[wave][oo][16 * mt + lane] = s;
 #pragma unroll
       for (int i = 0; i < 4; ++i) st[mt][i] = acc_empty();
@@ -983,21 +989,20 @@ __device__ __forceinline__ void static_for(F &f) {
   }
 }
 
-// The shared-tile form of the pieces stage (MixSmem::SH): 128 rows in groups of
-// 16 RT, every wave holding the pieces of one group.  With two row tiles per
+// The shared-tile form of the pieces stage (MixSmem::SH): 128 or 64 rows in
+// groups of 16 RT, every wave holding the pieces of one group.  With two row tiles per
 // wave each model piece read from LDS serves two products; the workgroup reads
 // each model tile from L2 once per step: the tile's piece chunks go straight
 // from memory into an LDS ring (buffer loads to LDS, each wave issuing every
-// NW-th chunk).  The tiles go in stages of two.  Four waves (and eight with
-// one row tile each, the bf16 form) run both tiles of a stage; eight waves of
-// two row tiles take one tile of the stage each, waves w and w + 4 (one SIMD)
-// holding the same rows, their sums meeting in the merge.  Three stages fit the
+// NW-th chunk).  The tiles go in stages of two.  Where the waves just cover the
+// rows each runs both tiles of a stage; where two waves hold the same rows
+// (TS = 2: 64 rows on four waves, 128 on eight of two row tiles each) they take
+// one tile of the stage each and their sums meet in the merge.  Three stages fit the
 // ring: a stage's loads are issued two stages ahead, spread over the products
 // of the stage in hand (all at once after the barrier they held every wave up
-// for about 400 cycles), and are complete one stage before their use, so a
-// wave reads its next tile's first blocks before the barrier.  Per stage a wave
-// waits for its own loads of the next stage and then for the other waves at a
-// barrier: past it every wave is done with the slots the next loads overwrite.
+// for about 400 cycles).  Per stage a wave waits for its own loads and then for
+// the other waves at a barrier: past it the stage is complete and every wave is
+// done with the slots the next loads overwrite.
 //
 // Bound: the matrix pipe (36 fp16 products of 16 cycles per wave and tile) and,
 // with it, the card's power: its clock falls as the pipe fills.  A product
@@ -1014,7 +1019,7 @@ __device__ __forceinline__ void static_for(F &f) {
 template <int D, int MT, int NW, int PF>
 __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D, MT, NW, PF> &sm, int T0, int T1) {
   using SM = MixSmem<D, MT, NW, PF>;
-  static_assert(SM::SH && MT == 8 && (NW == 4 || NW == 8), "shared-tile form: 128 rows on four or eight waves");
+  static_assert(SM::SH && (NW == 4 || (NW == 8 && MT == 8)), "shared-tile form: 64 rows on four, 128 on four or eight waves");
   using G = Geo<D>;
   constexpr bool HF = PF == kPfF16x2;   // two fp16 pieces (else three bf16 pieces)
   constexpr int NPC = SM::NPC;
@@ -1022,6 +1027,10 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   constexpr int RG = MT / RT;    // row groups
   constexpr int TS = SM::TS;     // waves per row group: each takes every TS-th tile
   static_assert(RG * TS == NW && (TS == 1 || TS == 2), "shared-tile form: the waves cover the rows");
+  // two waves per SIMD: a stage outlasts its loads, so all of them are waited
+  // for, and the next tile's first blocks are read before the barrier; one wave
+  // per SIMD: the loads get two stages, the first reads wait behind the barrier
+  constexpr bool XB = NW == 8;
   constexpr int FQ = G::NP + D + 1, KQA = FQ / 32, GQA = (FQ % 32) / 8, IQA = FQ % 8;
   constexpr int FY = D + 1, KYA = kBfNKQ + FY / 32, GYA = (FY % 32) / 8, IYA = FY % 8;
   constexpr int kTileBytes = kBfNKB * NPC * 1024;
@@ -1105,38 +1114,42 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       }
     }
   }
-  auto output_of = [&](int tile) {
-    int oo = 0;
+  // the output of a tile and the first tile past it: every output has a tile,
+  // so tile_off grows up to n_tiles; scalar selects only
+  auto locate = [&](int tile, int &oo, int &nb) {
 #pragma unroll
-    for (int i = 1; i < kMaxOut; ++i) oo += (i < md.n_out && md.tile_off[i] <= tile) ? 1 : 0;
-    return oo;
-  };
-  auto next_boundary = [&](int tile) {
-    int nb = md.n_tiles;
-#pragma unroll
-    for (int i = 1; i <= kMaxOut; ++i) {
-      const int v = md.tile_off[i];
-      nb = (v > tile && v < nb) ? v : nb;
+    for (int i = kMaxOut; i >= 1; --i) {
+      const bool past = md.tile_off[i] > tile;
+      nb = past ? md.tile_off[i] : nb;
+      oo = past ? i - 1 : oo;
     }
-    return nb;
+    oo = __builtin_amdgcn_readfirstlane(oo);
+    nb = __builtin_amdgcn_readfirstlane(nb);
   };
-  auto put = [&](u32x4 (&v)[NPC], auto I, float x, int mt) {
-    constexpr int i = decltype(I)::value;
-    uint16_t pc[3];
-    split(x, mt, pc);
-#pragma unroll
-    for (int p = 0; p < NPC; ++p) {
-      uint32_t w = v[p][i / 2];
-      w = (i & 1) ? ((w & 0x0000FFFFu) | ((uint32_t)pc[p] << 16)) : ((w & 0xFFFF0000u) | pc[p]);
-      v[p][i / 2] = w;
-    }
-  };
+  // output oo's anchors into their feature slots: one LDS round trip, and a
+  // select instead of a branch for the lanes that hold the slots
   auto set_anchor = [&](int oo) {
+    float m[RT], y[RT];
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
-      const int row = row0 + 16 * mt;
-      if ((lane >> 4) == GQA) put(Bs[mt][KQA], std::integral_constant<int, IQA>{}, -sm.mref[row][oo], mt);
-      if ((lane >> 4) == GYA) put(Bs[mt][KYA], std::integral_constant<int, IYA>{}, -sm.yref[row][oo], mt);
+      m[mt] = sm.mref[row0 + 16 * mt][oo];
+      y[mt] = sm.yref[row0 + 16 * mt][oo];
+    }
+    auto put = [&](u32x4 (&v)[NPC], auto I, bool mine, float x, int mt) {
+      constexpr int i = decltype(I)::value;
+      uint16_t pc[3];
+      split(x, mt, pc);
+#pragma unroll
+      for (int p = 0; p < NPC; ++p) {
+        const uint32_t w = v[p][i / 2];
+        const uint32_t n = (i & 1) ? ((w & 0x0000FFFFu) | ((uint32_t)pc[p] << 16)) : ((w & 0xFFFF0000u) | pc[p]);
+        v[p][i / 2] = mine ? n : w;
+      }
+    };
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt) {
+      put(Bs[mt][KQA], std::integral_constant<int, IQA>{}, (lane >> 4) == GQA, -m[mt], mt);
+      put(Bs[mt][KYA], std::integral_constant<int, IYA>{}, (lane >> 4) == GYA, -y[mt], mt);
     }
   };
   // sums over the lane's models 4 (lane/16) + i: one per i, or (eight waves,
@@ -1155,14 +1168,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     for (int mt = 0; mt < RT; ++mt) {
       Acc s = acc_sum(st[mt][0], st[mt][1]);
       if constexpr (NS == 4) s = acc_sum(s, acc_sum(st[mt][2], st[mt][3]));
-#pragma unroll
-      for (int m = 16; m <= 32; m <<= 1) {
-        s.Z += __shfl_xor(s.Z, m);
-        s.S1 += __shfl_xor(s.S1, m);
-        s.S2 += __shfl_xor(s.S2, m);
-        s.S3 += __shfl_xor(s.S3, m);
-        s.mx = fmaxf(s.mx, __shfl_xor(s.mx, m));
-      }
+      s = sum_groups(s);
       if (lane < 16) sm.part[half][oo][row0 + 16 * mt] = s;
     }
     clear_sums();
@@ -1237,16 +1243,22 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   int o = 0, nb = 0;
   // the products of one tile (piece chunks W) into set c, the epilogue of the
   // tile before from set p, (LD) the loads of stage st_ld into ring stage
-  // `ring_ld`, and the first blocks of the next tile (Wn)
-  auto body = [&](int tile, const u32x4(*W)[64], const u32x4(*Wn)[64], int st_ld, int ring_ld, auto LD, auto CI,
-                  auto PI, auto SC) {
+  // `ring_ld`, and (NEXT) the first blocks of the next tile (Wn); PRE: this
+  // tile's were read so
+  auto body = [&](int tile, const u32x4(*W)[64], const u32x4(*Wn)[64], int st_ld, int ring_ld, auto LD, auto PRE,
+                  auto NEXT, auto CI, auto PI, auto SC) {
     constexpr int c = decltype(CI)::value;
+    if constexpr (!decltype(PRE)::value) {
+      ldb(W, 0);
+      ldb(W, 1);
+    }
     if (tile >= nb) {
-      epi_all(PI, SC);
-      clear_pending(PI);
-      if (nb > 0) flush(o);
-      o = output_of(tile);
-      nb = next_boundary(tile);
+      if (nb > 0) {
+        epi_all(PI, SC);
+        clear_pending(PI);
+        flush(o);
+      }
+      locate(tile, o, nb);
       set_anchor(o);
     }
     constexpr int NPR = HF ? 3 : 6;
@@ -1264,7 +1276,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       if constexpr (r == 0) {
         if constexpr (kb + 2 < kBfNKB)
           ldb(W, kb + 2);
-        else
+        else if constexpr (decltype(NEXT)::value)
           ldb(Wn, kb + 2 - kBfNKB);
       }
       if constexpr (sl == 0) {   // for the epilogue, one tile later
@@ -1295,10 +1307,12 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
+  using Yes = std::true_type;
+  using Cross = std::integral_constant<bool, XB>;
   auto enter = [&]() {
-    // this wave's loads are complete; no memory access moves across the barrier
-    // (compiler fences on both sides)
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), expcnt and lgkmcnt untouched
+    // this wave's loads are complete (all, or all but the latest stage's); no
+    // memory access moves across the barrier (compiler fences on both sides)
+    __builtin_amdgcn_s_waitcnt(XB ? 0x0F70 : 0x0F70 | kLoads);   // vmcnt(0 or kLoads), expcnt and lgkmcnt untouched
     __asm__ __volatile__("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
@@ -1310,22 +1324,24 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     auto next = [&](int r) { return r + 1 == NSTG ? 0 : r + 1; };
     clear_pending(I1{});
     enter();
-    ldb(W(0, half), 0);
-    ldb(W(0, half), 1);
+    if constexpr (XB) {
+      ldb(W(0, half), 0);
+      ldb(W(0, half), 1);
+    }
     int ring = 0, done = 0;   // ring stage of the stage in hand; tiles this wave has run
     // one stage: the loads go to the stage whose ring slots the last barrier freed
     auto stage = [&](int st_i, auto CI, auto PI) {
       const int r1 = next(ring), rl = next(r1), sl = st_i + 2;
       if constexpr (TS == 2) {
         if (2 * st_i + half < n) {
-          body(T0 + 2 * st_i + half, W(ring, half), W(r1, half), sl, rl, std::true_type{}, CI, PI, SC);
+          body(T0 + 2 * st_i + half, W(ring, half), W(r1, half), sl, rl, Yes{}, Cross{}, Cross{}, CI, PI, SC);
           ++done;
         }
       } else {
-        body(T0 + 2 * st_i, W(ring, 0), W(ring, 1), sl, rl, std::true_type{}, CI, PI, SC);
+        body(T0 + 2 * st_i, W(ring, 0), W(ring, 1), sl, rl, Yes{}, Cross{}, Yes{}, CI, PI, SC);
         ++done;
         if (2 * st_i + 1 < n) {
-          body(T0 + 2 * st_i + 1, W(ring, 1), W(r1, 0), n_st, rl, std::false_type{}, PI, CI, SC);
+          body(T0 + 2 * st_i + 1, W(ring, 1), W(r1, 0), n_st, rl, std::false_type{}, Yes{}, Cross{}, PI, CI, SC);
           ++done;
         }
       }
@@ -1647,17 +1663,21 @@ constexpr int kNoiseChunk = 16;   // steps of noise drawn ahead into LDS
 template <int DYN, int MT, int NW, int PF = 0>
 struct RollSmem {
   static constexpr int ROWS = 16 * MT;
-  // steps per noise chunk: 1 for the 128-row shared-tile form (its LDS holds the tile ring)
-  static constexpr int CH = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH ? 1 : kNoiseChunk;
+  // steps per noise chunk, and whether the costs wait for the end of the chunk
+  // too: the shared-tile form, whose LDS holds the tile ring, draws four steps
+  // ahead (one where the ring fills it: 128 rows of bf16 pieces) and evaluates
+  // each step's costs at once, four lanes to a row
+  static constexpr bool SH = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH;
+  static constexpr int CH = !SH ? kNoiseChunk : PF == kPfBf16x3 && MT == 8 ? 1 : 4;
   MixSmem<Dims<DYN>::D, MT, NW, PF> sm;
   // the state, and (COMP) its compensation (euler_step_comp): in the shared-tile
   // form, whose steps are long beside the rows' serial work
-  static constexpr bool COMP = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH;
+  static constexpr bool COMP = PF == kPfBf16x3 || MixSmem<Dims<DYN>::D, MT, NW, PF>::SH;
   float xs[ROWS][Dims<DYN>::NX], xlo[COMP ? ROWS : 1][Dims<DYN>::NX];
   float us_s[CH][ROWS][4];           // applied controls u_nom + sigma eps of the chunk
   float xi_s[CH][ROWS][MixSmem<Dims<DYN>::D, MT, NW, PF>::XIS];
-  // x_{t+1} of the chunk's steps, for the costs (chunks of one step: xs)
-  std::conditional_t<CH == 1, char[16], float[CH][ROWS][Dims<DYN>::NX]> xc;
+  // x_{t+1} of the chunk's steps, for the costs (the shared-tile form: xs)
+  std::conditional_t<SH, char[16], float[CH][ROWS][Dims<DYN>::NX]> xc;
   float obs_s[kMaxObs * 3];
   // the batched kernel's work item: here, so that the kernel has one LDS object
   // (with two the compiler waits for every load to LDS in flight before each
@@ -1698,7 +1718,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   constexpr int D = DD::D, NX = DD::NX, NU = DD::NU, NO = DD::NO;
   constexpr int ROWS = 16 * MT;
   constexpr int CH = RollSmem<DYN, MT, NW, PF>::CH;
-  constexpr bool COMP = RollSmem<DYN, MT, NW, PF>::COMP;
+  constexpr bool COMP = RollSmem<DYN, MT, NW, PF>::COMP, SH = RollSmem<DYN, MT, NW, PF>::SH;
   MixSmem<D, MT, NW, PF> &sm = rs.sm;
   constexpr int SEGW = NX + 5 * NO;   // trace row: x_t, then 5 values per output (SampleArgs)
   const int tb = sg ? sg->tb : 0, te = sg ? sg->te : p.T;
@@ -1743,26 +1763,35 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   // consecutive steps per row so the stores coalesce
   auto flush_costs = [&](int t0, int n) {
     if (!writer || cost == nullptr) return;
+    if constexpr (SH) {
+      // the step's costs from rs.xs, the obstacles of a row over four lanes
+      for (int i = threadIdx.x; i < ROWS * 4; i += NW * 64) {
+        const int rr = i >> 2, q = i & 3;
+        const float c = state_cost_quad<float, DYN>(p, rs.obs_s, rs.xs[rr], q);
+        const int64_t ss = s_base + rr;
+        if (q == 0 && rr < spw && ss < (int64_t)p.K * p.Ms) cost[ss * p.T + t0] = p.dt * c;
+      }
+    } else {
     const bool failed = sm.pair_fail != 0;
     for (int i = threadIdx.x; i < ROWS * n; i += NW * 64) {
       const int rr = i / n, cc = i - rr * n;
       const int64_t ss = s_base + rr;
       if (rr >= spw || ss >= (int64_t)p.K * p.Ms) continue;
-      const float *xe;
-      if constexpr (CH == 1)
-        xe = rs.xs[rr];
-      else
-        xe = rs.xc[cc][rr];
-      float c = p.dt * state_cost<float>(p, rs.obs_s, xe);
+      float c = p.dt * state_cost<float>(p, rs.obs_s, rs.xc[cc][rr]);
       if constexpr (DYN == kDynQuadHybrid)
         if (p.ctrl_cost) c += rs.xi_s[cc][rr][7];
       cost[ss * p.T + t0 + cc] = failed ? __builtin_nanf("") : c;
     }
+    }
   };
   for (int t = tb; t < te; ++t) {
     const int tc = (t - tb) % CH;
+    if (SH && t > tb) {
+      __syncthreads();  // the step's states are in rs.xs
+      flush_costs(t - 1, 1);
+    }
     if (tc == 0) {
-      if (t > tb) {
+      if (t > tb && !SH) {
         __syncthreads();  // the chunk's states are in rs.xc
         flush_costs(t - CH, CH);
         // the control terms of the flushed chunk are read from the draw slots
@@ -1776,7 +1805,9 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
         const int64_t ss = s_base + rr;
         const bool act = rr < spw && ss < (int64_t)p.K * p.Ms && t + cc < te;
         if (!act) continue;
-        const uint32_t kk = (uint32_t)(ss / p.Ms), mm = (uint32_t)(ss % p.Ms);
+        // K max(M, 1) < 2^31: the 64-bit division would cost more than the draw
+        const uint32_t kk = p.Ms == 1 ? (uint32_t)ss : (uint32_t)ss / (uint32_t)p.Ms;
+        const uint32_t mm = (uint32_t)ss - kk * (uint32_t)p.Ms;
         if (blk == 0) {
           float e4[4], pert[NU];
           normals<float, 4>(p.key0, p.key1, wc, kk, 0u, (uint32_t)(t + cc), e4);
@@ -1862,7 +1893,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
       for (int a = 0; a < NX; ++a) {
         rs.xs[row][a] = xn[a];
         if constexpr (COMP) rs.xlo[row][a] = lo[a];
-        if constexpr (CH > 1) rs.xc[tc][row][a] = xn[a];
+        if constexpr (!SH) rs.xc[tc][row][a] = xn[a];
       }
     }
   }
@@ -1871,7 +1902,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
     for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(te - tb) * SEGW + a] = rs.xs[row][a];
   }
   __syncthreads();
-  const int tl = tb + ((te - tb - 1) / CH) * CH;
+  const int tl = SH ? te - 1 : tb + ((te - tb - 1) / CH) * CH;
   flush_costs(tl, te - tl);
 }
 
@@ -1963,15 +1994,15 @@ static hipError_t rollout_mfma_t(const RolloutArgs<float> &ra, const MfmaModel &
   return hipGetLastError();
 }
 
-// A pieces form's plain launch: the shared tile for tiles of 33..128 rows (128
-// rows, two row tiles on each of 4 waves or one on each of 8), else one or two
-// 16-row tiles per wave.
+// A pieces form's plain launch: the shared tile for tiles of 33..128 rows (of
+// 64 rows up to 64 on 4 waves, else of 128), else one or two 16-row tiles per
+// wave.
 template <int PF>
 static hipError_t rollout_pieces_t(const RolloutArgs<float> &ra, const MfmaModel &md, int spw, int waves,
                                    hipStream_t s) {
-  if (spw > 32)
-    return waves == 8 ? rollout_mfma_t<kDynQuad12, 8, 8, PF>(ra, md, spw, s)
-                      : rollout_mfma_t<kDynQuad12, 8, 4, PF>(ra, md, spw, s);
+  if (spw > 32 && waves == 8) return rollout_mfma_t<kDynQuad12, 8, 8, PF>(ra, md, spw, s);
+  if (spw > 64) return rollout_mfma_t<kDynQuad12, 8, 4, PF>(ra, md, spw, s);
+  if (spw > 32) return rollout_mfma_t<kDynQuad12, 4, 4, PF>(ra, md, spw, s);
   if (waves == 8) return rollout_mfma_t<kDynQuad12, 1, 8, PF>(ra, md, spw, s);
   if (spw <= 16) return rollout_mfma_t<kDynQuad12, 1, 4, PF>(ra, md, spw, s);
   return rollout_mfma_t<kDynQuad12, 2, 4, PF>(ra, md, spw, s);
@@ -2095,8 +2126,11 @@ static void batched_pieces_t(const BatchedProblem *probs, const BatchedItem *ite
     if (waves == 8)
       hipLaunchKernelGGL((rollout_batched_kernel<kDynQuad12, 8, 8, PF>), dim3(grid), dim3(512), 0, s, probs, items,
                          n_items, queue);
-    else
+    else if (max_spw > 64)
       hipLaunchKernelGGL((rollout_batched_kernel<kDynQuad12, 8, 4, PF>), dim3(grid), dim3(256), 0, s, probs, items,
+                         n_items, queue);
+    else
+      hipLaunchKernelGGL((rollout_batched_kernel<kDynQuad12, 4, 4, PF>), dim3(grid), dim3(256), 0, s, probs, items,
                          n_items, queue);
   } else if (waves == 8) {
     hipLaunchKernelGGL((rollout_batched_kernel<kDynQuad12, 1, 8, PF>), dim3(grid), dim3(512), 0, s, probs, items,
