@@ -831,7 +831,9 @@ pi_status lwpr_predict(const pi_lwpr *m, const void *Z, int64_t N, void *mean, v
   hipError_t e = folded_base(m, use_mfma, ws, s, &base);
   if (e == hipSuccess) {
     if (use_mfma)
-      e = launch_predict_mfma(a, mfma_layout(m->d, m->n_out, m->L_off), base, Z, N, mean, var, s);
+      // left to the library: the bf16 pieces, float32 products to float32 rounding
+      e = launch_predict_mfma(a, mfma_layout(m->d, m->n_out, m->L_off), base, Z, N, mean, var,
+                              variant == PI_VARIANT_AUTO && bf_model_ok(m), s);
     else
       e = launch_predict_direct(m->dtype, a, base, Z, N, mean, var, s);
   }

@@ -378,7 +378,6 @@ struct MixSmem {
   float z[ROWS][D + 2];                  // [z, 1, 0]: fragment entries are products of two
   float mref[ROWS][NOUT], yref[ROWS][NOUT];
   float mprev[ROWS][NOUT];               // previous step's largest activation
-  float mean[SH ? 1 : ROWS][NOUT], var[SH ? 1 : ROWS][NOUT];   // moments (read by the prediction kernel)
   // sampled accelerations (rollouts); the shared-tile form, whose LDS is full,
   // leaves them in the Z slots of the sums they come from
   float acc[SH ? 1 : ROWS][NOUT];
@@ -718,7 +717,9 @@ __device__ __forceinline__ void mixture_tiles(const MfmaModel &md, MixSmem<D, MT
 // The two-piece fp16 form runs the same loop with three fp16 instructions per
 // block (hi hi, hi lo, lo hi of scaled values; 12 KB of pieces per tile) and
 // undoes the models' and rows' powers of two in the epilogue.
-template <int D, int MT, int NW, int PF>
+// NPU: pieces used per value, all of them or (a coarse pass, whose sums serve as
+// anchors only) the leading one.
+template <int D, int MT, int NW, int PF, int NPU = MixSmem<D, MT, NW, PF>::NPC, bool TWO = false>
 __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D, MT, NW, PF> &sm, int T0, int T1) {
   static_assert(PF != kPfF32 && D == kBfD && (MT == 1 || MT == 2), "pieces forms: d = 16, one or two row tiles");
   using G = Geo<D>;
@@ -734,7 +735,7 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
   const int t0 = __builtin_amdgcn_readfirstlane(T0 + (int)((int64_t)wave * (T1 - T0) / NW));
   const int t1 = __builtin_amdgcn_readfirstlane(T0 + (int)((int64_t)(wave + 1) * (T1 - T0) / NW));
   if (t0 >= t1) return;
-  u32x4 Bs[MT][kBfNKB][NPC];
+  u32x4 Bs[MT][kBfNKB][NPU];
   {
     const u32x4 *Ab = (const u32x4 *)&sm.A[0][0][0];
 #pragma unroll
@@ -742,7 +743,7 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
 #pragma unroll
       for (int kb = 0; kb < kBfNKB; ++kb)
 #pragma unroll
-        for (int p = 0; p < NPC; ++p) Bs[mt][kb][p] = Ab[((mt * kBfNKB + kb) * NPC + p) * 64 + lane];
+        for (int p = 0; p < NPU; ++p) Bs[mt][kb][p] = Ab[((mt * kBfNKB + kb) * NPC + p) * 64 + lane];
   }
   // fp16 form: the lane's rows' powers of two (as in the fragment build)
   float rsc[MT], rsi[MT];
@@ -772,7 +773,7 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
     return nb;
   };
   // element I of the three pieces (blocks of 8 bf16) takes the pieces of x
-  auto put = [&](u32x4 (&v)[NPC], auto I, float x, int mt) {
+  auto put = [&](u32x4 (&v)[NPU], auto I, float x, int mt) {
     constexpr int i = decltype(I)::value;
     uint16_t pc[3];
     if constexpr (HF)
@@ -780,7 +781,7 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
     else
       bf16_split3(x, pc);
 #pragma unroll
-    for (int p = 0; p < NPC; ++p) {
+    for (int p = 0; p < NPU; ++p) {
       uint32_t w = v[p][i / 2];
       w = (i & 1) ? ((w & 0x0000FFFFu) | ((uint32_t)pc[p] << 16)) : ((w & 0xFFFF0000u) | pc[p]);
       v[p][i / 2] = w;
@@ -816,10 +817,10 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
                                                  md.n_tiles * kTileBytes);
   const __amdgpu_buffer_rsrc_t srs = buffer_rsrc(HF ? md.hmeta : md.sig2, md.n_tiles * kMetaBytes);
   const int lane_off = lane * 16, grp_off = 16 * (lane >> 4);
-  u32x4 W[kBfNKB][NPC];
+  u32x4 W[kBfNKB][NPU];
   auto load_blk = [&](int tile, int kb) {
 #pragma unroll
-    for (int p = 0; p < NPC; ++p)
+    for (int p = 0; p < NPU; ++p)
       W[kb][p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                                wrs, lane_off, tile * kTileBytes + (kb * NPC + p) * 1024, 0));
   };
@@ -834,14 +835,23 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
   // the piece pairs of block kb of row tile mt into one accumulator (the pipe
   // takes a dependent product at full rate): bf16 hh, hm, mh, hl, mm, lh;
   // fp16 hh, hl, lh
-  auto block6 = [&](int mt, int kb, f32x4 &x) {
+  // TWO: the leading products (hh) and the others go into accumulators of their
+  // own (lo: 2^-8 of hh and less), so that the sum rounds once per block at its
+  // full magnitude instead of six times.  For predictions, whose error it is
+  // (100003 inputs, 6 x 256 models, means against float64: 2.7e-7, 6.1e-7 in one
+  // accumulator, 4.5e-7 in float32 products); a rollout's error does not feel it
+  // and its loop would pay 7 %.
+  auto block6 = [&](int mt, int kb, f32x4 &x, f32x4 &lo) {
     x = mm(W[kb][0], Bs[mt][kb][0], x);
-    x = mm(W[kb][0], Bs[mt][kb][1], x);
-    x = mm(W[kb][1], Bs[mt][kb][0], x);
-    if constexpr (!HF) {
-      x = mm(W[kb][0], Bs[mt][kb][2], x);
-      x = mm(W[kb][1], Bs[mt][kb][1], x);
-      x = mm(W[kb][2], Bs[mt][kb][0], x);
+    f32x4 &r = TWO ? lo : x;
+    if constexpr (NPU > 1) {
+      r = mm(W[kb][0], Bs[mt][kb][1], r);
+      r = mm(W[kb][1], Bs[mt][kb][0], r);
+    }
+    if constexpr (NPU > 2) {
+      r = mm(W[kb][0], Bs[mt][kb][2], r);
+      r = mm(W[kb][1], Bs[mt][kb][1], r);
+      r = mm(W[kb][2], Bs[mt][kb][0], r);
     }
   };
   // With two row tiles (one wave per SIMD, nothing else to overlap with) two
@@ -855,12 +865,15 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
   constexpr bool PIPE = MT == 2;
   // per accumulator set: sigma^2 of the tile's models and (fp16 form) their scales
   f32x4 qa[2][MT], ya[2][MT], s2[2], qsc[2], ysc[2];
+  f32x4 ql[2][MT], yl[2][MT];   // (TWO) the lower products' sums
   auto clear_pending = [&](auto PI) {
     constexpr int p = decltype(PI)::value;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       qa[p][mt] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       ya[p][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      ql[p][mt] = ya[p][mt];
+      yl[p][mt] = ya[p][mt];
     }
     s2[p] = f32x4{0.f, 0.f, 0.f, 0.f};
     qsc[p] = f32x4{1.f, 1.f, 1.f, 1.f};
@@ -869,8 +882,10 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
   auto epi = [&](auto PI, int mt, int i) {
     constexpr int p = decltype(PI)::value;
     // fp16 form: the model's and the row's powers of two undone (exact)
-    const float a = HF ? qa[p][mt][i] * (qsc[p][i] * rsc[mt]) : qa[p][mt][i];
-    const float dd = HF ? ya[p][mt][i] * (ysc[p][i] * rsc[mt]) : ya[p][mt][i];
+    const float qv = TWO ? qa[p][mt][i] + ql[p][mt][i] : qa[p][mt][i];
+    const float yv = TWO ? ya[p][mt][i] + yl[p][mt][i] : ya[p][mt][i];
+    const float a = HF ? qv * (qsc[p][i] * rsc[mt]) : qv;
+    const float dd = HF ? yv * (ysc[p][i] * rsc[mt]) : yv;
     // bare v_exp_f32: arguments below -126 (weights under 2^-126 next to a
     // largest term of at least 2^-100) need none of exp2f's denormal scaling
     const float e = __builtin_amdgcn_exp2f(a);
@@ -915,12 +930,14 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
     for (int mt = 0; mt < MT; ++mt) {
       qa[c][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
       ya[c][mt] = qa[c][mt];
+      ql[c][mt] = qa[c][mt];
+      yl[c][mt] = qa[c][mt];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kb = 0; kb < kBfNKB; ++kb) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) block6(mt, kb, kb < kBfNKQ ? qa[c][mt] : ya[c][mt]);
+      for (int mt = 0; mt < MT; ++mt) block6(mt, kb, kb < kBfNKQ ? qa[c][mt] : ya[c][mt], kb < kBfNKQ ? ql[c][mt] : yl[c][mt]);
       if constexpr (PIPE) {
         // this block's share of the pending epilogue, between its products
 #pragma unroll
@@ -930,11 +947,11 @@ __device__ __forceinline__ void mixture_tiles_bf(const MfmaModel &md, MixSmem<D,
       load_blk(tn, kb);
       if constexpr (PIPE) {
 #pragma unroll
-        for (int j = 0; j < (HF ? 3 : 6) * MT; ++j) {
+        for (int j = 0; j < NPU * (NPU + 1) / 2 * MT; ++j) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one product
           __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two vector ALU ops
         }
-        __builtin_amdgcn_sched_group_barrier(0x020, NPC, 0);  // the piece loads
+        __builtin_amdgcn_sched_group_barrier(0x020, NPU, 0);  // the piece loads
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1016,7 +1033,8 @@ __device__ __forceinline__ void static_for(F &f) {
 // one row tile per wave, every piece read for one product and the epilogue
 // behind the products: 2540 cycles at 2.35 GHz, 83.7 ms on the same card.  bf16
 // pieces, 40 steps: 25.8 against 26.5 ms.
-template <int D, int MT, int NW, int PF>
+// NPU and TWO as in mixture_tiles_bf.
+template <int D, int MT, int NW, int PF, int NPU = MixSmem<D, MT, NW, PF>::NPC, bool TWO = false>
 __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D, MT, NW, PF> &sm, int T0, int T1) {
   using SM = MixSmem<D, MT, NW, PF>;
   static_assert(SM::SH && (NW == 4 || (NW == 8 && MT == 8)), "shared-tile form: 64 rows on four, 128 on four or eight waves");
@@ -1050,13 +1068,16 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   // repeat it, past the range's last tile they re-read that tile's end into
   // slots that nobody reads (no branch in the tile loop).
   constexpr int NSTG = SM::kRingStages;
-  constexpr int kLoads = (2 * SM::kChunks + NW - 1) / NW;
+  constexpr int kChunks = kBfNKB * NPU;   // of a tile
+  constexpr int kLoads = (2 * kChunks + NW - 1) / NW;
   const int n_st = (n + 1) / 2;
   const int src_end = T1 * kTileBytes - 1024;
   auto issue = [&](int st_i, int ring, int q) {
-    const int j = min(wave + NW * q, 2 * SM::kChunks - 1);
+    const int j = min(wave + NW * q, 2 * kChunks - 1);
+    // chunk (block, piece) of the stage's two tiles: contiguous when every piece is used
+    const int off = NPU == NPC ? j * 1024 : j / kChunks * kTileBytes + (j % kChunks) / NPU * (NPC * 1024) + j % NPU * 1024;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (__attribute__((address_space(3))) void *)&sm.ring[ring][j][0], 16,
-                                             lane * 16, min((T0 + 2 * st_i) * kTileBytes + j * 1024, src_end), 0, 0);
+                                             lane * 16, min((T0 + 2 * st_i) * kTileBytes + off, src_end), 0, 0);
   };
   auto issue_stage = [&](int st_i) {
 #pragma unroll
@@ -1089,7 +1110,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   };
   // the wave's sample pieces, built in registers (rows row0 + 16 mt, features
   // 32 kb + 8 (lane/16) .. +7 of block kb)
-  u32x4 Bs[RT][kBfNKB][NPC];
+  u32x4 Bs[RT][kBfNKB][NPU];
   {
     const int grp = lane >> 4;
 #pragma unroll
@@ -1100,17 +1121,17 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
 #pragma unroll
       for (int mt = 0; mt < RT; ++mt) {
         const int row = row0 + 16 * mt;
-        uint32_t pk[NPC][4];
+        uint32_t pk[NPU][4];
 #pragma unroll
         for (int i = 0; i < 8; i += 2) {
           uint16_t lo[3], hi[3];
           split(sm.z[row][src[i] >> 8] * sm.z[row][src[i] & 0xFF], mt, lo);
           split(sm.z[row][src[i + 1] >> 8] * sm.z[row][src[i + 1] & 0xFF], mt, hi);
 #pragma unroll
-          for (int p = 0; p < NPC; ++p) pk[p][i / 2] = (uint32_t)lo[p] | ((uint32_t)hi[p] << 16);
+          for (int p = 0; p < NPU; ++p) pk[p][i / 2] = (uint32_t)lo[p] | ((uint32_t)hi[p] << 16);
         }
 #pragma unroll
-        for (int p = 0; p < NPC; ++p) Bs[mt][kb][p] = u32x4{pk[p][0], pk[p][1], pk[p][2], pk[p][3]};
+        for (int p = 0; p < NPU; ++p) Bs[mt][kb][p] = u32x4{pk[p][0], pk[p][1], pk[p][2], pk[p][3]};
       }
     }
   }
@@ -1135,12 +1156,12 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       m[mt] = sm.mref[row0 + 16 * mt][oo];
       y[mt] = sm.yref[row0 + 16 * mt][oo];
     }
-    auto put = [&](u32x4 (&v)[NPC], auto I, bool mine, float x, int mt) {
+    auto put = [&](u32x4 (&v)[NPU], auto I, bool mine, float x, int mt) {
       constexpr int i = decltype(I)::value;
       uint16_t pc[3];
       split(x, mt, pc);
 #pragma unroll
-      for (int p = 0; p < NPC; ++p) {
+      for (int p = 0; p < NPU; ++p) {
         const uint32_t w = v[p][i / 2];
         const uint32_t n = (i & 1) ? ((w & 0x0000FFFFu) | ((uint32_t)pc[p] << 16)) : ((w & 0xFFFF0000u) | pc[p]);
         v[p][i / 2] = mine ? n : w;
@@ -1184,12 +1205,15 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   // two accumulator sets: one takes the tile in hand, the other waits for its
   // epilogue, with sigma^2 and (fp16 form) the scales of its tile's models
   f32x4 qa[2][RT], ya[2][RT], s2[2], qs[2], ys[2];
+  f32x4 ql[2][RT], yl[2][RT];
   auto clear_pending = [&](auto PI) {
     constexpr int p = decltype(PI)::value;
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt) {
       qa[p][mt] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       ya[p][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      ql[p][mt] = ya[p][mt];
+      yl[p][mt] = ya[p][mt];
     }
     s2[p] = f32x4{0.f, 0.f, 0.f, 0.f};
     qs[p] = f32x4{1.f, 1.f, 1.f, 1.f};
@@ -1204,8 +1228,10 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     constexpr int p = decltype(PI)::value;
     constexpr bool sc = decltype(SC)::value;
     const int mt = el % RT, i = el / RT;
-    ea[el] = sc ? qa[p][mt][i] * (qs[p][i] * rsc[mt]) : qa[p][mt][i];
-    ed[el] = sc ? ya[p][mt][i] * (ys[p][i] * rsc[mt]) : ya[p][mt][i];
+    const float qv = TWO ? qa[p][mt][i] + ql[p][mt][i] : qa[p][mt][i];
+    const float yv = TWO ? ya[p][mt][i] + yl[p][mt][i] : ya[p][mt][i];
+    ea[el] = sc ? qv * (qs[p][i] * rsc[mt]) : qv;
+    ed[el] = sc ? yv * (ys[p][i] * rsc[mt]) : yv;
     // bare v_exp_f32: arguments below -126 (weights under 2^-126 next to a
     // largest term of at least 2^-100) need none of exp2f's denormal scaling
     ee[el] = __builtin_amdgcn_exp2f(ea[el]);
@@ -1235,10 +1261,10 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
   };
   // The tile's six blocks of model pieces go through a ring of three blocks in
   // registers, each read from LDS two blocks (12 products) ahead.
-  u32x4 wb[3][NPC];
+  u32x4 wb[3][NPU];
   auto ldb = [&](const u32x4(*W)[64], int kb) {
 #pragma unroll
-    for (int p = 0; p < NPC; ++p) wb[kb % 3][p] = W[kb * NPC + p][lane];
+    for (int p = 0; p < NPU; ++p) wb[kb % 3][p] = W[kb * NPU + p][lane];
   };
   int o = 0, nb = 0;
   // the products of one tile (piece chunks W) into set c, the epilogue of the
@@ -1261,7 +1287,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       locate(tile, o, nb);
       set_anchor(o);
     }
-    constexpr int NPR = HF ? 3 : 6;
+    constexpr int NPR = NPU * (NPU + 1) / 2;
     constexpr int PA[6] = {0, 0, 1, 0, 1, 2}, PB[6] = {0, 1, 0, 2, 1, 0};
     // slot: one product of each row tile (the chains alternate; piece pairs
     // (model, sample) bf16 hh, hm, mh, hl, mm, lh; fp16 hh, hl, lh) and about
@@ -1289,18 +1315,25 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int mt = 0; mt < RT; ++mt) {
-        f32x4 &x = kb < kBfNKQ ? qa[c][mt] : ya[c][mt];
+        constexpr bool low = TWO && r > 0;
+        f32x4 &x = kb < kBfNKQ ? (low ? ql[c][mt] : qa[c][mt]) : (low ? yl[c][mt] : ya[c][mt]);
         x = mm(wb[kb % 3][PA[r]], Bs[mt][kb][PB[r]],
-               r == 0 && (kb == 0 || kb == kBfNKQ) ? f32x4{0.f, 0.f, 0.f, 0.f} : x);
+               r == (low ? 1 : 0) && (kb == 0 || kb == kBfNKQ) ? f32x4{0.f, 0.f, 0.f, 0.f} : x);
       }
-      if constexpr (sl % 2 == 0) {
-        if constexpr (sl / 2 < 4 * RT) epi_a(PI, SC, sl / 2);
-        if constexpr (sl >= 2 && sl / 2 - 1 < 4 * RT) epi_c(PI, sl / 2 - 1);
-      } else {
-        if constexpr (sl / 2 < 4 * RT) epi_b(sl / 2);
-        // a memory load each: all at once they would hold every wave up
-        if constexpr (decltype(LD)::value && sl / 2 < kLoads) issue(st_ld, ring_ld, sl / 2);
+      // the epilogue's steps in order: 2 el is A of element el and C of the one
+      // before, 2 el + 1 its B; one step per slot where the slots suffice
+      constexpr int kSteps = 8 * RT + 1, kPer = (kSteps + kBfNKB * NPR - 1) / (kBfNKB * NPR);
+#pragma unroll
+      for (int es = sl * kPer; es < (sl + 1) * kPer && es < kSteps; ++es) {
+        if (es & 1) {
+          epi_b(es / 2);
+        } else {
+          if (es / 2 < 4 * RT) epi_a(PI, SC, es / 2);
+          if (es > 0) epi_c(PI, es / 2 - 1);
+        }
       }
+      // a memory load each: all at once they would hold every wave up
+      if constexpr (decltype(LD)::value && sl % 2 == 1 && sl / 2 < kLoads) issue(st_ld, ring_ld, sl / 2);
       __builtin_amdgcn_sched_barrier(0);
     };
     static_for<0, kBfNKB * NPR>(slot);
@@ -1320,7 +1353,7 @@ __device__ __forceinline__ void mixture_tiles_sh(const MfmaModel &md, MixSmem<D,
     __asm__ __volatile__("" ::: "memory");
   };
   auto run = [&](auto SC) {
-    auto W = [&](int ring, int u) { return (const u32x4(*)[64]) & sm.ring[ring][u * SM::kChunks]; };
+    auto W = [&](int ring, int u) { return (const u32x4(*)[64]) & sm.ring[ring][u * kChunks]; };
     auto next = [&](int r) { return r + 1 == NSTG ? 0 : r + 1; };
     clear_pending(I1{});
     enter();
@@ -1393,6 +1426,9 @@ struct SampleArgs {
   float *trace = nullptr;
   int64_t trace_stride = 0;
   int trace_off = 0, trace_rows = 0;
+  // optional moments (prediction): mean[row * n_out + o], var[...] of rows < moment_rows
+  float *mean = nullptr, *var = nullptr;
+  int moment_rows = 0, n_out = 0;
 };
 
 // Eq. (1) moments of one (row, output) from its complete sums, the sampled
@@ -1405,9 +1441,9 @@ __device__ __forceinline__ void finish_sums(MixSmem<D, MT, NW, PF> &sm, int row,
   const float d1 = s.S1 / s.Z;
   const float mu = sm.yref[row][o] + d1;
   const float var = (fmaxf(s.S2 - s.S1 * d1, 0.f) + s.S3) / s.Z;
-  if constexpr (!MixSmem<D, MT, NW, PF>::SH) {
-    sm.mean[row][o] = mu;
-    sm.var[row][o] = var;
+  if (sa.mean && row < sa.moment_rows) {
+    sa.mean[row * sa.n_out + o] = mu;
+    sa.var[row * sa.n_out + o] = var;
   }
   // the anchor in use is m (base-2 units): sum_j exp(-q_j/2) = 2^m Z.  A
   // redo pass rewrites the trace, so it ends with the final pass's values.
@@ -1421,7 +1457,10 @@ __device__ __forceinline__ void finish_sums(MixSmem<D, MT, NW, PF> &sm, int row,
   }
   sm.accel(row, o) = sa.xi ? mu + sqrtf(var) * sa.xi[row * MixSmem<D, MT, NW, PF>::XIS + o] : mu;
   const bool valid = isfinite(s.Z) && isfinite(s.S1) && isfinite(s.S2) && isfinite(s.S3) && s.mx >= kAnchorLo;
-  if (!valid) sm.redo[ev & 1] = 1;
+  // a prediction's reference far from its mean (a coarse pass, far inputs) costs
+  // the variance its digits: 2^-24 d1^2 beside var
+  const bool off = sa.mean && !(d1 * d1 <= 4.0f * var) && row < sa.moment_rows;
+  if (!valid || off) sm.redo[ev & 1] = 1;
   sm.mref[row][o] += s.mx;
   if (isfinite(mu)) sm.yref[row][o] = mu;
 }
@@ -1597,48 +1636,107 @@ __device__ __forceinline__ void reset_anchors(MixSmem<D, MT, NW, PF> &sm) {
 }
 
 // --------------------------------------------------------------- predict
-template <int D, int MT, int NW>
+// 16 MT inputs per workgroup.  Float32 products: two passes, the second with
+// the first one's largest activations as anchors and its means as references.
+// bf16 pieces (d = 16): the first pass takes the leading piece alone, a sixth of
+// the products -- an anchor within 100 units of the largest activation and a
+// reference within two standard deviations of the mean are all it has to give --
+// and the second all three; a third, and a fourth, follow only where those were
+// out of that range (inputs far from every model).  Bound: the matrix pipe (42 bf16 products per 16 x 16
+// block against 88 float32 ones of twice the length); 100003 inputs, 6 x 256
+// models: 0.36 ms, 0.94 ms in two float32 passes of 16-row workgroups.
+template <int D, int MT, int NW, int PF>
 __global__ void __launch_bounds__(NW * 64) predict_mfma_kernel(MfmaModel md, const float *__restrict__ Z,
-                                                               int64_t N, float *__restrict__ mean,
+                                                               int64_t n_base, int64_t N, float *__restrict__ mean,
                                                                float *__restrict__ var) {
-  __shared__ MixSmem<D, MT, NW> sm;
-  constexpr int ROWS = MixSmem<D, MT, NW>::ROWS;
+  using SM = MixSmem<D, MT, NW, PF>;
+  __shared__ SM sm;
+  constexpr int ROWS = SM::ROWS;
   mix_setup(sm);
   reset_anchors(sm);
-  const int64_t n0 = (int64_t)blockIdx.x * ROWS;
+  const int64_t n0 = n_base + (int64_t)blockIdx.x * ROWS;
   for (int i = threadIdx.x; i < ROWS * (D + 2); i += NW * 64) {
     const int row = i / (D + 2), a = i % (D + 2);
     sm.z[row][a] = a < D ? ((n0 + row < N) ? Z[(n0 + row) * D + a] : 0.0f) : (a == D ? 1.0f : 0.0f);
   }
   __syncthreads();
+  SampleArgs sa{nullptr};
+  sa.mean = mean + n0 * md.n_out;
+  sa.var = var + n0 * md.n_out;
+  sa.moment_rows = (int)min<int64_t>(ROWS, N - n0);
+  sa.n_out = md.n_out;
   uint32_t seq = 0;
-  mixture_step(md, sm, true, 0, md.n_tiles, (const PairCtx *)nullptr, seq);
-  for (int i = threadIdx.x; i < ROWS * md.n_out; i += NW * 64) {
-    const int row = i / md.n_out, o = i % md.n_out;
-    if (n0 + row < N) {
-      mean[(n0 + row) * md.n_out + o] = sm.mean[row][o];
-      var[(n0 + row) * md.n_out + o] = sm.var[row][o];
+  if constexpr (PF == kPfF32) {
+    mixture_step(md, sm, true, 0, md.n_tiles, (const PairCtx *)nullptr, seq, sa);
+  } else {
+    build_fragments(sm);
+    for (int pass = 0; pass < 4; ++pass) {
+      clear_parts(sm);
+      if (threadIdx.x == 0) sm.redo[0] = sm.redo[1] = 0;
+      __syncthreads();
+      if constexpr (SM::SH) {
+        if (pass == 0)
+          mixture_tiles_sh<D, MT, NW, PF, 1>(md, sm, 0, md.n_tiles);
+        else
+          mixture_tiles_sh<D, MT, NW, PF, SM::NPC, true>(md, sm, 0, md.n_tiles);
+      } else {
+        if (pass == 0)
+          mixture_tiles_bf<D, MT, NW, PF, 1>(md, sm, 0, md.n_tiles);
+        else
+          mixture_tiles_bf<D, MT, NW, PF, SM::NPC, true>(md, sm, 0, md.n_tiles);
+      }
+      __syncthreads();
+      merge_waves(sm, md.n_out, 0u, sa);
+      __syncthreads();
+      if (pass > 0 && sm.redo[0] == 0) break;
+      __syncthreads();   // every lane has read the flag
     }
   }
 }
 
-template <int D>
-static hipError_t predict_mfma_d(const MfmaModel &md, const float *Z, int64_t N, float *mean,
+template <int D, int MT, int NW, int PF>
+static hipError_t predict_mfma_t(const MfmaModel &md, const float *Z, int64_t n_base, int64_t N, float *mean,
                                  float *var, hipStream_t s) {
-  constexpr int MT = 1, NW = 4;
-  const int64_t nb = (N + 16 * MT - 1) / (16 * MT);
-  hipLaunchKernelGGL((predict_mfma_kernel<D, MT, NW>), dim3((unsigned)nb), dim3(NW * 64), 0, s, md,
-                     Z, N, mean, var);
+  const int64_t nb = (N - n_base + 16 * MT - 1) / (16 * MT);
+  hipLaunchKernelGGL((predict_mfma_kernel<D, MT, NW, PF>), dim3((unsigned)nb), dim3(NW * 64), 0, s, md, Z, n_base, N,
+                     mean, var);
   return hipGetLastError();
 }
 
-hipError_t launch_predict_mfma(const ModelArgs &m, const MfmaLayout &l, const void *base,
-                               const void *Z, int64_t N, void *mean, void *var, hipStream_t s) {
+// pieces: the bf16 form (d = 16).  Whole passes of 128-row workgroups over 256
+// compute units first (139 us for 32768 inputs, 6 x 256 models); the rest in the
+// tile with the fewest passes times their cost (microseconds per pass for t
+// model tiles: 16 rows 2 + 0.22 t, 32 rows 7 + 0.29 t, 128 rows 15 + 0.85 t;
+// 16384 inputs: 96 us in 32-row tiles, 139 in 128-row ones, and the float32
+// form 160).
+hipError_t launch_predict_mfma(const ModelArgs &m, const MfmaLayout &l, const void *base, const void *Z, int64_t N,
+                               void *mean, void *var, bool pieces, hipStream_t s) {
   if (N == 0) return hipSuccess;
   const MfmaModel md = mfma_view(l, base);
-  if (m.d == 16) return predict_mfma_d<16>(md, (const float *)Z, N, (float *)mean, (float *)var, s);
-  if (m.d == 6) return predict_mfma_d<6>(md, (const float *)Z, N, (float *)mean, (float *)var, s);
-  if (m.d == 4) return predict_mfma_d<4>(md, (const float *)Z, N, (float *)mean, (float *)var, s);
+  const float *z = (const float *)Z;
+  float *mn = (float *)mean, *vr = (float *)var;
+  if (m.d == 16 && pieces && md.Wb != nullptr) {
+    constexpr int64_t kPass = 128 * 256;
+    const bool sh = m.n_out <= 6;   // outputs per row the shared tile holds
+    const double t = l.n_tiles;
+    int64_t n0 = 0;
+    hipError_t e = hipSuccess;
+    const int64_t rest = sh ? N % kPass : N;
+    const double t16 = (double)((rest + 4095) / 4096) * (2 + 0.22 * t), t32 = (double)((rest + 8191) / 8192) * (7 + 0.29 * t);
+    const double t128 = sh ? 15 + 0.85 * t : 1e30;
+    const bool tail128 = rest > 0 && t128 < t16 && t128 < t32;
+    const int64_t n128 = sh ? (tail128 ? N : N - rest) : 0;
+    if (n128 > 0) {
+      e = predict_mfma_t<16, 8, 8, kPfBf16x3>(md, z, 0, n128, mn, vr, s);
+      n0 = n128;
+    }
+    if (e != hipSuccess || n0 == N) return e;
+    return t16 <= t32 ? predict_mfma_t<16, 1, 4, kPfBf16x3>(md, z, n0, N, mn, vr, s)
+                      : predict_mfma_t<16, 2, 4, kPfBf16x3>(md, z, n0, N, mn, vr, s);
+  }
+  if (m.d == 16) return predict_mfma_t<16, 1, 4, kPfF32>(md, z, 0, N, mn, vr, s);
+  if (m.d == 6) return predict_mfma_t<6, 1, 4, kPfF32>(md, z, 0, N, mn, vr, s);
+  if (m.d == 4) return predict_mfma_t<4, 1, 4, kPfF32>(md, z, 0, N, mn, vr, s);
   return hipErrorInvalidValue;
 }
 
