@@ -10,49 +10,69 @@
 namespace pi2rh {
 
 // ----------------------------------------------------------------- fold
-// One block per 16 local models.  One lane per model folds the PLS chain
-// (Sec. 2) into y = beta_0 + b . (z - c) -- b is the derivative of y w.r.t.
-// the centred input, accumulated backwards through the deflation steps in
-// double -- then all lanes write the 16 contiguous records, coalesced:
+// One block per 16 local models, 16 lanes each (one input coordinate per lane).
+// The lanes of a model fold its PLS chain (Sec. 2) into y = beta_0 + b . (z - c)
+// -- b is the derivative of y w.r.t. the centred input, accumulated backwards
+// through the deflation steps in double -- then all lanes write the 16
+// contiguous records, coalesced:
 // [c | theta (upper triangle of D + D^T, diagonal D_aa) | b | beta_0 | sigma^2].
+// Bound by latency: 1536 models of d = 16 28 us with one lane per model and
+// the pair of every entry searched for, 15 us so.
 template <typename Real>
 __global__ void __launch_bounds__(256) fold_direct_kernel(ModelArgs m, Real *__restrict__ rec) {
-  __shared__ double bv[16][kMaxD];
+  __shared__ Real bv[16][kMaxD];
+  __shared__ Real Dl[16][kMaxD * kMaxD + 1];
+  __shared__ unsigned char pa[kMaxD * (kMaxD + 1) / 2], pb[kMaxD * (kMaxD + 1) / 2];
   const int j0 = blockIdx.x * 16, d = m.d, R = m.R, RS = d + d * (d + 1) / 2 + d + 2;
-  const int nj = min(16, m.Ltot - j0);
-  if ((int)threadIdx.x < nj) {
-    const int j = j0 + threadIdx.x;
-    const Real *U = (const Real *)m.proj_u + (size_t)j * R * d;
-    const Real *P = m.proj_p ? (const Real *)m.proj_p + (size_t)j * R * d : U;
-    const Real *B = (const Real *)m.beta + (size_t)j * (R + 1);
-    double rb[kMaxD];
-    for (int a = 0; a < d; ++a) rb[a] = 0.0;
-    for (int r = R - 1; r >= 0; --r) {
-      double pr = 0.0;
-      for (int a = 0; a < d; ++a) pr += (double)P[r * d + a] * rb[a];
-      const double sb = (double)B[r + 1] - pr;
-      for (int a = 0; a < d; ++a) rb[a] += sb * (double)U[r * d + a];
+  const int nj = min(16, m.Ltot - j0), np = d * (d + 1) / 2;
+  for (int e = threadIdx.x; e < nj * d * d; e += 256)
+    Dl[e / (d * d)][e % (d * d)] = ((const Real *)m.metric)[(size_t)j0 * d * d + e];
+  if ((int)threadIdx.x < np) {
+    int a = 0, rem = threadIdx.x;
+    while (rem >= d - a) {
+      rem -= d - a;
+      ++a;
     }
-    for (int a = 0; a < d; ++a) bv[threadIdx.x][a] = rb[a];
+    pa[threadIdx.x] = (unsigned char)a;
+    pb[threadIdx.x] = (unsigned char)(a + rem);
+  }
+  {
+    const int col = threadIdx.x >> 4, a = threadIdx.x & 15;
+    const bool on = col < nj && a < d;
+    const size_t j = (size_t)j0 + (col < nj ? col : 0);
+    const Real *U = (const Real *)m.proj_u + j * R * d;
+    const Real *P = m.proj_p ? (const Real *)m.proj_p + j * R * d : U;
+    const Real *B = (const Real *)m.beta + j * (R + 1);
+    Real ru[kMaxR], rp[kMaxR], rbeta[kMaxR];
+#pragma unroll
+    for (int r = 0; r < kMaxR; ++r) {
+      const bool use = r < R && on;
+      ru[r] = use ? U[r * d + a] : (Real)0;
+      rp[r] = use ? P[r * d + a] : (Real)0;
+      rbeta[r] = r < R && col < nj ? B[r + 1] : (Real)0;
+    }
+    double rb = 0.0;
+#pragma unroll
+    for (int r = kMaxR - 1; r >= 0; --r) {
+      if (r >= R) continue;
+      double pr = (double)rp[r] * rb;
+#pragma unroll
+      for (int k = 8; k >= 1; k >>= 1) pr += __shfl_xor(pr, k);
+      rb += ((double)rbeta[r] - pr) * (double)ru[r];
+    }
+    if (on) bv[col][a] = (Real)rb;
   }
   __syncthreads();
-  const int np = d * (d + 1) / 2;
-  for (int e = threadIdx.x; e < nj * RS; e += blockDim.x) {
+  for (int e = threadIdx.x; e < nj * RS; e += 256) {
     const int jj = e / RS, f = e % RS, j = j0 + jj;
     Real v;
     if (f < d) {
       v = ((const Real *)m.centre)[(size_t)j * d + f];
     } else if (f < d + np) {
-      int a = 0, rem = f - d;
-      while (rem >= d - a) {
-        rem -= d - a;
-        ++a;
-      }
-      const int b = a + rem;
-      const Real *D = (const Real *)m.metric + (size_t)j * d * d;
-      v = (a == b) ? D[a * d + a] : D[a * d + b] + D[b * d + a];
+      const int a = pa[f - d], b = pb[f - d];
+      v = (a == b) ? Dl[jj][a * d + a] : Dl[jj][a * d + b] + Dl[jj][b * d + a];
     } else if (f < d + np + d) {
-      v = (Real)bv[jj][f - d - np];
+      v = bv[jj][f - d - np];
     } else if (f == d + np + d) {
       v = ((const Real *)m.beta)[(size_t)j * (R + 1)];
     } else {

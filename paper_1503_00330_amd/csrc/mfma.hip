@@ -117,12 +117,24 @@ __device__ __forceinline__ void f16_split2(float v, uint16_t *pc) {
 }
 
 // ----------------------------------------------------------------- fold
-// One block per tile of 16 model slots.  Phase 1: one lane per model computes
-// in double the derived vectors (h = -(D + D^T) c, kappa = c^T D c, the folded
-// PLS map b and y0 = beta0 - b.c) into LDS; phase 2: every lane writes whole
-// fragments, coalesced.
+// One block per tile of 16 model slots.  Phase 1: 16 lanes per model (one input
+// coordinate each) compute in double the derived vectors (h = -(D + D^T) c,
+// kappa = c^T D c, the folded PLS map b and y0 = beta0 - b.c); phase 2: the float32
+// feature values of every slot go into LDS once; phase 3: every lane writes
+// whole 16-byte fragments of each form, coalesced.  Bound by latency (a block
+// reads 21 KB and writes 42 KB at d = 16): 96 tiles 114 us with one lane per
+// model and every value recomputed for every form, 16 us so.
 constexpr int kFoldThreads = 256;
 static_assert(kFoldThreads >= kHfMeta, "one fold thread per per-tile value of the fp16 form");
+constexpr int kFoldVals = kMaxD * (kMaxD + 1) / 2 + kMaxD + 2 + kMaxD + 2;   // quadratic-form, then prediction features
+
+// Sum (or maximum) over the 16 lanes of a model, in every lane.
+template <typename T, class Op>
+__device__ __forceinline__ T fold_reduce(T v, Op op) {
+#pragma unroll
+  for (int m = 8; m >= 1; m >>= 1) v = op(v, __shfl_xor(v, m));
+  return v;
+}
 
 __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, MfmaLayout l,
                                                                  float *__restrict__ W,
@@ -130,114 +142,122 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
                                                                  uint32_t *__restrict__ Wb,
                                                                  uint32_t *__restrict__ Wh,
                                                                  float *__restrict__ hmeta) {
-  __shared__ double hv[16][kMaxD], bv[16][kMaxD], kap[16], y0v[16];
-  __shared__ float Dl[16][kMaxD * kMaxD];
-  __shared__ int jcol[16];
-  const int tile = blockIdx.x, d = m.d, R = m.R;
+  __shared__ float Dl[16][kMaxD * kMaxD + 1];
+  __shared__ double cs[16][kMaxD];
+  __shared__ float val[16][kFoldVals + 1];
+  __shared__ unsigned char pa[kMaxD * (kMaxD + 1) / 2], pb[kMaxD * (kMaxD + 1) / 2];
+  __shared__ int eq[16], ey[16];
+  const int tile = blockIdx.x, d = m.d, R = m.R, tid = threadIdx.x;
   const MfmaGeom g = MfmaGeom::make(d);
   int o = 0;
   while (o + 1 < m.n_out && tile >= l.tile_off[o + 1]) ++o;
   const int jfirst = m.L_off[o] + (tile - l.tile_off[o]) * 16;
   const int nvalid = min(16, m.L_off[o + 1] - jfirst);
-  // stage the metrics of the tile's models (coalesced)
-  for (int e = threadIdx.x; e < nvalid * d * d; e += blockDim.x)
+  // the metrics and centres of the tile's models, and the feature pairs
+  for (int e = tid; e < nvalid * d * d; e += kFoldThreads)
     Dl[e / (d * d)][e % (d * d)] = ((const float *)m.metric)[(size_t)jfirst * d * d + e];
-  __syncthreads();
-  if (threadIdx.x < 16) {
-    const int col = threadIdx.x;
-    const int j = col < nvalid ? jfirst + col : -1;
-    jcol[col] = j;
-    if (j >= 0) {
-      const float *c = (const float *)m.centre + (size_t)j * d;
-      const float *D = Dl[col];
-      const float *U = (const float *)m.proj_u + (size_t)j * R * d;
-      const float *P = m.proj_p ? (const float *)m.proj_p + (size_t)j * R * d : U;
-      const float *B = (const float *)m.beta + (size_t)j * (R + 1);
-      double cc[kMaxD];
-      for (int a = 0; a < d; ++a) cc[a] = (double)c[a];
-      double kappa = 0.0;
-      for (int a = 0; a < d; ++a) {
-        double h = 0.0;
-        for (int b = 0; b < d; ++b) {
-          h += ((double)D[a * d + b] + (double)D[b * d + a]) * cc[b];
-          kappa += cc[a] * (double)D[a * d + b] * cc[b];
-        }
-        hv[col][a] = -h;
-      }
-      kap[col] = kappa;
-      // y = beta0 + b.(z - c): b by reverse accumulation through the deflation chain
-      double rb[kMaxD];
-      for (int a = 0; a < d; ++a) rb[a] = 0.0;
-      for (int r = R - 1; r >= 0; --r) {
-        double pr = 0.0;
-        for (int a = 0; a < d; ++a) pr += (double)P[r * d + a] * rb[a];
-        const double sb = (double)B[r + 1] - pr;
-        for (int a = 0; a < d; ++a) rb[a] += sb * (double)U[r * d + a];
-      }
-      double y0 = (double)B[0];
-      for (int a = 0; a < d; ++a) {
-        bv[col][a] = rb[a];
-        y0 -= rb[a] * cc[a];
-      }
-      y0v[col] = y0;
-      sig2[tile * 16 + col] = ((const float *)m.sigma2)[j];
-    } else {
-      sig2[tile * 16 + col] = 0.0f;
+  for (int e = tid; e < nvalid * d; e += kFoldThreads)
+    cs[e / d][e % d] = (double)((const float *)m.centre)[(size_t)jfirst * d + e];
+  if (tid < g.NP) {
+    int a = 0, rem = tid;
+    while (rem >= d - a) {
+      rem -= d - a;
+      ++a;
+    }
+    pa[tid] = (unsigned char)a;
+    pb[tid] = (unsigned char)(a + rem);
+  }
+  const int col = tid >> 4, a = tid & 15;
+  const bool valid = col < nvalid, on = valid && a < d;
+  const size_t j = (size_t)jfirst + (valid ? col : 0);
+  float ru[kMaxR], rp[kMaxR], rbeta[kMaxR];
+  {
+    const float *U = (const float *)m.proj_u + j * R * d;
+    const float *P = m.proj_p ? (const float *)m.proj_p + j * R * d : U;
+    const float *B = (const float *)m.beta + j * (R + 1);
+#pragma unroll
+    for (int r = 0; r < kMaxR; ++r) {
+      const bool use = r < R && on;
+      ru[r] = use ? U[r * d + a] : 0.0f;
+      rp[r] = use ? P[r * d + a] : 0.0f;
+      rbeta[r] = r < R && valid ? B[r + 1] : 0.0f;
     }
   }
+  const float beta0 = valid ? ((const float *)m.beta)[j * (R + 1)] : 0.0f;
+  const float s2 = valid ? ((const float *)m.sigma2)[j] : 0.0f;
   __syncthreads();
-  const int NE = g.KB4 * 64 * 4;
-  const int fqs = g.NP + d + 1, fys = 4 * g.KQB + d + 1;
-  // the float32 value of feature f (quadratic-form features from 0, the
-  // prediction features from 4 KQB) for model slot col
-  auto value = [&](int f, int col) {
-    const int j = jcol[col];
-    float v = 0.0f;
-    if (f == fqs || f == fys) {
-      v = 1.0f;
-    } else if (j < 0) {
-      v = (f == g.NP + d) ? kPadAct : 0.0f;
-    } else if (f < g.NP) {
-      int a = 0, rem = f;
-      while (rem >= d - a) {
-        rem -= d - a;
-        ++a;
-      }
-      const int b = a + rem;
-      const float *D = Dl[col];
-      const double th = (a == b) ? (double)D[a * d + a] : (double)D[a * d + b] + (double)D[b * d + a];
-      v = (float)(kAlpha * th);
-    } else if (f < g.NP + d) {
-      v = (float)(kAlpha * hv[col][f - g.NP]);
-    } else if (f == g.NP + d) {
-      v = (float)(kAlpha * kap[col]);
-    } else if (f >= 4 * g.KQB && f < 4 * g.KQB + d) {
-      v = (float)bv[col][f - 4 * g.KQB];
-    } else if (f == 4 * g.KQB + d) {
-      v = (float)y0v[col];
+  auto add = [](double x, double y) { return x + y; };
+  double h = 0.0, kap = 0.0;
+  const double ca = on ? cs[col][a] : 0.0;
+  if (on)
+    for (int b = 0; b < d; ++b) {
+      const double cb = cs[col][b], Dab = (double)Dl[col][a * d + b];
+      h += (Dab + (double)Dl[col][b * d + a]) * cb;
+      kap += ca * Dab * cb;
     }
-    return v;
-  };
-  float *dst = W + (size_t)tile * NE;
-  for (int e = threadIdx.x; e < NE; e += blockDim.x) {
-    const int comp = e & 3, lane = (e >> 2) & 63, kb4 = e >> 8;
-    dst[e] = value(4 * (4 * kb4 + comp) + lane / 16, lane & 15);
+  const double kappa = fold_reduce(kap, add);
+  // y = beta0 + b.(z - c): b by reverse accumulation through the deflation chain
+  double rb = 0.0;
+#pragma unroll
+  for (int r = kMaxR - 1; r >= 0; --r) {
+    if (r >= R) continue;
+    const double pr = fold_reduce((double)rp[r] * rb, add);
+    rb += ((double)rbeta[r] - pr) * (double)ru[r];
+  }
+  const double y0 = (double)beta0 - fold_reduce(rb * ca, add);
+  // padded slots: activation kPadAct, everything else 0
+  if (a < d) {
+    val[col][g.NP + a] = on ? (float)(kAlpha * -h) : 0.0f;
+    val[col][g.KQ + a] = on ? (float)rb : 0.0f;
+  }
+  if (a == 0) {
+    val[col][g.NP + d] = valid ? (float)(kAlpha * kappa) : kPadAct;
+    val[col][g.NP + d + 1] = 1.0f;
+    val[col][g.KQ + d] = valid ? (float)y0 : 0.0f;
+    val[col][g.KQ + d + 1] = 1.0f;
+    sig2[tile * 16 + col] = s2;
+  }
+  for (int f = a; f < g.NP; f += 16) {
+    const int x = pa[f], y = pb[f];
+    const double th = x == y ? (double)Dl[col][x * d + x] : (double)Dl[col][x * d + y] + (double)Dl[col][y * d + x];
+    val[col][f] = valid ? (float)(kAlpha * th) : 0.0f;
+  }
+  __syncthreads();
+  // float32 fragments: feature f of the contraction is quadratic-form feature f,
+  // or from 4 KQB on prediction feature f - 4 KQB
+  float4 *dst = (float4 *)(W + (size_t)tile * g.KB4 * 256);
+  for (int e = tid; e < g.KB4 * 64; e += kFoldThreads) {
+    const int lane = e & 63, kb4 = e >> 6;
+    float v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int f = 4 * (4 * kb4 + c) + lane / 16, fy = f - 4 * g.KQB;
+      v[c] = f < g.KQ ? val[lane & 15][f] : fy >= 0 && fy < g.KY ? val[lane & 15][g.KQ + fy] : 0.0f;
+    }
+    dst[e] = make_float4(v[0], v[1], v[2], v[3]);
   }
   if (Wb == nullptr) return;
+  // the value of piece-form feature k of block kb: blocks 0 .. kBfNKQ-1 hold the
+  // quadratic-form features, the last the prediction features
+  auto piece_value = [&](int kb, int k, int slot) {
+    return kb < kBfNKQ ? (k < g.KQ ? val[slot][k] : 0.0f) : (k < g.KY ? val[slot][g.KQ + k] : 0.0f);
+  };
   // the same values as three bf16 pieces, in the A-operand layout of the bf16
   // 16x16x32 instruction: block kb, piece p, lane (model lane%16, features
-  // 8 (lane/16) .. +7 of the block); blocks 0..kBfNKQ-1 hold the quadratic-form
-  // features, the last the prediction features
-  uint16_t *dstb = (uint16_t *)(Wb + (size_t)tile * kBfTileU32);
-  for (int e = threadIdx.x; e < kBfNKB * 64 * 8; e += blockDim.x) {
-    const int i = e & 7, lane = (e >> 3) & 63, kb = e >> 9;
-    const int k = 32 * (kb < kBfNKQ ? kb : kb - kBfNKQ) + 8 * (lane / 16) + i;
-    const bool inside = kb < kBfNKQ ? k < g.KQ : k < g.KY;
-    const float v = inside ? value(kb < kBfNKQ ? k : 4 * g.KQB + k, lane & 15) : 0.0f;
-    uint16_t pc[3];
-    bf16_split3(v, pc);
+  // 8 (lane/16) .. +7 of the block)
+  u32x4 *dstb = (u32x4 *)(Wb + (size_t)tile * kBfTileU32);
+  for (int e = tid; e < kBfNKB * 64; e += kFoldThreads) {
+    const int lane = e & 63, kb = e >> 6, k0 = 32 * (kb < kBfNKQ ? kb : 0) + 8 * (lane / 16);
+    uint16_t pc[8][3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) dstb[((size_t)(kb * 3 + p) * 64 + lane) * 8 + i] = pc[p];
+    for (int i = 0; i < 8; ++i) bf16_split3(piece_value(kb, k0 + i, lane & 15), pc[i]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      u32x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = (uint32_t)pc[2 * i][p] | ((uint32_t)pc[2 * i + 1][p] << 16);
+      dstb[(kb * 3 + p) * 64 + lane] = w;
+    }
   }
   if (Wh == nullptr) return;
   // the two-piece fp16 form: each model's quadratic-form values and its
@@ -247,43 +267,48 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
   // within 2^-25 absolute, 2^-23 of m, the lo piece's subnormal step); any
   // other set is scaled by the power of two 2^-e that brings m to [2^13,
   // 2^14) (fp16 holds up to 65504; the padded models' -1e30 included).
-  __shared__ int eq[16], ey[16];
-  if (threadIdx.x < 32) {
-    const int col = threadIdx.x & 15;
-    const bool quad = threadIdx.x < 16;
-    float mx = 0.0f;
-    for (int k = 0; k < (quad ? g.KQ : g.KY); ++k) mx = fmaxf(mx, fabsf(value(quad ? k : 4 * g.KQB + k, col)));
-    int ex = 0;
-    if (mx > 0.0f) frexpf(mx, &ex);   // mx < 2^ex
-    (quad ? eq : ey)[col] = (ex > 14 || ex < -1) ? ex - 14 : 0;
+  {
+    float mq = 0.0f, my = 0.0f;
+    for (int f = a; f < g.KQ; f += 16) mq = fmaxf(mq, fabsf(val[col][f]));
+    for (int f = a; f < g.KY; f += 16) my = fmaxf(my, fabsf(val[col][g.KQ + f]));
+    auto mx = [](float x, float y) { return fmaxf(x, y); };
+    mq = fold_reduce(mq, mx);
+    my = fold_reduce(my, mx);
+    if (a < 2) {
+      const float mm = a == 0 ? mq : my;
+      int ex = 0;
+      if (mm > 0.0f) frexpf(mm, &ex);   // mm < 2^ex
+      (a == 0 ? eq : ey)[col] = (ex > 14 || ex < -1) ? ex - 14 : 0;
+    }
+    if (a == 2) hmeta[(size_t)tile * kHfMeta + col] = s2;
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
-    const int col = threadIdx.x & 15, part = threadIdx.x >> 4;
+  if (tid >= 16 && tid < 64) {
+    const int slot = tid & 15, part = tid >> 4;
     float v = 0.0f;
-    if (part == 0) {
-      v = jcol[col] >= 0 ? ((const float *)m.sigma2)[jcol[col]] : 0.0f;
-    } else if (part < 3) {
-      v = ldexpf(1.0f, part == 1 ? eq[col] : ey[col]);
-    } else if (col == kHfPlain - 48) {
+    if (part < 3) {
+      v = ldexpf(1.0f, part == 1 ? eq[slot] : ey[slot]);
+    } else if (slot == kHfPlain - 48) {
       int any = 0;
       for (int c = 0; c < 16; ++c) any |= eq[c] | ey[c];
       v = any == 0 ? 1.0f : 0.0f;
     }
-    hmeta[(size_t)tile * kHfMeta + threadIdx.x] = v;
+    hmeta[(size_t)tile * kHfMeta + tid] = v;
   }
-  uint16_t *dsth = (uint16_t *)(Wh + (size_t)tile * kHfTileU32);
-  for (int e = threadIdx.x; e < kBfNKB * 64 * 8; e += blockDim.x) {
-    const int i = e & 7, lane = (e >> 3) & 63, kb = e >> 9;
-    const int k = 32 * (kb < kBfNKQ ? kb : kb - kBfNKQ) + 8 * (lane / 16) + i;
-    const bool inside = kb < kBfNKQ ? k < g.KQ : k < g.KY;
-    const int col = lane & 15;
-    const float v = inside ? ldexpf(value(kb < kBfNKQ ? k : 4 * g.KQB + k, col), -(kb < kBfNKQ ? eq[col] : ey[col]))
-                           : 0.0f;
-    uint16_t pc[2];
-    f16_split2(v, pc);
-    dsth[((size_t)(kb * 2 + 0) * 64 + lane) * 8 + i] = pc[0];
-    dsth[((size_t)(kb * 2 + 1) * 64 + lane) * 8 + i] = pc[1];
+  u32x4 *dsth = (u32x4 *)(Wh + (size_t)tile * kHfTileU32);
+  for (int e = tid; e < kBfNKB * 64; e += kFoldThreads) {
+    const int lane = e & 63, kb = e >> 6, k0 = 32 * (kb < kBfNKQ ? kb : 0) + 8 * (lane / 16);
+    const int sc = kb < kBfNKQ ? eq[lane & 15] : ey[lane & 15];
+    uint16_t pc[8][2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f16_split2(ldexpf(piece_value(kb, k0 + i, lane & 15), -sc), pc[i]);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      u32x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = (uint32_t)pc[2 * i][p] | ((uint32_t)pc[2 * i + 1][p] << 16);
+      dsth[(kb * 2 + p) * 64 + lane] = w;
+    }
   }
 }
 
