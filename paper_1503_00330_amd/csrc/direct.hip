@@ -386,45 +386,59 @@ hipError_t launch_subcost_reduce(int dtype, const void *sub, void *cost, int K, 
 }
 
 // ------------------------------------------------------------- update
-// Eq. (2) with the cost-to-go of Sec. 3.1.  Three stages, all in double:
-//  (1) one lane per rollout k: suffix sums S[i][k] = sum_{t>=i} cost[k][t];
-//  (2) block (chunk c, step i): over its rollouts, the local minimum m_c,
-//      Z_c = sum exp(-(S - m_c)/lambda) and N_c = sum exp(...) eps_{k,i};
-//  (3) one lane per step i merges the chunks in order (log-sum-exp shifts)
-//      and applies u_i += N / Z.  An optional stage (4) writes P_{k,i}.
-constexpr int kUpdChunk = 2048;   // rollouts per stage-2 block
-constexpr int kUpdThreads = 256;
+// Eq. (2) with the cost-to-go of Sec. 3.1, all sums in double:
+//  (1) the cost-to-go at the segment boundaries, S_b[j][k] = sum of row k's costs
+//      from step j seg_len on (only where (2) does not sum the rows itself);
+//  (2) one wave per (chunk of rollouts, segment of steps) walks its steps
+//      backwards with the cost-to-go of its rollouts in registers: the local
+//      minimum m_c, Z_c = sum exp(-(S - m_c)/lambda), N_c = sum exp(...) eps_{k,i};
+//  (3) one block per step merges the chunks (log-sum-exp shifts) and applies
+//      u_i += N / Z.  If the weights P_{k,i} are asked for, (4) writes
+//      them, walking the rows once more.
+// (2) is bound by its arithmetic: per (rollout, step) ten Philox rounds, two
+// Box-Muller pairs and one double exp.  (1) and (2) read the costs once each; S is
+// not stored.  K = 65536, T = 200 in float: 176 us with S and separate passes over it,
+// 98 us so (boundaries 12, partials 78 -- 230 vector instructions per pair --, merge 5).
+constexpr int kUpdChunk = 2048;   // the workspace holds one partial per so many rollouts and step, and S
+constexpr int kUpdSteps = 4, kUpdTiles = 2;   // steps and 64-rollout tiles per wave of stage 2
+constexpr int kUpdSegLen = 8;     // steps between boundaries (a multiple of it for long rows)
+constexpr int kUpdRows = 32;      // rows per block of stage 1
+constexpr int kUpdMaxSeg = 64;    // boundaries per row
+constexpr int kUpdQ = 2 + kMaxU;  // values per partial: m, Z, N
 
 size_t update_ws_bytes(int K, int T) {
   const int C = (K + kUpdChunk - 1) / kUpdChunk;
-  return align_up((size_t)K * T * 8, 256) + align_up((size_t)T * C * (2 + kMaxU) * 8, 256) +
+  return align_up((size_t)K * T * 8, 256) + align_up((size_t)T * C * kUpdQ * 8, 256) +
          align_up((size_t)T * 2 * 8, 256);
 }
 
-// Suffix sums S[t][k] = sum_{t' >= t} cost[k][t'] in double.  A block holds 64
-// rollouts and splits the horizon into 4 segments, one wave each: every lane
+// The weights W[t][k] = exp(-(S - m_t) / lambda) / Z_t of the merged minima and sums,
+// S = sum_{t' >= t} cost[k][t'] (t = 0 for a trajectory's weight).  A block holds 64
+// rollouts and splits the horizon into segments, one wave each: every lane
 // sums its (rollout, segment), the segment totals meet in LDS, and each lane
-// walks its segment backwards from the total of the later segments; the S
+// walks its segment backwards from the total of the later segments; the
 // stores of a wave cover 64 consecutive rollouts.  Two ways to read the costs:
 // each lane straight along its own row (every load of a wave touches 64 rows,
 // but all of a lane's loads are in flight at once: best when the grid is
 // small), or through a per-wave LDS tile in chunks of 16 steps (each load
 // covers 16 consecutive steps of 4 rollouts: best when bandwidth matters).
-constexpr int kSufK = 64, kSufSeg = 4, kSufChunk = 16;
-template <typename Real, bool kStaged>
-__global__ void __launch_bounds__(kSufK * kSufSeg) suffix_kernel(const Real *__restrict__ cost, int K, int T,
-                                                                 double *__restrict__ S) {
-  __shared__ double tile[kStaged ? kSufSeg : 1][kSufK][kSufChunk + 1];
-  __shared__ double tot[kSufSeg][kSufK];
-  const int lane = threadIdx.x % kSufK, seg = threadIdx.x / kSufK;
-  const int k0 = blockIdx.x * kSufK, k = k0 + lane;
-  const int lo = (int)((int64_t)seg * T / kSufSeg), hi = (int)((int64_t)(seg + 1) * T / kSufSeg);
+constexpr int kWgtK = 64, kWgtChunk = 16;
+template <typename Real, bool kStaged, int kSeg>
+__global__ void __launch_bounds__(kWgtK * kSeg) update_weights_kernel(const Real *__restrict__ cost, int K, int T,
+                                                                         double lambda, int weighting,
+                                                                         const double *__restrict__ norm,
+                                                                         double *__restrict__ W) {
+  __shared__ double tile[kStaged ? kSeg : 1][kWgtK][kWgtChunk + 1];
+  __shared__ double tot[kSeg][kWgtK];
+  const int lane = threadIdx.x % kWgtK, seg = threadIdx.x / kWgtK;
+  const int k0 = blockIdx.x * kWgtK, k = k0 + lane;
+  const int lo = (int)((int64_t)seg * T / kSeg), hi = (int)((int64_t)(seg + 1) * T / kSeg);
   const Real *row = cost + (int64_t)min(k, K - 1) * T;
-  double (*tl)[kSufChunk + 1] = tile[kStaged ? seg : 0];
+  double (*tl)[kWgtChunk + 1] = tile[kStaged ? seg : 0];
   // chunk [c0, c0 + w) of the segment into this wave's tile (rows past K read row K-1)
   auto load = [&](int c0, int w) {
-    for (int e = lane; e < kSufK * kSufChunk; e += kSufK) {
-      const int r = e / kSufChunk, c = e % kSufChunk;
+    for (int e = lane; e < kWgtK * kWgtChunk; e += kWgtK) {
+      const int r = e / kWgtChunk, c = e % kWgtChunk;
       if (c < w) tl[r][c] = (double)cost[(int64_t)min(k0 + r, K - 1) * T + c0 + c];
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -432,8 +446,8 @@ __global__ void __launch_bounds__(kSufK * kSufSeg) suffix_kernel(const Real *__r
   };
   double sum = 0.0;
   if constexpr (kStaged) {
-    for (int c0 = lo; c0 < hi; c0 += kSufChunk) {
-      const int w = min(kSufChunk, hi - c0);
+    for (int c0 = lo; c0 < hi; c0 += kWgtChunk) {
+      const int w = min(kWgtChunk, hi - c0);
       load(c0, w);
       for (int c = 0; c < w; ++c) sum += tl[lane][c];
       __builtin_amdgcn_wave_barrier();
@@ -444,14 +458,20 @@ __global__ void __launch_bounds__(kSufK * kSufSeg) suffix_kernel(const Real *__r
   tot[seg][lane] = sum;
   __syncthreads();
   double acc = 0.0;
-  for (int j = kSufSeg - 1; j > seg; --j) acc += tot[j][lane];
+  for (int j = kSeg - 1; j > seg; --j) acc += tot[j][lane];
+  double whole = 0.0;
+  for (int j = kSeg - 1; j >= 0; --j) whole += tot[j][lane];
+  auto weight = [&](int t) {
+    const double S = weighting == PI_W_TRAJECTORY ? whole : acc;
+    W[(int64_t)t * K + k] = exp(-(S - norm[2 * t]) / lambda) / norm[2 * t + 1];
+  };
   if constexpr (kStaged) {
-    for (int c1 = hi; c1 > lo; c1 -= kSufChunk) {
-      const int c0 = max(lo, c1 - kSufChunk), w = c1 - c0;
+    for (int c1 = hi; c1 > lo; c1 -= kWgtChunk) {
+      const int c0 = max(lo, c1 - kWgtChunk), w = c1 - c0;
       load(c0, w);
       for (int c = w - 1; c >= 0; --c) {
         acc += tl[lane][c];
-        if (k < K) S[(int64_t)(c0 + c) * K + k] = acc;
+        if (k < K) weight(c0 + c);
       }
       __builtin_amdgcn_wave_barrier();
     }
@@ -459,114 +479,327 @@ __global__ void __launch_bounds__(kSufK * kSufSeg) suffix_kernel(const Real *__r
     if (k >= K) return;
     for (int t = hi - 1; t >= lo; --t) {
       acc += (double)row[t];
-      S[(int64_t)t * K + k] = acc;
+      weight(t);
     }
   }
 }
 
+// Four consecutive costs of a row as doubles; steps from te on read as 0.  vec: every
+// row and the base are 16-byte aligned and T is a multiple of four.
 template <typename Real>
-__global__ void __launch_bounds__(kUpdThreads) update_chunk_kernel(ProbDev<Real> p, double lambda,
-                                                                   int weighting,
-                                                                   const uint32_t *__restrict__ iter,
-                                                                   const double *__restrict__ S,
-                                                                   double *__restrict__ part) {
-  __shared__ double red[kUpdThreads];
-  __shared__ double acc[kUpdThreads][kMaxU + 1];
-  const int c = blockIdx.x, i = blockIdx.y, C = gridDim.x;
-  const int K = p.K;
-  const int k0 = c * kUpdChunk, k1 = min(K, k0 + kUpdChunk);
-  const double *Si = S + (int64_t)(weighting == PI_W_TRAJECTORY ? 0 : i) * K;
-  double mn = 1.0 / 0.0;
-  for (int k = k0 + threadIdx.x; k < k1; k += blockDim.x) mn = fmin(mn, Si[k]);
-  red[threadIdx.x] = mn;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
+__device__ __forceinline__ void load_cost4(const Real *__restrict__ row, int t, int te, bool vec, Real (&c)[4]) {
+  if (vec) {
+    if (t >= te) {
+      c[0] = c[1] = c[2] = c[3] = (Real)0;
+    } else if constexpr (sizeof(Real) == 4) {
+      const float4 v = *(const float4 *)(row + t);
+      c[0] = v.x, c[1] = v.y, c[2] = v.z, c[3] = v.w;
+    } else {
+      const double2 v = *(const double2 *)(row + t), w = *(const double2 *)(row + t + 2);
+      c[0] = v.x, c[1] = v.y, c[2] = w.x, c[3] = w.y;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] = t + i < te ? row[t + i] : (Real)0;
   }
-  mn = red[0];
+}
+
+// Stage 1: lanes take (row, segment) pairs in memory order, the segment sums meet
+// in LDS, one lane per row walks them backwards, and the boundaries go out
+// transposed, 32 rows at a time.  Bound by reading the costs.
+template <typename Real>
+__global__ void __launch_bounds__(256) update_bound_kernel(const Real *__restrict__ cost, int K, int T, int seg_len,
+                                                           int nseg, int vec, double *__restrict__ Sb) {
+  __shared__ double tot[kUpdRows][kUpdMaxSeg + 1];
+  const int k0 = blockIdx.x * kUpdRows;
+  for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
+    const int r = e / nseg, j = e - r * nseg;
+    const Real *row = cost + (int64_t)min(k0 + r, K - 1) * T;
+    const int te = min(T, (j + 1) * seg_len);
+    double sum = 0.0;
+    for (int t = j * seg_len; t < te; t += 8) {
+      Real a[4], b[4];
+      load_cost4(row, t, te, vec, a);
+      load_cost4(row, t + 4, te, vec, b);
+      sum += (((double)a[0] + (double)a[1]) + ((double)a[2] + (double)a[3])) +
+             (((double)b[0] + (double)b[1]) + ((double)b[2] + (double)b[3]));
+    }
+    tot[r][j] = sum;
+  }
+  __syncthreads();
+  if (threadIdx.x < kUpdRows) {
+    double acc = 0.0;
+    for (int j = nseg - 1; j >= 0; --j) {
+      acc += tot[threadIdx.x][j];
+      tot[threadIdx.x][j] = acc;
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
+    const int r = e % kUpdRows, j = e / kUpdRows;
+    if (k0 + r < K) Sb[(int64_t)j * K + k0 + r] = tot[r][j];
+  }
+}
+
+// Cross-lane sums of doubles.  fold32 / fold16 add lane pairs 32 / 16 apart of two
+// values at once: a's sums end in the lower half-wave / even rows, b's in the upper / odd.
+template <int STEP>
+__device__ __forceinline__ void swap_rows(double &a, double &b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  uint32_t w[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t x = (uint32_t)(ua >> (32 * h)), y = (uint32_t)(ub >> (32 * h));
+    if constexpr (STEP == 32) {
+      auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+      w[h][0] = r[0], w[h][1] = r[1];
+    } else {
+      auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+      w[h][0] = r[0], w[h][1] = r[1];
+    }
+  }
+  a = __longlong_as_double((long long)((uint64_t)w[0][0] | ((uint64_t)w[1][0] << 32)));
+  b = __longlong_as_double((long long)((uint64_t)w[0][1] | ((uint64_t)w[1][1] << 32)));
+}
+template <int STEP>
+__device__ __forceinline__ double fold_rows(double a, double b) {
+  swap_rows<STEP>(a, b);
+  return a + b;
+}
+template <int ROT>
+__device__ __forceinline__ double row_rotate(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + ROT, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + ROT, 0xf, 0xf, true);
+  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+__device__ __forceinline__ double row_sum(double v) {   // over 16 lanes, in every lane
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  return v + row_rotate<1>(v);
+}
+__device__ __forceinline__ double wave_min(double v) {
+  v = fmin(v, row_rotate<8>(v));
+  v = fmin(v, row_rotate<4>(v));
+  v = fmin(v, row_rotate<2>(v));
+  v = fmin(v, row_rotate<1>(v));
+  double a = v, b = v;
+  swap_rows<16>(a, b);
+  v = fmin(a, b);
+  a = b = v;
+  swap_rows<32>(a, b);
+  return fmin(a, b);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row_sum(v);
+  v = fold_rows<16>(v, v);
+  return fold_rows<32>(v, v);
+}
+
+// d / lambda with the quotient's rounding error corrected once (d >= 0, inv = 1/lambda;
+// infinities and NaN pass through).
+__device__ __forceinline__ double scaled(double d, double lambda, double inv) {
+  const double q = d * inv, r = fma(-q, lambda, d);
+  return fabs(r) < 1.0 / 0.0 ? fma(r, inv, q) : (d > 0.0 ? q : d);
+}
+
+// Stage 2.  A wave holds NT tiles of 64 rollouts and SEG steps; it sums the costs
+// between its last step and the next boundary (nseg = 0: the row's end) itself.
+// Partials go to part[step][q][chunk].  Rollouts past K weigh exp(-inf) = 0.
+template <typename Real, int NU, int NT, int SEG>
+__global__ void __launch_bounds__(256) update_part_kernel(ProbDev<Real> p, double lambda, double inv, int weighting,
+                                                          const uint32_t *__restrict__ iter,
+                                                          const Real *__restrict__ cost,
+                                                          const double *__restrict__ Sb, int seg_len, int nseg,
+                                                          int vec, int C, double *__restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, K = p.K, T = p.T;
+  // waves of a block: neighbouring segments of the same rows, or neighbouring chunks
+  const int chunk = SEG > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
+  const int t0 = SEG > 1 ? (blockIdx.y * 4 + wave) * SEG : blockIdx.y;
+  if (chunk >= C || t0 >= T) return;
+  const bool whole = weighting == PI_W_TRAJECTORY;
   const uint32_t wc = stream_word(kTagCtrl, p.problem_id, *iter);
-  double z = 0.0, n[kMaxU] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = k0 + threadIdx.x; k < k1; k += blockDim.x) {
-    const double om = exp(-(Si[k] - mn) / lambda);
-    Real eps[4];
-    normals<Real, 4>(p.key0, p.key1, wc, (uint32_t)k, 0u, (uint32_t)i, eps);
-    z += om;
+  const Real *row[NT];
+  double acc[NT];
+  bool in[NT];
 #pragma unroll
-    for (int a = 0; a < kMaxU; ++a)
-      if (a < p.n_u) n[a] += om * (double)(p.noise_std[a] * eps[a]);
+  for (int n = 0; n < NT; ++n) {
+    const int64_t k = ((int64_t)chunk * NT + n) * 64 + lane;
+    in[n] = k < K;
+    const int64_t kc = in[n] ? k : K - 1;
+    row[n] = cost + kc * T;
+    acc[n] = 0.0;
+    // the cost-to-go behind the wave's last step (of the whole row for a
+    // trajectory's weight)
+    int from = whole ? 0 : min(T, t0 + SEG), to = T;
+    if (nseg > 0) {
+      const int j = whole ? 0 : t0 / seg_len + 1;
+      if (j < nseg) acc[n] = Sb[(int64_t)j * K + kc];
+      to = whole ? 0 : min(T, j * seg_len);
+    }
+    for (int t = from; t < to; t += 4) {
+      Real c[4];
+      load_cost4(row[n], t, to, false, c);   // from need not be a multiple of four
+      acc[n] += ((double)c[0] + (double)c[1]) + ((double)c[2] + (double)c[3]);
+    }
   }
-  acc[threadIdx.x][0] = z;
+  constexpr int W = SEG > 1 ? 4 : 1;   // steps per load
+#pragma unroll 1
+  for (int h = SEG - W; h >= 0; h -= W) {
+    if (t0 + h >= T) continue;
+    Real c[NT][4];
 #pragma unroll
-  for (int a = 0; a < kMaxU; ++a) acc[threadIdx.x][1 + a] = n[a];
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int q = 0; q <= kMaxU; ++q) acc[threadIdx.x][q] += acc[threadIdx.x + w][q];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    double *o = part + ((int64_t)i * C + c) * (2 + kMaxU);
-    o[0] = mn;
-    for (int q = 0; q <= kMaxU; ++q) o[1 + q] = acc[0][q];
+    for (int n = 0; n < NT; ++n) {
+      if (W > 1)
+        load_cost4(row[n], t0 + h, T, vec, c[n]);
+      else
+        c[n][0] = row[n][t0];
+    }
+#pragma unroll
+    for (int w = W - 1; w >= 0; --w) {
+      const int i = t0 + h + w;
+      if (i >= T) continue;
+      double S[NT], mn = 1.0 / 0.0;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        if (!whole) acc[n] += (double)c[n][w];
+        S[n] = in[n] ? acc[n] : 1.0 / 0.0;
+        mn = fmin(mn, S[n]);
+      }
+      mn = wave_min(mn);
+      // a chunk of infinite costs only: no weight, and no inf - inf
+      const double base = mn < 1.0 / 0.0 ? mn : 0.0;
+      double z = 0.0, N[NU];
+#pragma unroll
+      for (int a = 0; a < NU; ++a) N[a] = 0.0;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const double om = exp(-scaled(S[n] - base, lambda, inv));
+        Real eps[4];
+        normals<Real, NU>(p.key0, p.key1, wc, (uint32_t)((chunk * NT + n) * 64 + lane), 0u, (uint32_t)i, eps);
+        z += om;
+#pragma unroll
+        for (int a = 0; a < NU; ++a) N[a] += om * (double)(p.noise_std[a] * eps[a]);
+      }
+      double *o = part + (int64_t)i * kUpdQ * C + chunk;
+      if constexpr (NU == 2) {
+        const double x = row_sum(fold_rows<16>(fold_rows<32>(N[0], N[1]), fold_rows<32>(z, z)));
+        // rows: N0, z, N1, z
+        if (lane == 0) o[0] = mn, o[2 * C] = x;
+        if (lane == 16) o[C] = x;
+        if (lane == 32) o[3 * C] = x;
+      } else {
+        const double x = row_sum(fold_rows<16>(fold_rows<32>(N[0], N[1]), fold_rows<32>(N[2], N[3])));
+        z = wave_sum(z);
+        // rows: N0, N2, N1, N3
+        if (lane == 0) o[0] = mn, o[C] = z, o[2 * C] = x;
+        if (lane == 16) o[4 * C] = x;
+        if (lane == 32) o[3 * C] = x;
+        if (lane == 48) o[5 * C] = x;
+      }
+    }
   }
 }
 
+// Stage 3, one block per step: every lane reads its chunks' partials at once, so the
+// block waits for memory once; then minima and sums over the waves and through LDS.
 template <typename Real>
-__global__ void update_apply_kernel(int T, int C, int n_u, double lambda,
-                                    const double *__restrict__ part,
-                                    Real *__restrict__ u_nom, double *__restrict__ norm,
-                                    uint32_t *__restrict__ iter) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) update_apply_kernel(int C, int n_u, double lambda,
+                                                           const double *__restrict__ part,
+                                                           Real *__restrict__ u_nom, double *__restrict__ norm,
+                                                           uint32_t *__restrict__ iter) {
+  __shared__ double wmin[4], wsum[4][1 + kMaxU];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.x;
   // the iteration's draws have all been consumed: advance the iteration word
-  if (i == 0) *iter += 1u;
-  if (i >= T) return;
-  const double *pi_ = part + (int64_t)i * C * (2 + kMaxU);
-  double mn = 1.0 / 0.0;
-  for (int c = 0; c < C; ++c) mn = fmin(mn, pi_[c * (2 + kMaxU)]);
-  double z = 0.0, n[kMaxU] = {0.0, 0.0, 0.0, 0.0};
-  for (int c = 0; c < C; ++c) {
-    const double *q = pi_ + c * (2 + kMaxU);
-    const double f = (q[0] == mn) ? 1.0 : exp(-(q[0] - mn) / lambda);
-    z += q[1] * f;
-    for (int a = 0; a < kMaxU; ++a) n[a] += q[2 + a] * f;
+  if (i == 0 && threadIdx.x == 0) *iter += 1u;
+  const double *pi_ = part + (int64_t)i * kUpdQ * C;
+  double m = 1.0 / 0.0, v[1 + kMaxU] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int c = threadIdx.x; c < C; c += 256) {
+    const double mc = pi_[c], mn = fmin(m, mc);
+    const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda), fc = mc == mn ? 1.0 : exp(-(mc - mn) / lambda);
+#pragma unroll
+    for (int q = 0; q <= kMaxU; ++q)
+      if (q <= n_u) v[q] = v[q] * f + pi_[(int64_t)(1 + q) * C + c] * fc;
+    m = mn;
   }
-  for (int a = 0; a < n_u; ++a) u_nom[i * n_u + a] = (Real)((double)u_nom[i * n_u + a] + n[a] / z);
-  norm[2 * i] = mn;
-  norm[2 * i + 1] = z;
+  const double wm = wave_min(m);
+  if (lane == 0) wmin[wave] = wm;
+  __syncthreads();
+  const double mn = fmin(fmin(wmin[0], wmin[1]), fmin(wmin[2], wmin[3]));
+  const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda);
+#pragma unroll
+  for (int q = 0; q <= kMaxU; ++q) {
+    const double w = q <= n_u ? wave_sum(v[q] * f) : 0.0;
+    if (lane == 0) wsum[wave][q] = w;
+  }
+  __syncthreads();
+  auto total = [&](int q) { return (wsum[0][q] + wsum[1][q]) + (wsum[2][q] + wsum[3][q]); };
+  const int a = threadIdx.x;
+  if (a < n_u) u_nom[i * n_u + a] = (Real)((double)u_nom[i * n_u + a] + total(1 + a) / total(0));
+  if (a == 0) {
+    norm[2 * i] = mn;
+    norm[2 * i + 1] = total(0);
+  }
 }
 
-__global__ void update_weights_kernel(int K, int T, double lambda, int weighting,
-                                      const double *__restrict__ S, const double *__restrict__ norm,
-                                      double *__restrict__ W) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)K * T) return;
-  const int64_t i = idx / K, k = idx % K;
-  const double s = S[(weighting == PI_W_TRAJECTORY ? 0 : i) * (int64_t)K + k];
-  W[idx] = exp(-(s - norm[2 * i]) / lambda) / norm[2 * i + 1];
+template <typename Real, int NU>
+static void update_part(const ProbDev<Real> &p, const Real *cost, const uint32_t *iter, double *ws, double **part,
+                        int *nchunk, double lambda, int weighting, hipStream_t s) {
+  const int K = p.K, T = p.T;
+  const double inv = 1.0 / lambda;
+  // Up to 12 (tile, step) pairs per compute unit (of 256), every wave takes one: at
+  // 2048 x 50 in float 12.8 us against 16.6 with tiles and steps grouped, at 4096 x 100
+  // 19.3 against 16.9.  Rows of up to 40 steps are then summed by the waves themselves,
+  // which spares a launch: 3000 x 20 9.9 us against 11.1, 1000 x 50 13.2 against 11.9.
+  // So are rows of one segment at any K, as S_b and the partials need the place of
+  // more than that many steps of S.
+  const bool single = (int64_t)((K + 63) / 64) * T <= 3072, direct = T <= kUpdSegLen || (single && T <= 40);
+  const int nt = direct || single ? 1 : kUpdTiles, C = (K + 64 * nt - 1) / (64 * nt);
+  *nchunk = C;
+  if (direct) {
+    *part = ws;
+    hipLaunchKernelGGL((update_part_kernel<Real, NU, 1, 1>), dim3((C + 3) / 4, T), dim3(256), 0, s, p, lambda, inv,
+                       weighting, iter, cost, (const double *)nullptr, 0, 0, 0, C, ws);
+    return;
+  }
+  const int seg_len = kUpdSegLen * ((T + kUpdSegLen * kUpdMaxSeg - 1) / (kUpdSegLen * kUpdMaxSeg));
+  const int nseg = (T + seg_len - 1) / seg_len;
+  const int vec = T % 4 == 0 && (uintptr_t)cost % 16 == 0;
+  *part = (double *)((char *)ws + align_up((size_t)K * nseg * 8, 256));
+  hipLaunchKernelGGL(update_bound_kernel<Real>, dim3((K + kUpdRows - 1) / kUpdRows), dim3(256), 0, s, cost, K, T,
+                     seg_len, nseg, vec, ws);
+  if (single)
+    hipLaunchKernelGGL((update_part_kernel<Real, NU, 1, 1>), dim3((C + 3) / 4, T), dim3(256), 0, s, p, lambda, inv,
+                       weighting, iter, cost, (const double *)ws, seg_len, nseg, vec, C, *part);
+  else
+    hipLaunchKernelGGL((update_part_kernel<Real, NU, kUpdTiles, kUpdSteps>),
+                       dim3(C, (T + 4 * kUpdSteps - 1) / (4 * kUpdSteps)), dim3(256), 0, s, p, lambda, inv, weighting,
+                       iter, cost, (const double *)ws, seg_len, nseg, vec, C, *part);
 }
 
 template <typename Real>
 static hipError_t update_t(const ProbDev<Real> &p, const Real *cost, const uint32_t *iter,
                            Real *u_nom, double *W, void *ws, double lambda, int weighting,
                            hipStream_t s) {
-  const int K = p.K, T = p.T, C = (K + kUpdChunk - 1) / kUpdChunk;
-  double *S = (double *)ws;
-  double *part = (double *)((char *)ws + align_up((size_t)K * T * 8, 256));
-  double *norm = (double *)((char *)part + align_up((size_t)T * C * (2 + kMaxU) * 8, 256));
-  const unsigned nsb = (unsigned)((K + kSufK - 1) / kSufK);
-  if (nsb >= 256)   // enough blocks to cover the compute units: read through LDS
-    hipLaunchKernelGGL((suffix_kernel<Real, true>), dim3(nsb), dim3(kSufK * kSufSeg), 0, s, cost, K, T, S);
+  const int K = p.K, T = p.T;
+  double *part;
+  double *norm = (double *)((char *)ws + update_ws_bytes(K, T) - align_up((size_t)T * 2 * 8, 256));
+  int C;
+  if (p.n_u <= 2)
+    update_part<Real, 2>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
   else
-    hipLaunchKernelGGL((suffix_kernel<Real, false>), dim3(nsb), dim3(kSufK * kSufSeg), 0, s, cost, K, T, S);
-  hipLaunchKernelGGL(update_chunk_kernel<Real>, dim3(C, T), dim3(kUpdThreads), 0, s, p, lambda,
-                     weighting, iter, (const double *)S, part);
-  hipLaunchKernelGGL(update_apply_kernel<Real>, dim3((T + 63) / 64), dim3(64), 0, s, T, C, p.n_u,
-                     lambda, (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
+    update_part<Real, 4>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
+  hipLaunchKernelGGL(update_apply_kernel<Real>, dim3(T), dim3(256), 0, s, C, p.n_u, lambda,
+                     (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
   if (W) {
-    const int64_t n = (int64_t)K * T;
-    hipLaunchKernelGGL(update_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, K,
-                       T, lambda, weighting, (const double *)S, (const double *)norm, W);
+    const unsigned nb = (unsigned)((K + kWgtK - 1) / kWgtK);
+    if (nb >= 256)   // enough blocks to cover the compute units: read through LDS
+      hipLaunchKernelGGL((update_weights_kernel<Real, true, 4>), dim3(nb), dim3(kWgtK * 4), 0, s, cost, K, T, lambda,
+                         weighting, (const double *)norm, W);
+    else             // more waves per block instead
+      hipLaunchKernelGGL((update_weights_kernel<Real, false, 16>), dim3(nb), dim3(kWgtK * 16), 0, s, cost, K, T,
+                         lambda, weighting, (const double *)norm, W);
   }
   return hipGetLastError();
 }

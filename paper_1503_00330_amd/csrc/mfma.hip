@@ -1946,13 +1946,10 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
           // counter block blk-1 of the sub-rollout's draw: normals 4(blk-1) .. 4(blk-1)+3
           const Philox4 r4 = philox4x32_10((uint32_t)(t + cc), kk, (mm << 4) | (uint32_t)(blk - 1), wd,
                                            p.key0, p.key1);
-          float s0, c0, s1, c1;
-          const float rad0 = sqrtf(-2.0f * logf(unit_open<float>(r4.v[0])));
-          const float rad1 = sqrtf(-2.0f * logf(unit_open<float>(r4.v[2])));
-          sincos_2pi(unit_open<float>(r4.v[1]), &s0, &c0);
-          sincos_2pi(unit_open<float>(r4.v[3]), &s1, &c1);
           float *dst = &rs.xi_s[cc][rr][4 * (blk - 1)];
-          const float v[4] = {rad0 * c0, rad0 * s0, rad1 * c1, rad1 * s1};
+          float v[4];
+          box_muller(r4.v[0], r4.v[1], &v[0], &v[1]);
+          box_muller(r4.v[2], r4.v[3], &v[2], &v[3]);
           constexpr int XIS = MixSmem<D, MT, NW, PF>::XIS;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
