@@ -80,8 +80,10 @@ enum { PI_W_COST_TO_GO = 0, PI_W_TRAJECTORY = 1 };
  * d = 16); PI_VARIANT_AUTO picks it whenever those hold (rollouts of the 12-state
  * quadrotor with K max(M,1) > 2048 that leave tile_samples, tile_waves and
  * tile_split to the library too run PI_VARIANT_MFMA_BF16X3 instead, the same
- * float32 products), and requesting it otherwise returns PI_ERR_UNSUPPORTED.  PI_VARIANT_DIRECT is the per-sample
- * form (any d, float32 or float64).  PI_VARIANT_MFMA_BF16X3 (rollouts of the
+ * float32 products; rollouts of the other dynamics that leave them too run
+ * PI_VARIANT_DIRECT on models of up to 40 local models per output, up to 64 for
+ * K max(M,1) <= 4096), and requesting it otherwise returns PI_ERR_UNSUPPORTED.
+ * PI_VARIANT_DIRECT is the per-sample form (any d, float32 or float64).  PI_VARIANT_MFMA_BF16X3 (rollouts of the
  * float32 12-state quadrotor, d = 16; 8 waves need tiles of <= 16) runs the same
  * contraction on the bf16 matrix instructions: every float32 operand is the
  * exact sum of three bf16 pieces and the six piece products of weight at

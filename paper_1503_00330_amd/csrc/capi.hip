@@ -301,12 +301,22 @@ TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles) {
   return best;
 }
 
+// Whether a float32 problem that leaves the whole launch to the library (contraction,
+// tile, waves, pairing) runs on the small-model kernel instead of the matrix cores,
+// which pay a workgroup's barriers and an almost empty tile per step there.  Its
+// costs are the nearer ones (models 15/15/24, 1000 rollouts x 50 steps: 6e-8 of the
+// oracle's against 3e-7); times beside its limits.
+bool small_rollout(const pi_problem *p, const pi_lwpr *m, int64_t n) {
+  return p->variant == PI_VARIANT_AUTO && p->tile_samples == 0 && p->tile_waves == 0 && p->tile_split == 0 &&
+         p->dtype == PI_F32 && rollout_wave_ok(p->dyn, p->dtype, m->d, m->n_out, m->L_off, n);
+}
+
 RolloutPlan rollout_plan(const pi_problem *p, const pi_lwpr *m) {
   RolloutPlan r;
   const int64_t n = (int64_t)p->K * (p->M > 0 ? p->M : 1);
   const bool auto_bf = auto_pieces(p, m, n);
   r.pf = auto_bf ? kPfBf16x3 : variant_pf(p->variant);
-  r.mfma = p->variant == PI_VARIANT_MFMA || r.pf != kPfF32 || (p->variant == PI_VARIANT_AUTO && mfma_model_ok(m));
+  r.mfma = p->variant == PI_VARIANT_MFMA || r.pf != kPfF32 || (p->variant == PI_VARIANT_AUTO && mfma_model_ok(m) && !small_rollout(p, m, n));
   r.bf = r.pf != kPfF32;
   TileChoice tile{16, 4};
   if (r.bf && p->tile_samples == 0 && p->dyn == PI_DYN_QUAD12 && bf_model_ok(m))

@@ -148,6 +148,20 @@ __device__ __forceinline__ void normals_n(int n, uint32_t key0, uint32_t key1, u
     normals<Real, 8>(key0, key1, word3, k, m, t, out);
 }
 
+// ------------------------------------------------------------ cross-lane
+// v of the lane CTRL names (a DPP control), within rows of 16.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+
 // ---------------------------------------------------------------- dynamics
 // The LWPR input of a state and an applied control: z = [x ; u] for the point
 // mass and the 12-state quadrotor; for the hybrid quadrotor (Sec. 4.1: the
@@ -304,8 +318,8 @@ __device__ __forceinline__ Real state_cost_quad(const ProbDev<Real> &p, const Re
       ob += smooth ? p.obs_penalty * exp_(-p.obs_decay * d[j]) : (d[j] < r[j] * r[j] ? (Real)1 : (Real)0);
     }
   }
-  ob += __shfl_xor(ob, 1);
-  ob += __shfl_xor(ob, 2);
+  ob += dpp<0xB1>(ob);   // the neighbour, then the other pair
+  ob += dpp<0x4E>(ob);
   if (smooth) return c + ob;
   return ob > (Real)0 ? c + p.obs_penalty : c;
 }

@@ -324,10 +324,208 @@ static hipError_t rollout_group_t(const RolloutArgs<Real> &ra, const ModelArgs &
   return hipGetLastError();
 }
 
+// -------------------------------------------------- small-model rollouts
+// P lanes share one sub-rollout and its models (lane l: models l, l + P, ..), a wave
+// holds 64 / P of them, and nothing but the wave's own lanes takes part in a step: the
+// state is stepped by all P lanes alike, statistics cross lanes by DPP, there is no
+// barrier.  The mixture is evaluated in two passes over registers (maximum, weights
+// and mean; then the spread about the mean), one exponential per model.  Bound by
+// the serial chain of a step where the chip is not full (P = 16), by vector
+// instructions where it is (P = 4).  The whole step of 256 rollouts x 20, models
+// 16/16, in double: 144 -> 55 us; 1000 x 50, models 15/15/24, in float 162 us (matrix
+// cores) -> 65 us, 30400 sub-rollouts 366 -> 209 us.
+// Over the P lanes of a sub-rollout, the same bits in every lane: neighbours, pairs,
+// then half rows and rows mirrored.
+template <int P, typename Real, class Op>
+__device__ __forceinline__ Real lanes_reduce(Real v, Op op) {
+  static_assert(P == 4 || P == 8 || P == 16);
+  v = op(v, dpp<0xB1>(v));
+  v = op(v, dpp<0x4E>(v));
+  if constexpr (P >= 8) v = op(v, dpp<0x141>(v));
+  if constexpr (P >= 16) v = op(v, dpp<0x140>(v));
+  return v;
+}
+__device__ __forceinline__ float exp_act(float x) { return __builtin_amdgcn_exp2f(x); }   // base 2, x <= 0
+__device__ __forceinline__ double exp_act(double x) { return exp(x); }
+__device__ __forceinline__ float root_(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double root_(double x) { return sqrt(x); }
+
+template <typename Real, int D>
+constexpr int rec_pad() {   // record stride in LDS: whole 16-byte words
+  return (rec_stride<Real, D>() * (int)sizeof(Real) + 15) / 16 * 16 / (int)sizeof(Real);
+}
+
+template <typename Real, int DYN, int P, int NJ>
+__global__ void __launch_bounds__(64, NJ > 2 ? 2 : 1) rollout_wave_kernel(RolloutArgs<Real> ra, ModelArgs m,
+                                                                        const Real *__restrict__ rec) {
+  using DD = DynDims<DYN>;
+  constexpr int D = DD::D, NX = DD::NX, NU = DD::NU, NO = DD::NO;
+  constexpr int RS = rec_stride<Real, D>(), RSP = rec_pad<Real, D>();
+  extern __shared__ __attribute__((aligned(16))) char wave_lds[];
+  Real *tile = (Real *)wave_lds;
+  __shared__ Real obs[kMaxObs * 3];
+  const ProbDev<Real> &p = ra.p;
+  for (int i = threadIdx.x; i < 3 * p.n_obs; i += 64) obs[i] = p.obs[i];
+  for (int i = threadIdx.x; i < m.Ltot * RS; i += 64) tile[i / RS * RSP + i % RS] = rec[i];
+  __syncthreads();
+  const int l = threadIdx.x % P;
+  const int64_t n = (int64_t)p.K * p.Ms, row = (int64_t)blockIdx.x * (64 / P) + threadIdx.x / P;
+  const uint32_t s = (uint32_t)min(row, n - 1);   // lanes past the last sub-rollout repeat it
+  const uint32_t k = p.Ms == 1 ? s : s / (uint32_t)p.Ms, mm = s - k * (uint32_t)p.Ms;
+  const uint32_t it = *ra.iter;
+  const uint32_t wc = stream_word(kTagCtrl, p.problem_id, it);
+  const uint32_t wd = stream_word(kTagDyn, p.problem_id, it);
+  const Real kAct = (Real)(sizeof(Real) == 4 ? -0.72134752044448170368 : -0.5);   // -log2(e) / 2 in float
+  const Real ninf = -(Real)(1.0 / 0.0);
+  auto add = [](Real a, Real b) { return a + b; };
+  auto mx2 = [](Real a, Real b) { return a > b ? a : b; };
+  Real x[NX], lo[NX];
+#pragma unroll
+  for (int a = 0; a < NX; ++a) x[a] = ra.x0[a], lo[a] = 0;
+  for (int tb = 0; tb < p.T; tb += P) {
+    // lane l draws step tb + l
+    Real uc[NU], xc[NO], cc = 0, keep = 0;
+    {
+      const int t = min(tb + l, p.T - 1);
+      Real e[NU], pert[NU];
+      normals<Real, NU>(p.key0, p.key1, wc, k, 0u, (uint32_t)t, e);
+#pragma unroll
+      for (int a = 0; a < NU; ++a) {
+        pert[a] = p.noise_std[a] * e[a];
+        uc[a] = ra.u_nom[t * NU + a] + pert[a];
+      }
+#pragma unroll
+      for (int o = 0; o < NO; ++o) xc[o] = 0;
+      if (p.M > 0) normals<Real, NO>(p.key0, p.key1, wd, k, mm, (uint32_t)t, xc);
+      if constexpr (DYN == kDynQuadHybrid)
+        if (p.ctrl_cost) cc = control_cost<Real>(p, ra.u_nom + t * NU, pert);
+    }
+    const int nt = min(P, p.T - tb);
+    for (int tc = 0; tc < nt; ++tc) {
+      Real u[NU], xi[NO], z[D], acc[NO];
+#pragma unroll
+      for (int a = 0; a < NU; ++a) u[a] = __shfl(uc[a], tc, P);
+#pragma unroll
+      for (int o = 0; o < NO; ++o) xi[o] = p.M > 0 ? __shfl(xc[o], tc, P) : (Real)0;
+      lwpr_input<DYN>(x, u, z);
+      int off = 0;
+      if constexpr (NJ > 2) asm volatile("" : "+s"(off));   // keep the records in LDS
+// every model's distance and prediction, then the statistics of all
+      // outputs side by side, whose chains hide each other's latency
+      Real act[NO][NJ], y[NO][NJ], s2[NO][NJ], mx[NO], Z[NO], S1[NO], S2[NO], mu[NO];
+      constexpr int G = NJ > 2 ? 2 : NJ;   // models between two looks at the output's end
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        const int j0 = m.L_off[o], L = m.L_off[o + 1] - j0;
+#pragma unroll
+        for (int g = 0; g < NJ; g += G) {
+#pragma unroll
+          for (int jj = g; jj < g + G; ++jj) act[o][jj] = ninf, y[o][jj] = 0, s2[o][jj] = 0;
+          if (NJ > 2 && g * P >= L) continue;
+#pragma unroll
+          for (int jj = g; jj < g + G; ++jj) {
+            const int j = jj * P + l;
+            const Real *r = tile + off + (j0 + min(j, L - 1)) * RSP;
+            Real q;
+            eval_record<Real, D>(r, z, q, y[o][jj]);
+            act[o][jj] = j < L ? kAct * q : ninf;
+            s2[o][jj] = r[RS - 1];
+          }
+        }
+      }
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        mx[o] = act[o][0];
+#pragma unroll
+        for (int jj = 1; jj < NJ; ++jj) mx[o] = mx2(act[o][jj], mx[o]);
+        mx[o] = lanes_reduce<P>(mx[o], mx2);
+      }
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        Z[o] = S1[o] = S2[o] = 0;
+#pragma unroll
+        for (int jj = 0; jj < NJ; ++jj) {
+          act[o][jj] = exp_act(act[o][jj] - mx[o]);
+          Z[o] += act[o][jj];
+          S1[o] += act[o][jj] * y[o][jj];
+          S2[o] += act[o][jj] * s2[o][jj];
+        }
+        Z[o] = lanes_reduce<P>(Z[o], add);
+        S1[o] = lanes_reduce<P>(S1[o], add);
+      }
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        mu[o] = ratio(S1[o], Z[o]);
+        acc[o] = mu[o];
+      }
+      if (p.M > 0) {
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+          Real M2 = 0;
+#pragma unroll
+          for (int jj = 0; jj < NJ; ++jj) {
+            const Real dy = y[o][jj] - mu[o];
+            M2 += act[o][jj] * dy * dy;
+          }
+          acc[o] += root_(ratio(lanes_reduce<P>(M2 + S2[o], add), Z[o])) * xi[o];
+        }
+      }
+      Real xn[NX];
+      if constexpr (sizeof(Real) == 4)
+        euler_step_comp<Real>(DYN, p.dt, x, acc, u, xn, lo);
+      else
+        euler_step<Real>(DYN, p.dt, x, acc, u, xn);
+#pragma unroll
+      for (int a = 0; a < NX; ++a) x[a] = xn[a];
+      Real c = p.dt * state_cost_quad<Real, DYN>(p, obs, x, l % 4);
+      if constexpr (DYN == kDynQuadHybrid)
+        if (p.ctrl_cost) c += __shfl(cc, tc, P);
+      keep = l == tc ? c : keep;
+    }
+    // lane l holds the cost of step tb + l
+    if (row < n && l < nt) ra.cost[row * p.T + tb + l] = keep;
+  }
+}
+
+// The lanes per sub-rollout: 16 while their waves leave the chip's vector units idle,
+// then 4 (8 for more than 32 models per output), which reduce less and hold each
+// lane's whole share of the models.  50 steps, models 15/15/24, float: 4000
+// sub-rollouts 77 us with 16 lanes and 159 with 4, 16000 172 and 168, 30400 319 and
+// 213; 16/16: 16000 97 and 139, 30400 177 and 182; 30/40/35: 4000 157 (8 lanes 183),
+// 8000 195 (181); 16/16 in double: 8000 163 and 236, 16000 301 and 259.
+template <typename Real, int DYN>
+static hipError_t rollout_wave_t(const RolloutArgs<Real> &ra, const ModelArgs &m, const void *rec, hipStream_t s) {
+  const int64_t n = (int64_t)ra.p.K * ra.p.Ms;
+  const int L = max_models(m.n_out, m.L_off);
+  const int64_t wide = L > 32 ? 6144 : L <= 16 && sizeof(Real) == 4 ? 24576 : 12288;
+  const size_t lds = wave_lds_bytes(sizeof(Real) == 8 ? PI_F64 : PI_F32, m.d, m.Ltot);
+  auto go = [&](auto kernel, int lanes) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n * lanes + 63) / 64)), dim3(64), lds, s, ra, m, (const Real *)rec);
+  };
+  if (n <= wide) {
+    if (L <= 16)
+      go(rollout_wave_kernel<Real, DYN, 16, 1>, 16);
+    else if (L <= 32)
+      go(rollout_wave_kernel<Real, DYN, 16, 2>, 16);
+    else
+      go(rollout_wave_kernel<Real, DYN, 16, 4>, 16);
+  } else if (L <= 16) {
+    go(rollout_wave_kernel<Real, DYN, 4, 4>, 4);
+  } else if (L <= 32) {
+    go(rollout_wave_kernel<Real, DYN, 4, 8>, 4);
+  } else {
+    go(rollout_wave_kernel<Real, DYN, 8, 8>, 8);
+  }
+  return hipGetLastError();
+}
+
 template <typename Real>
 static hipError_t rollout_direct_t(const RolloutArgs<Real> &ra, const ModelArgs &m, const void *rec,
                                    hipStream_t s) {
   const int64_t n = (int64_t)ra.p.K * ra.p.Ms;
+  if (rollout_wave_ok(ra.p.dyn, sizeof(Real) == 8 ? PI_F64 : PI_F32, m.d, m.n_out, m.L_off, n))
+    return ra.p.dyn == kDynPointMass2D ? rollout_wave_t<Real, kDynPointMass2D>(ra, m, rec, s)
+                                       : rollout_wave_t<Real, kDynQuadHybrid>(ra, m, rec, s);
   // fewer sub-rollouts than 32 lanes per compute unit: split the models over lanes
   if (n < 256 * 32) return rollout_group_t(ra, m, rec, s);
   const unsigned nb = (unsigned)((n + 127) / 128);
@@ -566,24 +764,17 @@ __device__ __forceinline__ double fold_rows(double a, double b) {
   swap_rows<STEP>(a, b);
   return a + b;
 }
-template <int ROT>
-__device__ __forceinline__ double row_rotate(double v) {
-  const uint64_t u = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + ROT, 0xf, 0xf, true);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + ROT, 0xf, 0xf, true);
-  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
-}
 __device__ __forceinline__ double row_sum(double v) {   // over 16 lanes, in every lane
-  v += row_rotate<8>(v);
-  v += row_rotate<4>(v);
-  v += row_rotate<2>(v);
-  return v + row_rotate<1>(v);
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x122>(v);
+  return v + dpp<0x121>(v);
 }
 __device__ __forceinline__ double wave_min(double v) {
-  v = fmin(v, row_rotate<8>(v));
-  v = fmin(v, row_rotate<4>(v));
-  v = fmin(v, row_rotate<2>(v));
-  v = fmin(v, row_rotate<1>(v));
+  v = fmin(v, dpp<0x128>(v));
+  v = fmin(v, dpp<0x124>(v));
+  v = fmin(v, dpp<0x122>(v));
+  v = fmin(v, dpp<0x121>(v));
   double a = v, b = v;
   swap_rows<16>(a, b);
   v = fmin(a, b);

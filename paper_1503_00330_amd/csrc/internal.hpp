@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/pi2rh.h"
 #include "common.hpp"
 
@@ -26,8 +28,32 @@ struct ModelArgs {
 // y = beta0 + b . dl with dl = z - c.  b is the PLS chain
 // s_r = u_r . r_r, r_{r+1} = r_r - s_r p_r folded into one linear map.
 inline int direct_stride(int d) { return d + d * (d + 1) / 2 + d + 2; }
+inline int max_models(int n_out, const int *L_off) {
+  int L = 1;
+  for (int o = 0; o < n_out; ++o) L = std::max(L, L_off[o + 1] - L_off[o]);
+  return L;
+}
 inline size_t direct_bytes(int dtype, int d, int Ltot) {
   return align_up((size_t)Ltot * direct_stride(d) * (dtype == PI_F64 ? 8 : 4), 256);
+}
+// Small-model rollouts (rollout_wave_kernel): the records of the whole model in a
+// block's LDS (padded to 16 bytes), at most kWaveModels models per output.  Up to 40
+// (32 in double) at any size; beyond, while a sub-rollout's 16 lanes find idle vector
+// units, and in double where a lane per sub-rollout leaves most of them idle.
+// 50 steps, against the next best form: 30/40/35 models, float, 1000 rollouts 113 us
+// (matrix cores 166), 30400 394 (452), 60/64/50 1000 123 (181), 30400 585 (510);
+// double, 30/25 1000 84 (16 lanes and LDS exchange 257), 30400 574 (lane per
+// rollout 1342), 56/50 1000 219 (318), 6000 826 (477), 12000 1004 (2431), 128000 7299 (5924).
+constexpr int kWaveLds = 32768, kWaveModels = 64;
+inline size_t wave_lds_bytes(int dtype, int d, int Ltot) {
+  return (size_t)Ltot * align_up((size_t)direct_stride(d) * (dtype == PI_F64 ? 8 : 4), 16);
+}
+inline bool rollout_wave_ok(int dyn, int dtype, int d, int n_out, const int *L_off, int64_t n) {
+  const int L = max_models(n_out, L_off);
+  const bool f64 = dtype == PI_F64;
+  const bool n_ok = f64 ? n <= 2048 || (n >= 8192 && n <= 32768) : n <= 4096;
+  return dyn != PI_DYN_QUAD12 && (L <= (f64 ? 32 : 40) || (L <= kWaveModels && n_ok)) &&
+         wave_lds_bytes(dtype, d, L_off[n_out]) <= kWaveLds;
 }
 
 // ---- MFMA (FP32) folded model ---------------------------------------------

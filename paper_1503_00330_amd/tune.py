@@ -202,7 +202,12 @@ def tune_rollout(prob, model, candidates: Optional[Iterable[Tuple[int, int, int,
 
 def ensure(prob, model, path: Optional[str] = None, reps: int = 3):
     """Applies the cached launch for this shape, tuning (and caching) it first
-    if there is none.  Returns the (samples, waves, split, variant) in use."""
+    if there is none.  A problem that the library runs on its small-model kernel,
+    which has no launch shape, is left to it.  Returns the (samples, waves, split,
+    variant) in use."""
+    from . import rollout_describe
+    if _requested(prob) == 0 and rollout_describe(prob, model)["variant"] == "direct":
+        return _launch(prob)
     if not apply(prob, model, path):
         best, _ = tune_rollout(prob, model, reps=reps, path=path)
         _set_launch(prob, best)
