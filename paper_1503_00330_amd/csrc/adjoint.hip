@@ -468,37 +468,58 @@ __global__ void adj_param_finish_kernel(ModelArgs m, const Real *__restrict__ mo
 // Stage 4a, matrix-core sums: G_j = sum qbar [z z^T, z, 1] and sum ybar per
 // chunk, added in chunk order in double, then centred at c_j:
 //   sum qbar dl dl^T = G_zz - G_z c^T - c G_z^T + G_1 c c^T,  sum qbar dl = G_z - G_1 c.
+// One block per model: a thread per sum adds the chunks (neighbouring threads read
+// neighbouring sums), then per entry of dJ/dD and per component of dJ/dc.  With a
+// thread per model 40 chunks of 1536 models took 436 us, 11 us so.
+constexpr int kFinThreads = 192;
 template <int DYN>
-__global__ void adj_param_mfma_finish_kernel(ModelArgs m, MfmaLayout l, const float *__restrict__ model, int nch,
-                                             const float *__restrict__ gpart, int width, double scale,
-                                             const double *gJ, float *__restrict__ gc, float *__restrict__ gD) {
+__global__ void __launch_bounds__(kFinThreads) adj_param_mfma_finish_kernel(
+    ModelArgs m, MfmaLayout l, const float *__restrict__ model, int nch, const float *__restrict__ gpart, int width,
+    double scale, const double *gJ, float *__restrict__ gc, float *__restrict__ gD) {
   using G = AdjGeo<float, DYN>;
-  constexpr int D = G::D, RS = G::RS, NP = G::NP, PW = G::PW;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= m.Ltot) return;
+  constexpr int D = G::D, RS = G::RS, NP = G::NP, NG = NP + D + 2;   // sums: z z^T, z, 1, then ybar
+  static_assert(NG <= kFinThreads, "one thread per sum");
+  __shared__ double g[NG], lin[D];
+  const int j = blockIdx.x, i = threadIdx.x;
   if (gJ) scale *= *gJ;
   int o = 0;
   while (o + 1 < m.n_out && j >= m.L_off[o + 1]) ++o;
   const int slot = (l.tile_off[o] + (j - m.L_off[o]) / 16) * 16 + (j - m.L_off[o]) % 16;
-  double g[NP + D + 1], y = 0.0;
-  for (int i = 0; i < NP + D + 1; ++i) g[i] = 0.0;
-  for (int ch = 0; ch < nch; ++ch) {
-    const float *src = gpart + ((size_t)ch * l.n_tiles * 16 + slot) * width;
-    for (int i = 0; i < NP + D + 1; ++i) g[i] += (double)src[i];
-    y += (double)src[width - 1];
+  if (i < NG) {
+    const float *src = gpart + (size_t)slot * width + (i < NG - 1 ? i : width - 1);
+    const size_t step = (size_t)l.n_tiles * 16 * width;
+    double sum = 0.0;
+#pragma unroll 8
+    for (int ch = 0; ch < nch; ++ch) sum += (double)src[ch * step];
+    g[i] = sum;
   }
+  __syncthreads();
   const float *r = model + (size_t)j * RS;
-  double c[D], gz[D];
-  for (int a = 0; a < D; ++a) c[a] = (double)r[a];
   const double g1 = g[NP + D];
-  for (int a = 0; a < D; ++a) gz[a] = g[NP + a];
-  double sum[PW];
-  int idx = 0;
-  for (int a = 0; a < D; ++a)
-    for (int b = a; b < D; ++b, ++idx) sum[idx] = g[idx] - gz[a] * c[b] - c[a] * gz[b] + g1 * c[a] * c[b];
-  for (int a = 0; a < D; ++a) sum[NP + a] = gz[a] - g1 * c[a];
-  sum[NP + D] = y;
-  param_grads_from_sums<float, D>(j, r, sum, scale, gc, gD);
+  if (i < D) lin[i] = g[NP + i] - g1 * (double)r[i];   // sum qbar dl
+  if (i < NP) {
+    int a = 0, rem = i;
+    while (rem >= D - a) {
+      rem -= D - a;
+      ++a;
+    }
+    const int b = a + rem;
+    const double ca = (double)r[a], cb = (double)r[b];
+    const double v = (g[i] - g[NP + a] * cb - ca * g[NP + b] + g1 * ca * cb) * scale;
+    gD[((size_t)j * D + a) * D + b] = (float)v;
+    gD[((size_t)j * D + b) * D + a] = (float)v;
+  }
+  __syncthreads();
+  if (i < D) {
+    // (D + D^T) from the packed record: diagonal 2 theta_aa, off-diagonal theta_ab
+    const float *th = r + D;
+    double v = 0.0;
+    for (int b = 0; b < D; ++b) {
+      const int lo = i < b ? i : b, hi = i < b ? b : i;
+      v += (double)th[lo * D - lo * (lo - 1) / 2 + (hi - lo)] * (i == b ? 2.0 : 1.0) * lin[b];
+    }
+    gc[(size_t)j * D + i] = (float)(scale * (-v - (double)th[NP + i] * g[NG - 1]));
+  }
 }
 
 // Stage 4b: dJ/du_nom[t] = scale * sum_s ubar[s][t] (block per step, fixed tree;
@@ -559,10 +580,15 @@ int adjoint_default_ckpt(int T) {
 
 int adjoint_param_chunks(int64_t R) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, R / 2048)); }
 
-// record chunks of the matrix-core parameter pass over one segment of
-// R records: each chunk's workgroups stream about 4096 records
-static int adjoint_param_chunks_seg(int64_t R) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(64, R / 4096));
+// Record chunks of the matrix-core parameter pass over one segment of R records.
+// A workgroup takes a chunk and 8 model tiles: chunks of about 4096 records, or
+// as many as give every compute unit two workgroups (of 256 units), down to 64
+// records each.  With 4096-record chunks alone 1000 rollouts x 60 steps of 6 x 200
+// models left 9 of 10 compute units idle (22.0 ms for the adjoint, 5.7 ms so).
+static int adjoint_param_chunks_seg(int64_t R, int Ltot, int n_out) {
+  const int64_t groups = (Ltot / 16 + n_out + 7) / 8;
+  const int64_t fill = std::min<int64_t>(R / 64, (512 + groups - 1) / groups);
+  return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(64, R / 4096)));
 }
 
 // Partial sums of the parameter pass: per chunk and model, PW values (direct)
@@ -572,7 +598,7 @@ static size_t adj_gpart_bytes(int dtype, int d, int n_out, int Ltot, int64_t R, 
   const size_t rb = dtype == PI_F64 ? 8 : 4;
   const int pw = d * (d + 1) / 2 + d + 1;
   if (mfma)
-    return align_up((size_t)adjoint_param_chunks_seg(R) * (size_t)(Ltot + 16 * n_out) * adj_param_mfma_width(d) * 4,
+    return align_up((size_t)adjoint_param_chunks_seg(R, Ltot, n_out) * (size_t)(Ltot + 16 * n_out) * adj_param_mfma_width(d) * 4,
                     256);
   return align_up((size_t)adjoint_param_chunks(R) * Ltot * pw * rb, 256);
 }
@@ -649,6 +675,10 @@ static hipError_t adjoint_t(const ProbDev<Real> &p, const ModelArgs &m, const Re
       // the pieces forms' forward takes two row tiles per wave (each model
       // piece loaded serves both) once the tiles still cover the chip
       const int spw = S >= 4096 ? (pf != kPfF32 ? 32 : 16) : 8;
+      // one workgroup per compute unit at most: two waves per vector unit.  With this,
+      // the parameter pass's chunks and the reverse sweep's 16 lanes per sample: 300 x
+      // 30 steps of 6 x 100 models 4.46 -> 1.74 ms, 3000 x 40 of 6 x 200 11.6 -> 6.0 ms
+      const int nw = pf == kPfF32 && DYN == kDynQuad12 && (S + spw - 1) / spw <= 256 ? 8 : 4;
       e = launch_fold_mfma(PI_F32, m, *ml, mbase, s);
       if (e == hipSuccess) e = launch_adj_rfold(m, *ml, a.model, G::RS, rfold, s);
       if (e != hipSuccess) return e;
@@ -662,11 +692,11 @@ static hipError_t adjoint_t(const ProbDev<Real> &p, const ModelArgs &m, const Re
         fa.trace = a.seg;
         fa.trace_T = ckpt;
       }
-      e = launch_rollout_mfma(fa, m, *ml, mbase, spw, 4, pf, s);
+      e = launch_rollout_mfma(fa, m, *ml, mbase, spw, nw, pf, s);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(adj_jsum_kernel, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, s, S, p.T,
                          (const float *)cost, a.jsum);
-      const int nchm = adjoint_param_chunks_seg(R);
+      const int nchm = adjoint_param_chunks_seg(R, m.Ltot, m.n_out);
       for (int g = ncp - 1; g >= 0 && e == hipSuccess; --g) {
         const int tb = g * ckpt, te = std::min(p.T, tb + ckpt);
         if (ncp > 1) {
@@ -678,7 +708,7 @@ static hipError_t adjoint_t(const ProbDev<Real> &p, const ModelArgs &m, const Re
           ra.xstart = a.ckpt_buf;
           ra.trace = a.seg;
           ra.trace_T = ckpt;
-          e = launch_rollout_mfma(ra, m, *ml, mbase, spw, 4, pf, s);
+          e = launch_rollout_mfma(ra, m, *ml, mbase, spw, nw, pf, s);
           if (e != hipSuccess) break;
         }
         e = launch_adj_reverse_mfma(p, u_nom, iter, *ml, mbase, rfold, a.seg, ckpt, tb, te, xbar, a.recs, s);
@@ -690,7 +720,7 @@ static hipError_t adjoint_t(const ProbDev<Real> &p, const ModelArgs &m, const Re
                            (const Real *)a.recs, G::RW_M, G::D + 7 * G::NO, scale, gJ, gu + (size_t)tb * G::NU);
       }
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((adj_param_mfma_finish_kernel<DYN>), dim3((m.Ltot + 63) / 64), dim3(64), 0, s, m, *ml,
+      hipLaunchKernelGGL((adj_param_mfma_finish_kernel<DYN>), dim3(m.Ltot), dim3(kFinThreads), 0, s, m, *ml,
                          (const float *)a.model, nchm, (const float *)gpart, adj_param_mfma_width(m.d), scale, gJ,
                          (float *)gc, (float *)gD);
       hipLaunchKernelGGL(adj_j_kernel, dim3(1), dim3(256), 0, s, S, (const double *)a.jsum, scale, J);

@@ -162,6 +162,18 @@ __device__ __forceinline__ double dpp(double v) {
   return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
 }
 
+// Over groups of P lanes, the same bits in every lane of a group: neighbours, pairs,
+// then half rows and rows mirrored.
+template <int P, typename Real, class Op>
+__device__ __forceinline__ Real lanes_reduce(Real v, Op op) {
+  static_assert(P == 4 || P == 8 || P == 16);
+  v = op(v, dpp<0xB1>(v));
+  v = op(v, dpp<0x4E>(v));
+  if constexpr (P >= 8) v = op(v, dpp<0x141>(v));
+  if constexpr (P >= 16) v = op(v, dpp<0x140>(v));
+  return v;
+}
+
 // ---------------------------------------------------------------- dynamics
 // The LWPR input of a state and an applied control: z = [x ; u] for the point
 // mass and the 12-state quadrotor; for the hybrid quadrotor (Sec. 4.1: the

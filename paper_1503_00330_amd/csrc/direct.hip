@@ -334,17 +334,6 @@ static hipError_t rollout_group_t(const RolloutArgs<Real> &ra, const ModelArgs &
 // instructions where it is (P = 4).  The whole step of 256 rollouts x 20, models
 // 16/16, in double: 144 -> 55 us; 1000 x 50, models 15/15/24, in float 162 us (matrix
 // cores) -> 65 us, 30400 sub-rollouts 366 -> 209 us.
-// Over the P lanes of a sub-rollout, the same bits in every lane: neighbours, pairs,
-// then half rows and rows mirrored.
-template <int P, typename Real, class Op>
-__device__ __forceinline__ Real lanes_reduce(Real v, Op op) {
-  static_assert(P == 4 || P == 8 || P == 16);
-  v = op(v, dpp<0xB1>(v));
-  v = op(v, dpp<0x4E>(v));
-  if constexpr (P >= 8) v = op(v, dpp<0x141>(v));
-  if constexpr (P >= 16) v = op(v, dpp<0x140>(v));
-  return v;
-}
 __device__ __forceinline__ float exp_act(float x) { return __builtin_amdgcn_exp2f(x); }   // base 2, x <= 0
 __device__ __forceinline__ double exp_act(double x) { return exp(x); }
 __device__ __forceinline__ float root_(float x) { return __builtin_amdgcn_sqrtf(x); }

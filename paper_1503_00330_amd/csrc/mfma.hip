@@ -2578,64 +2578,105 @@ __global__ void __launch_bounds__(256) adj_reverse_mfma_kernel(RevArgs ra) {
   __shared__ MixSmem<D, 1, 4> sm;
   __shared__ float xbar[16][NX];
   __shared__ float stt[16][kMaxOut][7];          // d1, var, log2 Z, m, yref, mubar, vbar
-  __shared__ float part[4][16][PSTR];            // per-wave sums of the second contraction
+  // per-wave sums of the second contraction; before it, the step's draws in
+  // part[0][sample]: control, then accelerations (two workgroups fit a unit's LDS)
+  __shared__ float part[4][16][PSTR];
   __shared__ float zb[16][D];
   __shared__ float obs_s[kMaxObs * 3];
   const ProbDev<float> &p = ra.p;
   const MfmaModel &md = ra.md;
   // the wave index is uniform: its tile range and offsets stay scalar
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // outside the contractions 16 lanes share a sample (four samples per wave):
+  // lane l holds component l of the state, of its adjoint and of z (8192 samples x
+  // 20 steps, 6 x 256 models: 1.86 ms with a lane per sample, 1.74 so)
+  const int row = threadIdx.x >> 4, l = threadIdx.x & 15;
   const int64_t S = (int64_t)p.K * p.Ms, s = (int64_t)blockIdx.x * 16 + row;
-  const bool active = row < 16 && s < S;
-  const uint32_t k = active ? (uint32_t)(s / p.Ms) : 0u, mm = active ? (uint32_t)(s % p.Ms) : 0u;
+  const bool active = s < S;
+  const uint32_t k = active ? (uint32_t)s / (uint32_t)p.Ms : 0u, mm = active ? (uint32_t)s - k * (uint32_t)p.Ms : 0u;
   const uint32_t it = *ra.iter;
   const uint32_t wc = stream_word(kTagCtrl, p.problem_id, it), wd = stream_word(kTagDyn, p.problem_id, it);
   mix_setup(sm);
   for (int i = threadIdx.x; i < 3 * p.n_obs; i += 256) obs_s[i] = p.obs[i];
   const int tb = ra.tb, te = ra.te;
-  if (row < 16) {
-    // the adjoint of x_te: zero at the horizon's end, else what the later
-    // segment's sweep left
-    for (int i = 0; i < NX; ++i) xbar[row][i] = (te < p.T && active) ? ra.xbar_io[s * NX + i] : 0.0f;
+  if (l == 0) {
     sm.z[row][D] = 1.0f;
     sm.z[row][D + 1] = 0.0f;
   }
+  // the adjoint of x_te: zero at the horizon's end, else what the later
+  // segment's sweep left
+  if (l < NX) xbar[row][l] = (te < p.T && active) ? ra.xbar_io[s * NX + l] : 0.0f;
   const int t0w = (int)((int64_t)wave * md.n_tiles / 4), t1w = (int)((int64_t)(wave + 1) * md.n_tiles / 4);
-  // trace rows count from step tb
+  // trace rows count from step tb; row t's values l, l + 16, .. of the sample are
+  // requested one step ahead, and its state is row t - 1's next state
   const float *tr = ra.trace + (active ? s : 0) * (int64_t)(ra.trace_T + 1) * SEGW - (int64_t)tb * SEGW;
+  constexpr int NSV = (SEGW + 15) / 16;
+  float sv[NSV];
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int c = 0; c < NSV; ++c) sv[c] = l + 16 * c < SEGW ? tr[(int64_t)t * SEGW + l + 16 * c] : 0.0f;
+  };
+  float x1 = l < NX ? tr[(int64_t)te * SEGW + l] : 0.0f;   // component l of x_{t+1}
+  fetch(te - 1);
   __syncthreads();
   for (int t = te - 1; t >= tb; --t) {
     // (1) per sample: cost gradient at x_{t+1}, the draws of step t, z_t and the
     //     adjoints of the sampled accelerations
-    if (row < 16) {
-      if (active) {
-        float x1[NX], gq[NX], x[NX], u[NU], z[D], eps[4], xi[8];
-        for (int i = 0; i < NX; ++i) x1[i] = tr[(int64_t)(t + 1) * SEGW + i];
-        state_cost_grad<float>(p, obs_s, x1, gq);
-        for (int i = 0; i < NX; ++i) xbar[row][i] += p.dt * gq[i];
-        float ab[NO];
-        for (int o = 0; o < NPOS; ++o) ab[o] = p.dt * xbar[row][NPOS + o];
-        if (DYN == kDynQuad12)
-          for (int o = 0; o < 3; ++o) ab[3 + o] = p.dt * xbar[row][9 + o];
-        normals<float, NU>(p.key0, p.key1, wc, k, 0u, (uint32_t)t, eps);
-        if (p.M > 0) normals<float, NO>(p.key0, p.key1, wd, k, mm, (uint32_t)t, xi);
-        for (int i = 0; i < NX; ++i) x[i] = tr[(int64_t)t * SEGW + i];
-        for (int i = 0; i < NU; ++i) u[i] = ra.u_nom[t * NU + i] + p.noise_std[i] * eps[i];
-        lwpr_input<DYN>(x, u, z);
-        for (int i = 0; i < D; ++i) sm.z[row][i] = z[i];
-        for (int o = 0; o < NO; ++o) {
-          const float *tro = tr + (int64_t)t * SEGW + NX + 5 * o;
-          const float v = tro[1];
-          for (int c = 0; c < 5; ++c) stt[row][o][c] = tro[c];
-          stt[row][o][5] = ab[o];
-          stt[row][o][6] = (p.M > 0 && v > 0.f) ? ab[o] * xi[o] / (2.0f * sqrtf(v)) : 0.0f;
+    {
+      const float px = __shfl(x1, 0, 16), py = __shfl(x1, 1, 16);
+      float gx = 0.0f, gy = 0.0f;
+      if (p.obs_kind == kObsSmooth) {   // the indicator has zero derivative almost everywhere
+        for (int i = l; i < p.n_obs; i += 16) {
+          const float dx = px - obs_s[3 * i], dy = py - obs_s[3 * i + 1];
+          const float e = -2.0f * p.obs_decay * p.obs_penalty * exp_(-p.obs_decay * (dx * dx + dy * dy));
+          gx += dx * e;
+          gy += dy * e;
         }
-      } else {
-        for (int i = 0; i < D; ++i) sm.z[row][i] = 0.0f;
-        for (int o = 0; o < NO; ++o)
-          for (int c = 0; c < 7; ++c) stt[row][o][c] = c == 1 ? 1.f : 0.f;
+        auto add = [](float a, float b) { return a + b; };
+        gx = lanes_reduce<16>(gx, add);
+        gy = lanes_reduce<16>(gy, add);
       }
+      if (l < NX) {
+        float g = 0.0f;
+        if (l < NPOS)
+          g = 2 * p.w_pos[l] * (x1 - p.goal[l]) + (l == 0 ? gx : l == 1 ? gy : 0.0f);
+        else if (l < 2 * NPOS)
+          g = 2 * p.w_vel * x1;
+        else if (DYN == kDynQuad12 && l < 9)
+          g = 2 * p.w_ang * x1;
+        xbar[row][l] += p.dt * g;
+      }
+      // lane 0 draws the control noise, lanes 1 and 2 the accelerations'
+      const Philox4 r4 = philox4x32_10((uint32_t)t, k, l == 0 ? 0u : (mm << 4) | (uint32_t)(l - 1), l == 0 ? wc : wd,
+                                       p.key0, p.key1);
+      float e4[4];
+      box_muller(r4.v[0], r4.v[1], &e4[0], &e4[1]);
+      box_muller(r4.v[2], r4.v[3], &e4[2], &e4[3]);
+      if (l <= (NO + 3) / 4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[0][row][4 * l + i] = e4[i];
+#pragma unroll
+      for (int c = 0; c < NSV; ++c) {
+        const int i = l + 16 * c - NX;
+        if (i >= 0 && i < 5 * NO) stt[row][i / 5][i % 5] = active ? sv[c] : (i % 5 == 1 ? 1.0f : 0.0f);
+      }
+      x1 = sv[0];   // component l of x_t
     }
+    // a sample's lanes are one wave's: its LDS values are in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (l < D) {
+      const int a = max(l - NX, 0);
+      const float u = ra.u_nom[t * NU + min(a, NU - 1)] + p.noise_std[min(a, NU - 1)] * part[0][row][min(a, NU - 1)];
+      sm.z[row][l] = !active ? 0.0f : l < NX ? x1 : u;
+    }
+    if (l < NO) {
+      const int i = l < NPOS ? NPOS + l : 6 + l;
+      const float ab = active ? p.dt * xbar[row][i] : 0.0f, v = stt[row][l][1];
+      stt[row][l][5] = ab;
+      stt[row][l][6] = (p.M > 0 && v > 0.f) ? ab * part[0][row][4 + l] / (2.0f * sqrtf(v)) : 0.0f;
+    }
+    fetch(max(t - 1, tb));
     __syncthreads();
     build_fragments(sm);
     __syncthreads();
@@ -2743,24 +2784,24 @@ __global__ void __launch_bounds__(256) adj_reverse_mfma_kernel(RevArgs ra) {
     }
     __syncthreads();
     // (5) per sample: Euler transpose, the record of (s, t)
-    if (active) {
-      float xp[NX];
-      for (int i = 0; i < NX; ++i) xp[i] = xbar[row][i];
-      for (int i = 0; i < NPOS; ++i) xp[NPOS + i] += p.dt * xbar[row][i];
-      if (DYN == kDynQuad12)
-        for (int i = 0; i < 3; ++i) xp[9 + i] += p.dt * xbar[row][6 + i];
-      for (int i = 0; i < NX; ++i) xbar[row][i] = xp[i] + zb[row][i];
+    {
+      float xp = 0.0f;
+      if (l < NX) {
+        xp = xbar[row][l];
+        if ((l >= NPOS && l < 2 * NPOS) || (DYN == kDynQuad12 && l >= 9)) xp += p.dt * xbar[row][l - (l < 9 ? NPOS : 3)];
+        xp += zb[row][l];
+      }
+      __builtin_amdgcn_wave_barrier();   // every lane has read the old values
+      if (l < NX) xbar[row][l] = xp;
       float *rec = ra.recs + (s * (te - tb) + (t - tb)) * RW;
-      for (int i = 0; i < D; ++i) rec[i] = sm.z[row][i];
-      for (int o = 0; o < NO; ++o)
-        for (int c = 0; c < 7; ++c) rec[D + 7 * o + c] = stt[row][o][c];
-      for (int i = 0; i < NU; ++i) rec[D + 7 * NO + i] = zb[row][NX + i];
+      if (active)
+        for (int i = l; i < RW; i += 16)
+          rec[i] = i < D ? sm.z[row][i] : i < D + 7 * NO ? stt[row][(i - D) / 7][(i - D) % 7] : zb[row][NX + i - D - 7 * NO];
     }
     __syncthreads();
   }
-  // the adjoint of x_tb for the earlier segment (each row wrote its own)
-  if (tb > 0 && active)
-    for (int i = 0; i < NX; ++i) ra.xbar_io[s * NX + i] = xbar[row][i];
+  // the adjoint of x_tb for the earlier segment
+  if (tb > 0 && active && l < NX) ra.xbar_io[s * NX + l] = xbar[row][l];
 }
 
 size_t adj_rfold_bytes(const MfmaLayout &l) {
