@@ -581,13 +581,13 @@ int adjoint_default_ckpt(int T) {
 int adjoint_param_chunks(int64_t R) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, R / 2048)); }
 
 // Record chunks of the matrix-core parameter pass over one segment of R records.
-// A workgroup takes a chunk and 8 model tiles: chunks of about 4096 records, or
-// as many as give every compute unit two workgroups (of 256 units), down to 64
+// A workgroup takes a chunk and 16 model tiles: chunks of about 4096 records, or
+// as many as give every compute unit a workgroup (of 256 units), down to 64
 // records each.  With 4096-record chunks alone 1000 rollouts x 60 steps of 6 x 200
 // models left 9 of 10 compute units idle (22.0 ms for the adjoint, 5.7 ms so).
 static int adjoint_param_chunks_seg(int64_t R, int Ltot, int n_out) {
-  const int64_t groups = (Ltot / 16 + n_out + 7) / 8;
-  const int64_t fill = std::min<int64_t>(R / 64, (512 + groups - 1) / groups);
+  const int64_t groups = (Ltot / 16 + n_out + 15) / 16;
+  const int64_t fill = std::min<int64_t>(R / 64, (256 + groups - 1) / groups);
   return (int)std::max<int64_t>(1, std::max(fill, std::min<int64_t>(64, R / 4096)));
 }
 

@@ -2303,13 +2303,16 @@ MfmaModel mfma_model_view(const MfmaLayout &l, const void *base) { return mfma_v
 //      fragments of (1) serve unchanged as the A operand (rows = models,
 //      k = records) of a second contraction against the records' features,
 //      which the fragments built for (1) already hold.
-// Every workgroup holds a record chunk and 8 model tiles (2 per wave) and
+// Every workgroup holds a record chunk and 16 model tiles (2 per wave) and
 // writes per-chunk sums G_j (NF features) and sum_r ybar_{rj}; the finish pass
-// adds the chunks in double and centres them at c_j.
-constexpr int kPrmTilesPerWave = 2;
+// adds the chunks in double and centres them at c_j.  Bound by the matrix cores
+// (88 instructions per 16 x 16 tile: 1.13 ms of their time at 163840 records and
+// 6 x 256 models): 2.34 ms with 4 waves and three barriers per record tile, 2.03 with
+// 8 waves sharing a record tile's fragments, 1.85 with those built a tile ahead.
+constexpr int kPrmTilesPerWave = 2, kPrmWaves = 8;
 
 template <int D>
-__global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const float *__restrict__ recs, int RW,
+__global__ void __launch_bounds__(kPrmWaves * 64) adj_param_mfma_kernel(MfmaModel md, const float *__restrict__ recs, int RW,
                                                               int64_t R, int nch, float *__restrict__ gpart,
                                                               int accumulate) {
   using G = Geo<D>;
@@ -2318,22 +2321,24 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
   constexpr int PWM = NFB * 16 + 1;           // per-model partial: G (padded), sum ybar
   constexpr int KQS = G::FQS / 4, GQS = G::FQS % 4;
   constexpr int KYS = G::FYS / 4, GYS = G::FYS % 4;
-  __shared__ MixSmem<D, 1, 4> sm;
-  __shared__ float st[16][kMaxOut][7];        // d1, var, log2 Z, m, yref, mubar, vbar per record and output
+  // record tile n uses sm[n % 2] and st[n % 3]
+  __shared__ MixSmem<D, 1, kPrmWaves> sm[2];
+  __shared__ float st[3][16][kMaxOut][7];     // d1, var, log2 Z, m, yref, mubar, vbar per record and output
   // the wave index is uniform: its tiles' indices and offsets stay scalar
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ch = blockIdx.y;
   const int64_t r0 = R * ch / nch, r1 = R * (ch + 1) / nch;
   const int n_out = md.n_out;
-  mix_setup(sm);
-  for (int i = threadIdx.x; i < 16; i += 256) {
-    sm.z[i][D] = 1.0f;
-    sm.z[i][D + 1] = 0.0f;
+  mix_setup(sm[0]);
+  mix_setup(sm[1]);
+  for (int i = threadIdx.x; i < 32; i += kPrmWaves * 64) {
+    sm[i >> 4].z[i & 15][D] = 1.0f;
+    sm[i >> 4].z[i & 15][D + 1] = 0.0f;
   }
   int tile[kPrmTilesPerWave], tout[kPrmTilesPerWave];
 #pragma unroll
   for (int q = 0; q < kPrmTilesPerWave; ++q) {
-    tile[q] = (blockIdx.x * 4 + wave) * kPrmTilesPerWave + q;
+    tile[q] = (blockIdx.x * kPrmWaves + wave) * kPrmTilesPerWave + q;
     int oo = 0;
     for (int i = 1; i < n_out; ++i) oo += (md.tile_off[i] <= tile[q]) ? 1 : 0;
     tout[q] = oo;
@@ -2346,7 +2351,6 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
 #pragma unroll
     for (int fb = 0; fb < NFB; ++fb) acc[q][fb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float *Af = (const float *)&sm.A[0][0][0];
   // the wave's model tiles are fixed: W of the first one is requested ahead of
   // each record tile, the second one's right after the first contraction
   const __amdgpu_buffer_rsrc_t wrs = buffer_rsrc(md.W, md.n_tiles * G::KB4 * 1024);
@@ -2359,19 +2363,19 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
   // A record tile's inputs (z and the five statistics per output of 16
   // records) pass through registers: the next tile's are requested while the
   // current one is contracted, so their memory latency is hidden.
-  constexpr int NZI = (16 * D + 255) / 256, NSI = (16 * kMaxOut * 7 + 255) / 256;
+  constexpr int NZI = (16 * D + kPrmWaves * 64 - 1) / (kPrmWaves * 64), NSI = (16 * kMaxOut * 7 + kPrmWaves * 64 - 1) / (kPrmWaves * 64);
   float zr[NZI], sr[NSI];
   auto fetch = [&](int64_t rb) {
     const int nr = (int)min((int64_t)16, r1 - rb);
 #pragma unroll
     for (int k = 0; k < NZI; ++k) {
-      const int i = threadIdx.x + 256 * k;
+      const int i = threadIdx.x + kPrmWaves * 64 * k;
       const int row = i / D, a = i - row * D;
       zr[k] = (i < 16 * D && row < nr) ? recs[(rb + row) * RW + a] : 0.0f;
     }
 #pragma unroll
     for (int k = 0; k < NSI; ++k) {
-      const int i = threadIdx.x + 256 * k;
+      const int i = threadIdx.x + kPrmWaves * 64 * k;
       const int row = i / (n_out * 7), rem = i - row * (n_out * 7);
       const int o = rem / 7, c = rem - o * 7;
       // rows past the chunk carry mubar = vbar = 0, so they add nothing
@@ -2380,30 +2384,44 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
   };
   f32x4 B[G::KB4];
   loadW(B, 0);
-  if (r0 < r1) fetch(r0);
-  for (int64_t rb = r0; rb < r1; rb += 16) {
-    __syncthreads();  // the previous records' fragments and statistics are no longer read
+  auto store = [&](int zbuf, int sbuf) {
 #pragma unroll
     for (int k = 0; k < NZI; ++k) {
-      const int i = threadIdx.x + 256 * k;
-      if (i < 16 * D) sm.z[i / D][i % D] = zr[k];
+      const int i = threadIdx.x + kPrmWaves * 64 * k;
+      if (i < 16 * D) sm[zbuf].z[i / D][i % D] = zr[k];
     }
 #pragma unroll
     for (int k = 0; k < NSI; ++k) {
-      const int i = threadIdx.x + 256 * k;
+      const int i = threadIdx.x + kPrmWaves * 64 * k;
       if (i < 16 * n_out * 7) {
         const int row = i / (n_out * 7), rem = i - row * (n_out * 7);
-        st[row][rem / 7][rem % 7] = sr[k];
+        st[sbuf][row][rem / 7][rem % 7] = sr[k];
       }
     }
-    if (rb + 16 < r1) fetch(rb + 16);
+  };
+  // One barrier per record tile n: behind it the waves store tile n + 2's inputs,
+  // request tile n + 3's, build tile n + 1's fragments and contract tile n, so
+  // building overlaps the other waves' contractions.  (Tile n's statistics are read
+  // until the next barrier, hence their third buffer.)
+  if (r0 < r1) fetch(r0);
+  store(0, 0);
+  if (r0 + 16 < r1) fetch(r0 + 16);
+  __syncthreads();
+  build_fragments(sm[0]);
+  store(1, 1);
+  if (r0 + 32 < r1) fetch(r0 + 32);
+  int cur = 0, sc = 0;
+  for (int64_t rb = r0; rb < r1; rb += 16, cur ^= 1, sc = sc == 2 ? 0 : sc + 1) {
     __syncthreads();
-    build_fragments(sm);
-    __syncthreads();
+    store(cur, sc == 0 ? 2 : sc - 1);
+    if (rb + 48 < r1) fetch(rb + 48);
+    if (rb + 16 < r1) build_fragments(sm[cur ^ 1]);
+    const float *Af = (const float *)&sm[cur].A[0][0][0];
+    const auto &sn = st[sc];
     f32x4 A[G::KB4];
 #pragma unroll
     for (int q = 0; q < G::KB4; ++q) {
-      const float4 v = sm.A[0][q][lane];
+      const float4 v = sm[cur].A[0][q][lane];
       A[q] = f32x4{v.x, v.y, v.z, v.w};
     }
     // Phi(record 4k + i)[16 fb + lane%16] for the second contraction's B
@@ -2425,8 +2443,8 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
       const int o = tout[q];
       const int row = lane & 15;
       // the forward's anchors (activation anchor m, prediction reference yref)
-      if ((lane >> 4) == GQS) A[KQS / 4][KQS % 4] = -st[row][o][3];
-      if ((lane >> 4) == GYS) A[KYS / 4][KYS % 4] = -st[row][o][4];
+      if ((lane >> 4) == GQS) A[KQS / 4][KQS % 4] = -sn[row][o][3];
+      if ((lane >> 4) == GYS) A[KYS / 4][KYS % 4] = -sn[row][o][4];
       const float s2 = buffer_f32(srs, (lane & 15) * 4, tile[q] * 64);
       __builtin_amdgcn_sched_barrier(0);
       f32x4 qa = {0.f, 0.f, 0.f, 0.f}, qb = qa, ya = qa;
@@ -2451,17 +2469,17 @@ __global__ void __launch_bounds__(256) adj_param_mfma_kernel(MfmaModel md, const
         const int rr = 4 * (lane >> 4) + i;
         // normalised weight 2^(a - log2 Z) <= 1 (the bare v_exp_f32, whose
         // results below 2^-126 flush to 0, loses nothing); e = y - mu
-        const float w = __builtin_amdgcn_exp2f((qa[i] + qb[i]) - st[rr][o][2]), e = ya[i] - st[rr][o][0];
-        const float var = st[rr][o][1], mub = st[rr][o][5], vb = st[rr][o][6];
+        const float w = __builtin_amdgcn_exp2f((qa[i] + qb[i]) - sn[rr][o][2]), e = ya[i] - sn[rr][o][0];
+        const float var = sn[rr][o][1], mub = sn[rr][o][5], vb = sn[rr][o][6];
         ysum[q] += w * (mub + 2.0f * vb * e);
         qbar[i] = -0.5f * w * (mub * e + vb * (e * e + s2 - var));
       }
       // G[model][feature] += sum_r qbar[r][model] Phi(z_r)[feature]: instance i
       // takes records 4k + i at k = lane/16
 #pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int fb = 0; fb < NFB; ++fb)
           acc[q][fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qbar[i], phi[fb][i], acc[q][fb], 0, 0, 0);
       // restore the anchor slots for the next tile (they were set for output o)
       if ((lane >> 4) == GQS) A[KQS / 4][KQS % 4] = 0.0f;
@@ -2751,9 +2769,9 @@ __global__ void __launch_bounds__(256) adj_reverse_mfma_kernel(RevArgs ra) {
         qbar[i] = -0.5f * w * (mub * e + vb * (e * e + s2 - var));
       }
 #pragma unroll
-      for (int fb = 0; fb < RG::NFBQ; ++fb)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) accq[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qbar[i], P[fb][i], accq[fb], 0, 0, 0);
+        for (int fb = 0; fb < RG::NFBQ; ++fb) accq[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qbar[i], P[fb][i], accq[fb], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) accy = __builtin_amdgcn_mfma_f32_16x16x4f32(ybar[i], P[RG::NFBQ][i], accy, 0, 0, 0);
     }
@@ -2851,12 +2869,12 @@ int adj_param_mfma_width(int d) {
 hipError_t launch_adj_param_mfma(const MfmaLayout &l, const void *base, const float *recs, int RW, int64_t R,
                                  int nch, float *gpart, bool accumulate, hipStream_t s) {
   const MfmaModel md = mfma_view(l, base);
-  const dim3 grid((unsigned)((md.n_tiles + 4 * kPrmTilesPerWave - 1) / (4 * kPrmTilesPerWave)), (unsigned)nch);
+  const dim3 grid((unsigned)((md.n_tiles + kPrmWaves * kPrmTilesPerWave - 1) / (kPrmWaves * kPrmTilesPerWave)), (unsigned)nch);
   if (l.d == 16)
-    hipLaunchKernelGGL(adj_param_mfma_kernel<16>, grid, dim3(256), 0, s, md, recs, RW, R, nch, gpart,
+    hipLaunchKernelGGL(adj_param_mfma_kernel<16>, grid, dim3(kPrmWaves * 64), 0, s, md, recs, RW, R, nch, gpart,
                        (int)accumulate);
   else if (l.d == 6)
-    hipLaunchKernelGGL(adj_param_mfma_kernel<6>, grid, dim3(256), 0, s, md, recs, RW, R, nch, gpart,
+    hipLaunchKernelGGL(adj_param_mfma_kernel<6>, grid, dim3(kPrmWaves * 64), 0, s, md, recs, RW, R, nch, gpart,
                        (int)accumulate);
   else
     return hipErrorInvalidValue;
