@@ -213,7 +213,8 @@ pi_status pi_rollout_describe(const pi_problem *p, const pi_lwpr *m, int32_t *ou
 /* Eq. (1): for N inputs Z (dev [N][d]) writes the mixture mean and variance
  * of every output: mean, var dev [N][n_out] in the model's dtype.
  * `variant` selects the kernel (PI_VARIANT_*); PI_VARIANT_AUTO runs d = 16
- * float32 models with the three-piece bf16 products (see above).             */
+ * float32 models with the three-piece bf16 products (see above), and few
+ * inputs of models with d = 4 or 6 given unfolded without a fold.            */
 pi_status lwpr_predict(const pi_lwpr *m, const void *Z, int64_t N, void *mean, void *var,
                        int32_t variant, void *ws, size_t ws_bytes, void *stream);
 

@@ -301,6 +301,20 @@ TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles) {
   return best;
 }
 
+// Whether predictions left to the library skip the fold (predict_raw_kernel): models
+// of the small dynamics, in float up to two waves per vector unit of 256 compute
+// units and 512 models per output, in double while that beats a lane per input
+// walking all models.  Whole call without and with the fold, 16/16 models: 33 inputs
+// 12.3 and 17.3 us, 3000 19 and 15; 100/100: 1000 14.8 (double 15.8) and 14.8 (99);
+// 300/300: 33 12.3 and 17.8, 300 17.8 (double 17.8) and 17.7 (278), 3000 88 and 18 (276).
+bool predict_raw(const pi_lwpr *m, int variant, int64_t N) {
+  const int L = max_models(m->n_out, m->L_off);
+  const bool f64 = m->dtype == PI_F64;
+  const int64_t lim = f64 ? std::max<int64_t>(2048, 100 * (int64_t)m->L_off[m->n_out]) : 2048;
+  return variant == PI_VARIANT_AUTO && !m->folded && (m->d == 4 || m->d == 6) && (f64 || L <= 512) &&
+         N <= lim && N * m->n_out * ((L + 63) / 64) <= lim;
+}
+
 // Whether a float32 problem that leaves the whole launch to the library (contraction,
 // tile, waves, pairing) runs on the small-model kernel instead of the matrix cores,
 // which pay a workgroup's barriers and an almost empty tile per step there.  Its
@@ -837,6 +851,7 @@ pi_status lwpr_predict(const pi_lwpr *m, const void *Z, int64_t N, void *mean, v
   if (N == 0) return ok();
   hipStream_t s = (hipStream_t)stream;
   const ModelArgs a = model_args(m);
+  if (predict_raw(m, variant, N)) return launched(launch_predict_raw(m->dtype, a, Z, N, mean, var, s), "lwpr_predict");
   const void *base = nullptr;
   hipError_t e = folded_base(m, use_mfma, ws, s, &base);
   if (e == hipSuccess) {

@@ -154,6 +154,8 @@ hipError_t launch_fold_direct(int dtype, const ModelArgs &m, void *rec, hipStrea
 hipError_t launch_fold_mfma(int dtype, const ModelArgs &m, const MfmaLayout &l, void *base,
                             hipStream_t s);
 
+hipError_t launch_predict_raw(int dtype, const ModelArgs &m, const void *Z, int64_t N, void *mean, void *var,
+                              hipStream_t s);
 hipError_t launch_predict_direct(int dtype, const ModelArgs &m, const void *rec, const void *Z,
                                  int64_t N, void *mean, void *var, hipStream_t s);
 hipError_t launch_predict_mfma(const ModelArgs &m, const MfmaLayout &l, const void *base, const void *Z, int64_t N,
