@@ -1150,12 +1150,94 @@ __global__ void __launch_bounds__(256) plant_apply_kernel(ProbDev<Real> p, int C
   if (threadIdx.x < NX) x0[threadIdx.x] = xnew[threadIdx.x];
 }
 
+// Both kernels in one block, a wave per (output, chunk), where there are at most
+// kPlantWaves of these: the same sums in the same order, one launch less (a control
+// step of 256 x 20 point-mass rollouts in double: @PLANT@).
+constexpr int kPlantWaves = 8;
+template <typename Real, int DYN>
+__global__ void __launch_bounds__(kPlantWaves * 64) plant_small_kernel(ProbDev<Real> p, ModelArgs m, int C,
+                                                                      const Real *__restrict__ rec,
+                                                                      Real *__restrict__ x0,
+                                                                      Real *__restrict__ u_nom,
+                                                                      const uint32_t *__restrict__ iter) {
+  using DD = DynDims<DYN>;
+  constexpr int D = DD::D, NX = DD::NX, NU = DD::NU, NO = DD::NO;
+  constexpr int RS = rec_stride<Real, D>();
+  __shared__ MixStat<Real> part[kPlantWaves];
+  __shared__ Real acc_s[NO], xnew[NX];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = p.T * NU;
+  Real x[NX], u[NU];
+#pragma unroll
+  for (int a = 0; a < NX; ++a) x[a] = x0[a];
+#pragma unroll
+  for (int a = 0; a < NU; ++a) u[a] = u_nom[a];
+  if (wave < NO * C) {
+    const int o = wave / C, c = wave - o * C;
+    Real z[D];
+    lwpr_input<DYN>(x, u, z);
+    MixStat<Real> st = mix_empty<Real>();
+    const int j = m.L_off[o] + c * kShiftThreads + lane;
+    if (j < m.L_off[o + 1]) {
+      Real q, y;
+      eval_record<Real, D>(rec + (size_t)j * RS, z, q, y);
+      mix_add<false>(st, (Real)-0.5 * q, y, rec[(size_t)j * RS + RS - 1]);
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) st = mix_merge<false>(st, shfl_stat(st, w));
+    if (lane == 0) part[wave] = st;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < NO) {
+    const int o = threadIdx.x;
+    Real xi[8], xo = 0, mu, v;
+    normals<Real, NO>(p.key0, p.key1, stream_word(kTagPlant, p.problem_id, *iter), 0u, 0u, 0u, xi);
+#pragma unroll
+    for (int i = 0; i < NO; ++i) xo = i == o ? xi[i] : xo;
+    MixStat<Real> st = part[o * C];
+    for (int c = 1; c < C; ++c) st = mix_merge<false>(st, part[o * C + c]);
+    mix_finish(st, &mu, &v);
+    acc_s[o] = mu + sqrt_(v) * xo;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    Real acc[NO], xn[NX];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) acc[o] = acc_s[o];
+    euler_step<Real>(DYN, p.dt, x, acc, u, xn);
+#pragma unroll
+    for (int a = 0; a < NX; ++a) xnew[a] = xn[a];
+  }
+  // the plan's shift, as in plant_apply_kernel
+  for (int base = 0; base < n; base += blockDim.x) {
+    const int i = base + threadIdx.x;
+    Real v = 0;
+    if (i < n) v = (i + NU < n) ? u_nom[i + NU] : u_nom[i];
+    __syncthreads();
+    if (i < n) u_nom[i] = v;
+    __syncthreads();
+  }
+  if (threadIdx.x < NX) x0[threadIdx.x] = xnew[threadIdx.x];
+}
+
 template <typename Real>
 static hipError_t rh_shift_t(const ProbDev<Real> &p, const ModelArgs &m, const void *rec, void *part,
                              void *x0, void *u_nom, const uint32_t *iter, hipStream_t s) {
   int Lmax = 1;
   for (int o = 0; o < m.n_out; ++o) Lmax = max(Lmax, m.L_off[o + 1] - m.L_off[o]);
   const int C = (Lmax + kShiftThreads - 1) / kShiftThreads;
+  if (C * m.n_out <= kPlantWaves) {
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(kPlantWaves * 64), 0, s, p, m, C, (const Real *)rec, (Real *)x0,
+                         (Real *)u_nom, iter);
+    };
+    if (p.dyn == kDynPointMass2D)
+      go(plant_small_kernel<Real, kDynPointMass2D>);
+    else if (p.dyn == kDynQuadHybrid)
+      go(plant_small_kernel<Real, kDynQuadHybrid>);
+    else
+      go(plant_small_kernel<Real, kDynQuad12>);
+    return hipGetLastError();
+  }
   const dim3 grid(C, m.n_out);
   if (p.dyn == kDynPointMass2D) {
     hipLaunchKernelGGL((plant_partial_kernel<Real, kDynPointMass2D>), grid, dim3(kShiftThreads), 0, s, m,
