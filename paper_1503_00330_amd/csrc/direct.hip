@@ -1064,8 +1064,8 @@ hipError_t launch_update(int dtype, const void *pargs, const void *cost, const u
 // The plant step executes u_nom[0] under the PLANT stream.  Kernel 1: block
 // (o, c) evaluates 64 local models of output o at z = [x0 ; u_nom[0]], one per
 // lane, and merges them into one partial statistic (fixed tree order).
-// Kernel 2 (one block): merges the partials of every output in order, samples
-// the accelerations, steps Euler and shifts the plan left by one step (last
+// Kernel 2 (one block, a lane per output): merges the partials of every output in order,
+// samples the accelerations, steps Euler and shifts the plan left by one step (last
 // control repeated).  The iteration word is read, not advanced.
 constexpr int kShiftThreads = 64;
 
@@ -1109,29 +1109,33 @@ __global__ void __launch_bounds__(kShiftThreads) plant_partial_kernel(ModelArgs 
   if (threadIdx.x == 0) part[o * C + c] = red[0];
 }
 
+// The rest of the shift by one block, behind a barrier after `part`: a lane per output
+// merges its partials in order and samples its acceleration, one lane steps Euler, all
+// shift the plan.  acc, xnew: LDS.
 template <typename Real, int DYN>
-__global__ void __launch_bounds__(256) plant_apply_kernel(ProbDev<Real> p, int C,
-                                                          const MixStat<Real> *__restrict__ part,
-                                                          Real *__restrict__ x0, Real *__restrict__ u_nom,
-                                                          const uint32_t *__restrict__ iter) {
+__device__ __forceinline__ void plant_finish(const ProbDev<Real> &p, int C, const MixStat<Real> *part,
+                                             Real *__restrict__ x0, Real *__restrict__ u_nom,
+                                             const uint32_t *__restrict__ iter, Real *acc, Real *xnew) {
   using DD = DynDims<DYN>;
   constexpr int NX = DD::NX, NU = DD::NU, NO = DD::NO;
-  __shared__ Real xnew[kMaxX];
+  if ((int)threadIdx.x < NO) {
+    const int o = threadIdx.x;
+    Real xi[8], xo = 0, mu, v;
+    normals<Real, NO>(p.key0, p.key1, stream_word(kTagPlant, p.problem_id, *iter), 0u, 0u, 0u, xi);
+#pragma unroll
+    for (int i = 0; i < NO; ++i) xo = i == o ? xi[i] : xo;
+    MixStat<Real> st = part[o * C];
+    for (int c = 1; c < C; ++c) st = mix_merge<false>(st, part[o * C + c]);
+    mix_finish(st, &mu, &v);
+    acc[o] = mu + sqrt_(v) * xo;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const uint32_t it = *iter;
-    Real xi[8], acc[NO], xs[NX], xn[NX];
-    normals<Real, NO>(p.key0, p.key1, stream_word(kTagPlant, p.problem_id, it), 0u, 0u, 0u, xi);
-    for (int o = 0; o < NO; ++o) {
-      MixStat<Real> st = part[o * C];
-      for (int c = 1; c < C; ++c) st = mix_merge<false>(st, part[o * C + c]);
-      Real mu, v;
-      mix_finish(st, &mu, &v);
-      acc[o] = mu + sqrt_(v) * xi[o];
-    }
-    Real u0[NU];
-    for (int a = 0; a < NX; ++a) xs[a] = x0[a];
-    for (int a = 0; a < NU; ++a) u0[a] = u_nom[a];
-    euler_step<Real>(DYN, p.dt, xs, acc, u0, xn);
+    Real x[NX], u[NU], ac[NO], xn[NX];
+    for (int a = 0; a < NX; ++a) x[a] = x0[a];
+    for (int a = 0; a < NU; ++a) u[a] = u_nom[a];
+    for (int o = 0; o < NO; ++o) ac[o] = acc[o];
+    euler_step<Real>(DYN, p.dt, x, ac, u, xn);
     for (int a = 0; a < NX; ++a) xnew[a] = xn[a];
   }
   __syncthreads();
@@ -1150,9 +1154,18 @@ __global__ void __launch_bounds__(256) plant_apply_kernel(ProbDev<Real> p, int C
   if (threadIdx.x < NX) x0[threadIdx.x] = xnew[threadIdx.x];
 }
 
+template <typename Real, int DYN>
+__global__ void __launch_bounds__(1024) plant_apply_kernel(ProbDev<Real> p, int C,
+                                                           const MixStat<Real> *__restrict__ part,
+                                                           Real *__restrict__ x0, Real *__restrict__ u_nom,
+                                                           const uint32_t *__restrict__ iter) {
+  __shared__ Real acc[kMaxOut], xnew[kMaxX];
+  plant_finish<Real, DYN>(p, C, part, x0, u_nom, iter, acc, xnew);
+}
+
 // Both kernels in one block, a wave per (output, chunk), where there are at most
-// kPlantWaves of these: the same sums in the same order, one launch less (a control
-// step of 256 x 20 point-mass rollouts in double: @PLANT@).
+// kPlantWaves of these: the same sums in the same order, one launch less (control
+// step of 256 x 20 point-mass rollouts in double 54.3 -> 52.5 us).
 constexpr int kPlantWaves = 8;
 template <typename Real, int DYN>
 __global__ void __launch_bounds__(kPlantWaves * 64) plant_small_kernel(ProbDev<Real> p, ModelArgs m, int C,
@@ -1164,16 +1177,15 @@ __global__ void __launch_bounds__(kPlantWaves * 64) plant_small_kernel(ProbDev<R
   constexpr int D = DD::D, NX = DD::NX, NU = DD::NU, NO = DD::NO;
   constexpr int RS = rec_stride<Real, D>();
   __shared__ MixStat<Real> part[kPlantWaves];
-  __shared__ Real acc_s[NO], xnew[NX];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = p.T * NU;
-  Real x[NX], u[NU];
-#pragma unroll
-  for (int a = 0; a < NX; ++a) x[a] = x0[a];
-#pragma unroll
-  for (int a = 0; a < NU; ++a) u[a] = u_nom[a];
+  __shared__ Real acc[kMaxOut], xnew[kMaxX];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (wave < NO * C) {
     const int o = wave / C, c = wave - o * C;
-    Real z[D];
+    Real z[D], x[NX], u[NU];
+#pragma unroll
+    for (int a = 0; a < NX; ++a) x[a] = x0[a];
+#pragma unroll
+    for (int a = 0; a < NU; ++a) u[a] = u_nom[a];
     lwpr_input<DYN>(x, u, z);
     MixStat<Real> st = mix_empty<Real>();
     const int j = m.L_off[o] + c * kShiftThreads + lane;
@@ -1187,36 +1199,7 @@ __global__ void __launch_bounds__(kPlantWaves * 64) plant_small_kernel(ProbDev<R
     if (lane == 0) part[wave] = st;
   }
   __syncthreads();
-  if ((int)threadIdx.x < NO) {
-    const int o = threadIdx.x;
-    Real xi[8], xo = 0, mu, v;
-    normals<Real, NO>(p.key0, p.key1, stream_word(kTagPlant, p.problem_id, *iter), 0u, 0u, 0u, xi);
-#pragma unroll
-    for (int i = 0; i < NO; ++i) xo = i == o ? xi[i] : xo;
-    MixStat<Real> st = part[o * C];
-    for (int c = 1; c < C; ++c) st = mix_merge<false>(st, part[o * C + c]);
-    mix_finish(st, &mu, &v);
-    acc_s[o] = mu + sqrt_(v) * xo;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    Real acc[NO], xn[NX];
-#pragma unroll
-    for (int o = 0; o < NO; ++o) acc[o] = acc_s[o];
-    euler_step<Real>(DYN, p.dt, x, acc, u, xn);
-#pragma unroll
-    for (int a = 0; a < NX; ++a) xnew[a] = xn[a];
-  }
-  // the plan's shift, as in plant_apply_kernel
-  for (int base = 0; base < n; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    Real v = 0;
-    if (i < n) v = (i + NU < n) ? u_nom[i + NU] : u_nom[i];
-    __syncthreads();
-    if (i < n) u_nom[i] = v;
-    __syncthreads();
-  }
-  if (threadIdx.x < NX) x0[threadIdx.x] = xnew[threadIdx.x];
+  plant_finish<Real, DYN>(p, C, part, x0, u_nom, iter, acc, xnew);
 }
 
 template <typename Real>
@@ -1239,20 +1222,21 @@ static hipError_t rh_shift_t(const ProbDev<Real> &p, const ModelArgs &m, const v
     return hipGetLastError();
   }
   const dim3 grid(C, m.n_out);
+  const int apply = p.T * p.n_u > 256 ? 1024 : 256;   // the plan's shift in one pass, mostly
   if (p.dyn == kDynPointMass2D) {
     hipLaunchKernelGGL((plant_partial_kernel<Real, kDynPointMass2D>), grid, dim3(kShiftThreads), 0, s, m,
                        (const Real *)rec, (const Real *)x0, (const Real *)u_nom, (MixStat<Real> *)part);
-    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynPointMass2D>), dim3(1), dim3(256), 0, s, p, C,
+    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynPointMass2D>), dim3(1), dim3(apply), 0, s, p, C,
                        (const MixStat<Real> *)part, (Real *)x0, (Real *)u_nom, iter);
   } else if (p.dyn == kDynQuadHybrid) {
     hipLaunchKernelGGL((plant_partial_kernel<Real, kDynQuadHybrid>), grid, dim3(kShiftThreads), 0, s, m,
                        (const Real *)rec, (const Real *)x0, (const Real *)u_nom, (MixStat<Real> *)part);
-    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynQuadHybrid>), dim3(1), dim3(256), 0, s, p, C,
+    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynQuadHybrid>), dim3(1), dim3(apply), 0, s, p, C,
                        (const MixStat<Real> *)part, (Real *)x0, (Real *)u_nom, iter);
   } else {
     hipLaunchKernelGGL((plant_partial_kernel<Real, kDynQuad12>), grid, dim3(kShiftThreads), 0, s, m,
                        (const Real *)rec, (const Real *)x0, (const Real *)u_nom, (MixStat<Real> *)part);
-    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynQuad12>), dim3(1), dim3(256), 0, s, p, C,
+    hipLaunchKernelGGL((plant_apply_kernel<Real, kDynQuad12>), dim3(1), dim3(apply), 0, s, p, C,
                        (const MixStat<Real> *)part, (Real *)x0, (Real *)u_nom, iter);
   }
   return hipGetLastError();
