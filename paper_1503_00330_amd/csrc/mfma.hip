@@ -87,7 +87,9 @@ __device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, int lane_o
 // the value exactly (for values whose pieces stay above the float32 normal
 // range).  Products of two such values, summed over the six piece pairs whose
 // weight is at least 2^-24 (hi hi, hi mid, mid hi, hi lo, mid mid, lo hi),
-// reproduce the float32 product to within float32 rounding.
+// reproduce the float32 product to within float32 rounding.  A NaN keeps a NaN
+// leading piece (the rounding below would carry a mantissa of ones into the
+// sign and leave a zero).
 __host__ __device__ __forceinline__ uint16_t bf16_rn(float x, float *back) {
   uint32_t u = __builtin_bit_cast(uint32_t, x);
   u += 0x7FFFu + ((u >> 16) & 1u);
@@ -97,7 +99,8 @@ __host__ __device__ __forceinline__ uint16_t bf16_rn(float x, float *back) {
 }
 __host__ __device__ __forceinline__ void bf16_split3(float v, uint16_t *pc) {
   float h, m, l;
-  pc[0] = bf16_rn(v, &h);
+  const uint16_t hi = bf16_rn(v, &h);
+  pc[0] = v == v ? hi : (uint16_t)0x7FC0;
   const float r1 = v - h;
   pc[1] = bf16_rn(r1, &m);
   pc[2] = bf16_rn(r1 - m, &l);

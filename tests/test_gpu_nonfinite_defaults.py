@@ -1,0 +1,79 @@
+"""Non-finite inputs in the forms that the library picks by itself: the same
+entries are non-finite as in the oracle, whatever the bits of a NaN."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import DYN_QUAD12
+
+torch = pytest.importorskip("torch")
+pi = pytest.importorskip("paper_1503_00330_amd")
+
+pytestmark = pytest.mark.gpu
+F32, F64 = np.float32, np.float64
+# the default NaN, and those whose rounding to 16 bits would carry into the sign
+NAN_BITS = [0x7FC00000, 0x7FFFFFFF, 0xFFFFFFFF]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    yield
+    torch.cuda.synchronize()
+
+
+def _nan(bits):
+    return np.array([bits], np.uint32).view(F32)[0]
+
+
+def _same_nonfinite(got, ref, tol):
+    got, ref = np.asarray(got, F64), np.asarray(ref, F64)
+    assert np.array_equal(~np.isfinite(got), ~np.isfinite(ref))
+    fin = np.isfinite(ref)
+    if fin.any():
+        assert np.abs(got[fin] - ref[fin]).max() <= tol * np.abs(ref[fin]).max()
+
+
+# 16- and 32-row tiles, and the 128-row tiles with a remainder
+@pytest.mark.parametrize("N", [40, 5000, 32768 + 33])
+@pytest.mark.parametrize("bits", NAN_BITS)
+def test_nan_inputs_of_predictions(bits, N):
+    _, model = synth.tiny_problem(81, dyn=DYN_QUAD12, L=[20, 3, 17, 16, 1, 9], R=3, dtype=F32)
+    Z = np.random.default_rng(N).uniform(-1, 1, (N, 16)).astype(F32)
+    bad = [3, 21, N - 1]
+    Z[bad, [5, 0, 15]] = _nan(bits)
+    Z[30, 2] = np.inf
+    rows = np.r_[0:40, N - 8:N]
+    mean, var = pi.lwpr_predict(pi.DeviceModel(model), torch.from_numpy(Z).cuda())
+    om, ov = oracle.lwpr_predict(model, Z[rows])
+    assert np.isnan(om[bad[:2]]).all()
+    _same_nonfinite(mean.cpu().numpy()[rows], om, 1e-5)
+    _same_nonfinite(var.cpu().numpy()[rows], ov, 1e-5)
+
+
+# a NaN that reaches the costs through the model only: a control that is a model
+# input, or a model's parameter.  3 x 700 rollouts: the bf16 pieces by default
+@pytest.mark.parametrize("where", ["u_nom", "centre", "metric", "beta"])
+@pytest.mark.parametrize("bits", NAN_BITS)
+@pytest.mark.parametrize("kw", [{}, dict(variant=pi.PI_VARIANT_MFMA_BF16X3, tile_samples=128),
+                                dict(variant=pi.PI_VARIANT_MFMA_F16X2, tile_samples=128)])
+def test_nan_reaches_the_costs(bits, where, kw):
+    prob, model = synth.tiny_problem(31, dyn=DYN_QUAD12, L=[17, 12, 20, 9, 16, 11], R=3, K=700, T=5, M=3, dtype=F32,
+                                     n_obs=4)
+    j = int(model.L_off[2]) + 3
+    if where == "u_nom":
+        prob.u_nom[2, 1] = _nan(bits)
+    elif where == "centre":
+        model.centre[j, 5] = _nan(bits)
+    elif where == "metric":
+        model.metric[j, 4, 4] = _nan(bits)
+    else:
+        model.beta[j, 1] = _nan(bits)
+    dp, dm = pi.DeviceProblem(prob, **kw), pi.DeviceModel(model)
+    if not kw:
+        assert pi.rollout_describe(dp, dm)["variant"] == "mfma-bf16x3"
+    ref = oracle.rollout_cost(prob, model)
+    assert not np.isfinite(ref).all()
+    _same_nonfinite(pi.rollout_cost(dp, dm).cpu().numpy(), ref, 1e-4)
