@@ -233,13 +233,16 @@ __device__ __forceinline__ void euler_step(int dyn, Real dt, const Real *x, cons
 // state does not pick up half an ulp per step over the horizon -- without it,
 // the largest part of a float32 rollout's error.  (Where the increment exceeds
 // the state the captured error is itself rounded, below an ulp of the sum.)
-template <typename Real>
-__device__ __forceinline__ void euler_step_comp(int dyn, Real dt, const Real *x, const Real *acc, const Real *u,
-                                                Real *xn, Real *lo) {
-  auto add = [&](int a, Real rate) {
-    const Real y = dt * rate + lo[a];
+// An infinite state has no error to carry (inf - inf): lo is held within the
+// largest ulp there is, which no rounding error passes and which leaves an
+// infinity what it is.
+constexpr float kLargestUlp = 2.028241e31f;   // 2^104
+__device__ __forceinline__ void euler_step_comp(int dyn, float dt, const float *x, const float *acc, const float *u,
+                                                float *xn, float *lo) {
+  auto add = [&](int a, float rate) {
+    const float y = dt * rate + lo[a];
     xn[a] = x[a] + y;
-    lo[a] = y - (xn[a] - x[a]);
+    lo[a] = __builtin_amdgcn_fmed3f(y - (xn[a] - x[a]), -kLargestUlp, kLargestUlp);   // of a NaN: -kLargestUlp
   };
   if (dyn == kDynPointMass2D) {
 #pragma unroll
@@ -252,7 +255,7 @@ __device__ __forceinline__ void euler_step_comp(int dyn, Real dt, const Real *x,
     for (int a = 0; a < 3; ++a) {
       add(a, x[3 + a]);
       add(3 + a, acc[a]);
-      add(6 + a, (Real)kRateGain * (u[a] - x[6 + a]));
+      add(6 + a, (float)kRateGain * (u[a] - x[6 + a]));
     }
   } else {
 #pragma unroll

@@ -527,7 +527,7 @@ __global__ void __launch_bounds__(64, NJ > 2 ? 2 : 1) rollout_wave_kernel(Rollou
       }
       Real xn[NX];
       if constexpr (sizeof(Real) == 4)
-        euler_step_comp<Real>(DYN, p.dt, x, acc, u, xn, lo);
+        euler_step_comp(DYN, p.dt, x, acc, u, xn, lo);
       else
         euler_step<Real>(DYN, p.dt, x, acc, u, xn);
 #pragma unroll

@@ -2006,7 +2006,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
         lo[a] = rs.xlo[row][a];
       }
       applied(u);
-      euler_step_comp<float>(DYN, p.dt, x, acc, u, xn, lo);
+      euler_step_comp(DYN, p.dt, x, acc, u, xn, lo);
 #pragma unroll
       for (int a = 0; a < NX; ++a) {
         rs.xs[row][a] = xn[a];

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import synth
-from synth import DYN_QUAD12
+from synth import DYN_QUAD12, DYN_QUAD_HYBRID, OBS_SMOOTH
 
 torch = pytest.importorskip("torch")
 pi = pytest.importorskip("paper_1503_00330_amd")
@@ -77,3 +77,20 @@ def test_nan_reaches_the_costs(bits, where, kw):
     ref = oracle.rollout_cost(prob, model)
     assert not np.isfinite(ref).all()
     _same_nonfinite(pi.rollout_cost(dp, dm).cpu().numpy(), ref, 1e-4)
+
+
+# states of the hybrid model that its local models do not see stay infinite, and
+# their costs with them: small-model kernel, matrix cores (16 and 32 rows, pairs),
+# sub-rollouts, and every direct form in float64
+@pytest.mark.parametrize("at,value", [(0, np.inf), (1, -np.inf), (5, np.inf)])
+@pytest.mark.parametrize("M", [0, 2])
+@pytest.mark.parametrize("dtype,L,kw", [(F32, 15, {}), (F32, 100, {}), (F32, 15, dict(tile_samples=32)),
+                                        (F32, 100, dict(tile_split=2)), (F64, 15, {}), (F64, 100, {})])
+def test_infinite_states_keep_their_costs(dtype, L, kw, M, at, value):
+    prob, model = synth.tiny_problem(5, dyn=DYN_QUAD_HYBRID, L=[L, L, 3], R=2, K=40, T=23, M=M, dtype=dtype, n_obs=3,
+                                     obs_kind=OBS_SMOOTH)
+    prob.x0[at] = value
+    ref = oracle.rollout_cost(prob, model)
+    got = pi.rollout_cost(pi.DeviceProblem(prob, **kw), pi.DeviceModel(model)).cpu().numpy()
+    assert np.isposinf(ref[:, 1:]).all()
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref))
