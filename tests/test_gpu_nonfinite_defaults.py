@@ -94,3 +94,19 @@ def test_infinite_states_keep_their_costs(dtype, L, kw, M, at, value):
     got = pi.rollout_cost(pi.DeviceProblem(prob, **kw), pi.DeviceModel(model)).cpu().numpy()
     assert np.isposinf(ref[:, 1:]).all()
     assert np.array_equal(np.isposinf(got), np.isposinf(ref))
+
+
+# the last local model of an output predicts infinity with a weight above 0: the mean is
+# infinite, the accelerated velocity with it, and every later cost.  Models per
+# output that do not fill the lanes of the small-model kernel, 16 and 4 lanes per rollout
+@pytest.mark.parametrize("K", [40, 25000])
+@pytest.mark.parametrize("L", [[3, 15, 5], [17, 9, 30], [38, 1, 35]])
+@pytest.mark.parametrize("out", [0, 1, 2])
+def test_infinite_prediction_of_the_last_model(out, L, K):
+    prob, model = synth.tiny_problem(7, dyn=DYN_QUAD_HYBRID, L=L, R=2, K=K, T=3, M=0, dtype=F32, n_obs=2,
+                                     obs_kind=OBS_SMOOTH)
+    model.beta[int(model.L_off[out + 1]) - 1, 0] = np.inf
+    dp, dm = pi.DeviceProblem(prob), pi.DeviceModel(model)
+    assert pi.rollout_describe(dp, dm)["variant"] == "direct"
+    got = pi.rollout_cost(dp, dm).cpu().numpy()
+    assert np.isposinf(got).all()
