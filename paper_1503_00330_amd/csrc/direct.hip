@@ -58,7 +58,8 @@ __global__ void __launch_bounds__(256) fold_direct_kernel(ModelArgs m, Real *__r
       double pr = (double)rp[r] * rb;
 #pragma unroll
       for (int k = 8; k >= 1; k >>= 1) pr += __shfl_xor(pr, k);
-      rb += ((double)rbeta[r] - pr) * (double)ru[r];
+      // lanes without a coordinate stay 0: an infinite coefficient times 0 is not
+      rb += on ? ((double)rbeta[r] - pr) * (double)ru[r] : 0.0;
     }
     if (on) bv[col][a] = (Real)rb;
   }

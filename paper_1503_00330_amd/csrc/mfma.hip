@@ -205,7 +205,8 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
   for (int r = kMaxR - 1; r >= 0; --r) {
     if (r >= R) continue;
     const double pr = fold_reduce((double)rp[r] * rb, add);
-    rb += ((double)rbeta[r] - pr) * (double)ru[r];
+    // lanes without a coordinate stay 0: an infinite coefficient times 0 is not
+    rb += on ? ((double)rbeta[r] - pr) * (double)ru[r] : 0.0;
   }
   const double y0 = (double)beta0 - fold_reduce(rb * ca, add);
   // padded slots: activation kPadAct, everything else 0

@@ -110,3 +110,21 @@ def test_infinite_prediction_of_the_last_model(out, L, K):
     assert pi.rollout_describe(dp, dm)["variant"] == "direct"
     got = pi.rollout_cost(dp, dm).cpu().numpy()
     assert np.isposinf(got).all()
+
+
+# an infinite regression coefficient in inputs of fewer than 16 coordinates: one local
+# model per output, directions, centre and input signed so that every term of
+# y = beta_0 + sum_r beta_r u_r . r_r of output 0 is +inf and none is inf - inf
+@pytest.mark.parametrize("variant", [pi.PI_VARIANT_DIRECT, pi.PI_VARIANT_MFMA])
+@pytest.mark.parametrize("d,n_out", [(4, 3), (6, 2)])
+def test_infinite_coefficient_folds_to_infinity(d, n_out, variant):
+    rng = np.random.Generator(np.random.PCG64(3))
+    model = synth.make_lwpr(rng, d, [1] * n_out, 2).astype(F32)
+    model.proj_u = np.abs(model.proj_u)
+    model.proj_p = -np.abs(rng.uniform(0.1, 0.5, model.proj_u.shape)).astype(F32)
+    model.centre = -np.abs(model.centre) - F32(0.1)
+    model.beta[0, 2] = np.inf
+    Z = rng.uniform(0.1, 0.5, (5, d)).astype(F32)
+    mean, _ = pi.lwpr_predict(pi.DeviceModel(model), torch.from_numpy(Z).cuda(), variant=variant)
+    mean = mean.cpu().numpy()
+    assert np.isposinf(mean[:, 0]).all() and np.isfinite(mean[:, 1:]).all()
