@@ -87,23 +87,17 @@ __device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, int lane_o
 // the value exactly (for values whose pieces stay above the float32 normal
 // range).  Products of two such values, summed over the six piece pairs whose
 // weight is at least 2^-24 (hi hi, hi mid, mid hi, hi lo, mid mid, lo hi),
-// reproduce the float32 product to within float32 rounding.  A NaN keeps a NaN
-// leading piece (the rounding below would carry a mantissa of ones into the
-// sign and leave a zero).
-__host__ __device__ __forceinline__ uint16_t bf16_rn(float x, float *back) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  const uint32_t h = u & 0xFFFF0000u;
-  *back = __builtin_bit_cast(float, h);
-  return (uint16_t)(h >> 16);
-}
-__host__ __device__ __forceinline__ void bf16_split3(float v, uint16_t *pc) {
-  float h, m, l;
-  const uint16_t hi = bf16_rn(v, &h);
-  pc[0] = v == v ? hi : (uint16_t)0x7FC0;
-  const float r1 = v - h;
-  pc[1] = bf16_rn(r1, &m);
-  pc[2] = bf16_rn(r1 - m, &l);
+// reproduce the float32 product to within float32 rounding.  The conversion
+// instruction keeps a NaN a NaN (adding half a unit to the bits would carry a
+// mantissa of ones into the sign and leave a zero).
+__device__ __forceinline__ void bf16_split3(float v, uint16_t *pc) {
+  const __bf16 h = (__bf16)v;
+  const float r1 = v - (float)h;
+  const __bf16 m = (__bf16)r1;
+  const __bf16 l = (__bf16)(r1 - (float)m);
+  pc[0] = __builtin_bit_cast(uint16_t, h);
+  pc[1] = __builtin_bit_cast(uint16_t, m);
+  pc[2] = __builtin_bit_cast(uint16_t, l);
 }
 
 // Two fp16 pieces hi + lo of a float32 value of magnitude below 2^15, each
