@@ -233,16 +233,19 @@ __device__ __forceinline__ void euler_step(int dyn, Real dt, const Real *x, cons
 // state does not pick up half an ulp per step over the horizon -- without it,
 // the largest part of a float32 rollout's error.  (Where the increment exceeds
 // the state the captured error is itself rounded, below an ulp of the sum.)
-// An infinite state has no error to carry (inf - inf): lo is held within the
-// largest ulp there is, which no rounding error passes and which leaves an
-// infinity what it is.
+// An infinite state has no error to carry (inf - inf): where the local models do
+// not see the state (hybrid model: position and velocity) and so leave the rollout
+// finite otherwise, lo is held within the largest ulp there is, which no rounding
+// error passes and which leaves an infinity what it is.
 constexpr float kLargestUlp = 2.028241e31f;   // 2^104
 __device__ __forceinline__ void euler_step_comp(int dyn, float dt, const float *x, const float *acc, const float *u,
                                                 float *xn, float *lo) {
   auto add = [&](int a, float rate) {
     const float y = dt * rate + lo[a];
     xn[a] = x[a] + y;
-    lo[a] = __builtin_amdgcn_fmed3f(y - (xn[a] - x[a]), -kLargestUlp, kLargestUlp);   // of a NaN: -kLargestUlp
+    lo[a] = y - (xn[a] - x[a]);
+    if (dyn == kDynQuadHybrid && a < 6)
+      lo[a] = __builtin_amdgcn_fmed3f(lo[a], -kLargestUlp, kLargestUlp);   // of a NaN: -kLargestUlp
   };
   if (dyn == kDynPointMass2D) {
 #pragma unroll
