@@ -422,10 +422,19 @@ __global__ void __launch_bounds__(64, NJ > 2 ? 2 : 1) rollout_wave_kernel(Rollou
   __shared__ Real obs[kMaxObs * 3];
   const ProbDev<Real> &p = ra.p;
   for (int i = threadIdx.x; i < 3 * p.n_obs; i += 64) obs[i] = p.obs[i];
-  for (int i = threadIdx.x; i < m.Ltot * RS; i += 64) tile[i / RS * RSP + i % RS] = rec[i];
-  // a record of zeros for the lanes past an output's last model, whose weight is 0
-  // (a repeated model's infinite parameter times that weight would be NaN)
-  for (int i = threadIdx.x; i < RS; i += 64) tile[m.Ltot * RSP + i] = 0;
+  // Behind each output's records one of zeros, for the lanes past its last model, whose
+  // weight is 0 (a repeated model's infinite parameter times that weight would be NaN).
+  for (int i = threadIdx.x; i < m.Ltot * RS; i += 64) {
+    const int j = i / RS;
+    int slot = j;
+#pragma unroll
+    for (int o = 1; o < NO; ++o) slot += j >= m.L_off[o];
+    tile[slot * RSP + i % RS] = rec[i];
+  }
+  for (int i = threadIdx.x; i < NO * RS; i += 64) {
+    const int o = i / RS;
+    tile[(m.L_off[o + 1] + o) * RSP + i % RS] = 0;
+  }
   __syncthreads();
   const int l = threadIdx.x % P;
   const int64_t n = (int64_t)p.K * p.Ms, row = (int64_t)blockIdx.x * (64 / P) + threadIdx.x / P;
@@ -484,7 +493,7 @@ __global__ void __launch_bounds__(64, NJ > 2 ? 2 : 1) rollout_wave_kernel(Rollou
 #pragma unroll
           for (int jj = g; jj < g + G; ++jj) {
             const int j = jj * P + l;
-            const Real *r = tile + off + (j < L ? j0 + j : m.Ltot) * RSP;
+            const Real *r = tile + off + (j0 + o + min(j, L)) * RSP;
             Real q;
             eval_record<Real, D>(r, z, q, y[o][jj]);
             act[o][jj] = j < L ? kAct * q : ninf;
@@ -557,7 +566,7 @@ static hipError_t rollout_wave_t(const RolloutArgs<Real> &ra, const ModelArgs &m
   const int64_t n = (int64_t)ra.p.K * ra.p.Ms;
   const int L = max_models(m.n_out, m.L_off);
   const int64_t wide = L > 32 ? 6144 : L <= 16 && sizeof(Real) == 4 ? 24576 : 12288;
-  const size_t lds = wave_lds_bytes(sizeof(Real) == 8 ? PI_F64 : PI_F32, m.d, m.Ltot + 1);   // + the zero record
+  const size_t lds = wave_lds_bytes(sizeof(Real) == 8 ? PI_F64 : PI_F32, m.d, m.Ltot + m.n_out);   // + the records of zeros
   auto go = [&](auto kernel, int lanes) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n * lanes + 63) / 64)), dim3(64), lds, s, ra, m, (const Real *)rec);
   };
