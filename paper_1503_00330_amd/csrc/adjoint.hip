@@ -66,7 +66,7 @@ struct AdjArgs {
   const uint32_t *iter;
   const Real *model;    // folded direct records [Ltot][RS]
   int ckpt, ncp;
-  Real *ckpt_buf;       // [S][ncp][NX]
+  Real *ckpt_buf;       // [S][ncp][NX], matrix-core forward: [S][ncp][2 NX]
   Real *seg;            // [S][ckpt+1][SEGW]
   Real *recs;           // [S][T][RW]
   double *jsum;         // [S]
@@ -605,7 +605,8 @@ static size_t adj_gpart_bytes(int dtype, int d, int n_out, int Ltot, int64_t R, 
 
 // Direct kernels: model records, checkpoints [S][ncp][NX], the segment buffer
 // [S][ckpt+1][SEGW], records of every step [S][T][RW], cost sums, parameter
-// partials.  Matrix-core form: model records, checkpoints, one segment's
+// partials.  Matrix-core form: model records, checkpoints [S][ncp][2 NX] (states and their
+// carried rounding errors, so that a segment repeats the forward's states), one segment's
 // trace [S][ckpt+1][SEGW] and records [S][ckpt][RW], cost sums, parameter
 // partials over one segment, the matrix-core tiles and reverse-sweep
 // parameters, the forward costs [S][T] and the state adjoint [S][NX].
@@ -620,7 +621,7 @@ size_t adjoint_ws_bytes(int dtype, int dyn, int K, int M, int T, int Ltot, int d
   const int ncp = (T + ckpt - 1) / ckpt;
   const int segw = nx + (mfma ? 5 : 3) * no, rw = d + (mfma ? 7 : 5) * no + nu;
   const int64_t rec_steps = mfma ? ckpt : T;
-  size_t b = direct_bytes(dtype, d, Ltot) + align_up((size_t)S * ncp * nx * rb, 256) +
+  size_t b = direct_bytes(dtype, d, Ltot) + align_up((size_t)S * ncp * (mfma ? 2 : 1) * nx * rb, 256) +
              align_up((size_t)S * (ckpt + 1) * segw * rb, 256) + align_up((size_t)S * rec_steps * rw * rb, 256) +
              align_up((size_t)S * 8, 256) + adj_gpart_bytes(dtype, d, no, Ltot, S * rec_steps, mfma);
   if (mfma)
@@ -650,7 +651,7 @@ static hipError_t adjoint_t(const ProbDev<Real> &p, const ModelArgs &m, const Re
   a.ckpt = ckpt;
   a.ncp = ncp;
   a.ckpt_buf = (Real *)w;
-  w += align_up((size_t)S * ncp * G::NX * sizeof(Real), 256);
+  w += align_up((size_t)S * ncp * (mfma ? 2 : 1) * G::NX * sizeof(Real), 256);
   const int segw = mfma ? G::SEGW_M : G::SEGW, rw = mfma ? G::RW_M : G::RW;
   a.seg = (Real *)w;
   w += align_up((size_t)S * (ckpt + 1) * segw * sizeof(Real), 256);

@@ -171,10 +171,10 @@ struct RolloutArgs {
                           // of every output at step t (matrix-core kernels only)
   // Segments of the horizon (the adjoint's checkpointed forward; matrix-core
   // kernels only): steps [t_begin, t_end) (t_end < 0: T), starting from x0
-  // or, with xstart, from each sub-rollout's checkpoint xstart [S][nck][n_x]
-  // at slot t_begin / ckpt (nck = ceil(T / ckpt)).  With ckpt_out the state
-  // before every step t with t % ckpt == 0 is stored to ckpt_out (same
-  // layout).  Trace rows count from t_begin, trace_T + 1 of them per
+  // or, with xstart, from each sub-rollout's checkpoint xstart [S][nck][2 n_x]
+  // (the state, then its carried rounding errors) at slot t_begin / ckpt
+  // (nck = ceil(T / ckpt)).  With ckpt_out the state before every step t with
+  // t % ckpt == 0 is stored to ckpt_out (same layout).  Trace rows count from t_begin, trace_T + 1 of them per
   // sub-rollout (trace_T < 0: T).  cost may be null (nothing written).
   int t_begin = 0, t_end = -1, trace_T = -1, ckpt = 0;
   const Real *xstart = nullptr;

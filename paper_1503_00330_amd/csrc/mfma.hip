@@ -1867,13 +1867,12 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   const uint32_t wc = stream_word(kTagCtrl, p.problem_id, it);
   const uint32_t wd = stream_word(kTagDyn, p.problem_id, it);
   if (row < ROWS) {
-    if (sg && sg->xstart && active) {
-      const float *xs0 = sg->xstart + (s * nck + tb / ck) * NX;
-      for (int a = 0; a < NX; ++a) rs.xs[row][a] = xs0[a];
-    } else {
-      for (int a = 0; a < NX; ++a) rs.xs[row][a] = x0[a];
+    const bool seg = sg && sg->xstart && active;
+    const float *xs0 = seg ? sg->xstart + (s * nck + tb / ck) * (2 * NX) : x0;
+    for (int a = 0; a < NX; ++a) {
+      rs.xs[row][a] = xs0[a];
+      rs.xlo[row][a] = seg ? xs0[NX + a] : 0.0f;
     }
-    for (int a = 0; a < NX; ++a) rs.xlo[row][a] = 0.0f;
     sm.z[row][D] = 1.0f;
     sm.z[row][D + 1] = 0.0f;
   }
@@ -1970,9 +1969,12 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
           for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(t - tb) * SEGW + a] = x[a];
         }
         if (ckpt_out && t % ck == 0) {
-          float *dst = ckpt_out + (s * nck + t / ck) * NX;
+          float *dst = ckpt_out + (s * nck + t / ck) * (2 * NX);
 #pragma unroll
-          for (int a = 0; a < NX; ++a) dst[a] = x[a];
+          for (int a = 0; a < NX; ++a) {
+            dst[a] = x[a];
+            dst[NX + a] = rs.xlo[row][a];
+          }
         }
         lwpr_input<DYN>(x, u, z);
 #pragma unroll
