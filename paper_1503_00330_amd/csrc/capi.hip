@@ -578,9 +578,14 @@ struct BatchLayout {
 // 2.39 ms at 16384, 2.08 against 2.87 or 3.59 ms at 24576).
 constexpr int64_t kBatchSharedMinSamples = 16384;
 
-int batch_spw(const pi_problem &p, int64_t n_total) {
-  if (p.tile_samples > 0) return p.tile_samples;
-  return p.variant == PI_VARIANT_MFMA_F16X2 && n_total >= kBatchSharedMinSamples ? 128 : 16;
+// What a problem may ask for: its own tile, or the form's default, whichever the
+// library then picks.
+int batch_request(const pi_problem &p) {
+  return p.tile_samples > 0 ? p.tile_samples : p.variant == PI_VARIANT_MFMA_F16X2 ? 128 : 16;
+}
+
+int batch_spw(const pi_problem &p, bool shared) {
+  return p.tile_samples > 0 ? p.tile_samples : p.variant == PI_VARIANT_MFMA_F16X2 && shared ? 128 : 16;
 }
 
 pi_status batch_layout(int32_t B, const pi_problem *p, const pi_lwpr *m, BatchLayout *out) {
@@ -599,22 +604,29 @@ pi_status batch_layout(int32_t B, const pi_problem *p, const pi_lwpr *m, BatchLa
   BatchLayout L;
   L.waves = p[0].tile_waves > 0 ? p[0].tile_waves : 4;
   L.max_spw = 0;
+  L.pf = variant_pf(p[0].variant);
+  L.bf = L.pf != kPfF32;
   int64_t n_total = 0;   // rollouts of the whole batch
-  for (int b = 0; b < B; ++b) n_total += (int64_t)p[b].K * (p[b].M > 0 ? p[b].M : 1);
+  int max_req = 0;
+  bool mid = false;      // some problem asks for a tile that 8 waves run in the shared form only
+  for (int b = 0; b < B; ++b) {
+    n_total += (int64_t)p[b].K * (p[b].M > 0 ? p[b].M : 1);
+    max_req = std::max(max_req, batch_request(p[b]));
+    mid = mid || (p[b].tile_samples > 16 && p[b].tile_samples <= 32);
+  }
+  // tiles of 33..128 samples: the pieces forms' shared-tile launch
+  if (max_req > (L.bf ? 128 : 32))
+    return fail(PI_ERR_UNSUPPORTED, "batched launches take tile_samples <= 32 (<= 128 with the pieces forms)");
+  if (L.waves == 8 && max_req > 16 && max_req <= 32)
+    return fail(PI_ERR_UNSUPPORTED, "tile_waves 8 needs tile_samples <= 16 (or > 32 with the pieces forms)");
+  const bool shared = n_total >= kBatchSharedMinSamples || (L.waves == 8 && mid);
   L.spw.resize(B);
   L.n_tiles.resize(B);
   for (int b = 0; b < B; ++b) {
-    L.spw[b] = batch_spw(p[b], n_total);
+    L.spw[b] = batch_spw(p[b], shared);
     L.max_spw = std::max(L.max_spw, L.spw[b]);
     L.n_tiles[b] = ((int64_t)p[b].K * (p[b].M > 0 ? p[b].M : 1) + L.spw[b] - 1) / L.spw[b];
   }
-  L.pf = variant_pf(p[0].variant);
-  L.bf = L.pf != kPfF32;
-  // tiles of 33..128 samples: the pieces forms' shared-tile launch
-  if (L.max_spw > (L.bf ? 128 : 32))
-    return fail(PI_ERR_UNSUPPORTED, "batched launches take tile_samples <= 32 (<= 128 with the pieces forms)");
-  if (L.waves == 8 && L.max_spw > 16 && L.max_spw <= 32)
-    return fail(PI_ERR_UNSUPPORTED, "tile_waves 8 needs tile_samples <= 16 (or > 32 with the pieces forms)");
   if (L.bf) {
     for (int b = 0; b < B; ++b)
       if (!bf_model_ok(&m[b])) return fail(PI_ERR_UNSUPPORTED, "problem %d: no pieces form of its model", b);
