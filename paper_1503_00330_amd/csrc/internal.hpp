@@ -52,7 +52,8 @@ inline bool rollout_wave_ok(int dyn, int dtype, int d, int n_out, const int *L_o
   const int L = max_models(n_out, L_off);
   const bool f64 = dtype == PI_F64;
   const bool n_ok = f64 ? n <= 2048 || (n >= 8192 && n <= 32768) : n <= 4096;
-  return dyn != PI_DYN_QUAD12 && (L <= (f64 ? 32 : 40) || (L <= kWaveModels && n_ok)) &&
+  // at least four lanes to a sub-rollout, and a launch has fewer than 2^32 threads
+  return dyn != PI_DYN_QUAD12 && n < ((int64_t)1 << 30) && (L <= (f64 ? 32 : 40) || (L <= kWaveModels && n_ok)) &&
          wave_lds_bytes(dtype, d, L_off[n_out]) <= kWaveLds;
 }
 
