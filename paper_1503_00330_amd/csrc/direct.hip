@@ -671,6 +671,7 @@ constexpr int kUpdSegLen = 8;     // steps between boundaries (a multiple of it 
 constexpr int kUpdRows = 32;      // rows per block of stage 1
 constexpr int kUpdMaxSeg = 64;    // boundaries per row
 constexpr int kUpdQ = 2 + kMaxU;  // values per partial: m, Z, N
+constexpr int kUpdMaxGrid = 1 << 20;   // blocks of stages 1 and 3 (a launch has fewer than 2^32 threads)
 
 size_t update_ws_bytes(int K, int T) {
   const int C = (K + kUpdChunk - 1) / kUpdChunk;
@@ -777,33 +778,35 @@ template <typename Real>
 __global__ void __launch_bounds__(256) update_bound_kernel(const Real *__restrict__ cost, int K, int T, int seg_len,
                                                            int nseg, int vec, double *__restrict__ Sb) {
   __shared__ double tot[kUpdRows][kUpdMaxSeg + 1];
-  const int k0 = blockIdx.x * kUpdRows;
-  for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
-    const int r = e / nseg, j = e - r * nseg;
-    const Real *row = cost + (int64_t)min(k0 + r, K - 1) * T;
-    const int te = min(T, (j + 1) * seg_len);
-    double sum = 0.0;
-    for (int t = j * seg_len; t < te; t += 8) {
-      Real a[4], b[4];
-      load_cost4(row, t, te, vec, a);
-      load_cost4(row, t + 4, te, vec, b);
-      sum += (((double)a[0] + (double)a[1]) + ((double)a[2] + (double)a[3])) +
-             (((double)b[0] + (double)b[1]) + ((double)b[2] + (double)b[3]));
+  for (int64_t k0 = (int64_t)blockIdx.x * kUpdRows; k0 < K; k0 += (int64_t)gridDim.x * kUpdRows) {
+    for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
+      const int r = e / nseg, j = e - r * nseg;
+      const Real *row = cost + min(k0 + r, (int64_t)K - 1) * T;
+      const int te = min(T, (j + 1) * seg_len);
+      double sum = 0.0;
+      for (int t = j * seg_len; t < te; t += 8) {
+        Real a[4], b[4];
+        load_cost4(row, t, te, vec, a);
+        load_cost4(row, t + 4, te, vec, b);
+        sum += (((double)a[0] + (double)a[1]) + ((double)a[2] + (double)a[3])) +
+               (((double)b[0] + (double)b[1]) + ((double)b[2] + (double)b[3]));
+      }
+      tot[r][j] = sum;
     }
-    tot[r][j] = sum;
-  }
-  __syncthreads();
-  if (threadIdx.x < kUpdRows) {
-    double acc = 0.0;
-    for (int j = nseg - 1; j >= 0; --j) {
-      acc += tot[threadIdx.x][j];
-      tot[threadIdx.x][j] = acc;
+    __syncthreads();
+    if (threadIdx.x < kUpdRows) {
+      double acc = 0.0;
+      for (int j = nseg - 1; j >= 0; --j) {
+        acc += tot[threadIdx.x][j];
+        tot[threadIdx.x][j] = acc;
+      }
     }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
-    const int r = e % kUpdRows, j = e / kUpdRows;
-    if (k0 + r < K) Sb[(int64_t)j * K + k0 + r] = tot[r][j];
+    __syncthreads();
+    for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
+      const int r = e % kUpdRows, j = e / kUpdRows;
+      if (k0 + r < K) Sb[(int64_t)j * K + k0 + r] = tot[r][j];
+    }
+    __syncthreads();
   }
 }
 
@@ -964,41 +967,44 @@ __global__ void __launch_bounds__(256) update_part_kernel(ProbDev<Real> p, doubl
 // Stage 3, one block per step: every lane reads its chunks' partials at once, so the
 // block waits for memory once; then minima and sums over the waves and through LDS.
 template <typename Real>
-__global__ void __launch_bounds__(256) update_apply_kernel(int C, int n_u, double lambda,
+__global__ void __launch_bounds__(256) update_apply_kernel(int T, int C, int n_u, double lambda,
                                                            const double *__restrict__ part,
                                                            Real *__restrict__ u_nom, double *__restrict__ norm,
                                                            uint32_t *__restrict__ iter) {
   __shared__ double wmin[4], wsum[4][1 + kMaxU];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // the iteration's draws have all been consumed: advance the iteration word
-  if (i == 0 && threadIdx.x == 0) *iter += 1u;
-  const double *pi_ = part + (int64_t)i * kUpdQ * C;
-  double m = 1.0 / 0.0, v[1 + kMaxU] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int c = threadIdx.x; c < C; c += 256) {
-    const double mc = pi_[c], mn = fmin(m, mc);
-    const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda), fc = mc == mn ? 1.0 : exp(-(mc - mn) / lambda);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *iter += 1u;
+  for (int64_t i = blockIdx.x; i < T; i += gridDim.x) {
+    const double *pi_ = part + i * kUpdQ * C;
+    double m = 1.0 / 0.0, v[1 + kMaxU] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int c = threadIdx.x; c < C; c += 256) {
+      const double mc = pi_[c], mn = fmin(m, mc);
+      const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda), fc = mc == mn ? 1.0 : exp(-(mc - mn) / lambda);
 #pragma unroll
-    for (int q = 0; q <= kMaxU; ++q)
-      if (q <= n_u) v[q] = v[q] * f + pi_[(int64_t)(1 + q) * C + c] * fc;
-    m = mn;
-  }
-  const double wm = wave_min(m);
-  if (lane == 0) wmin[wave] = wm;
-  __syncthreads();
-  const double mn = fmin(fmin(wmin[0], wmin[1]), fmin(wmin[2], wmin[3]));
-  const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda);
+      for (int q = 0; q <= kMaxU; ++q)
+        if (q <= n_u) v[q] = v[q] * f + pi_[(int64_t)(1 + q) * C + c] * fc;
+      m = mn;
+    }
+    const double wm = wave_min(m);
+    if (lane == 0) wmin[wave] = wm;
+    __syncthreads();
+    const double mn = fmin(fmin(wmin[0], wmin[1]), fmin(wmin[2], wmin[3]));
+    const double f = m == mn ? 1.0 : exp(-(m - mn) / lambda);
 #pragma unroll
-  for (int q = 0; q <= kMaxU; ++q) {
-    const double w = q <= n_u ? wave_sum(v[q] * f) : 0.0;
-    if (lane == 0) wsum[wave][q] = w;
-  }
-  __syncthreads();
-  auto total = [&](int q) { return (wsum[0][q] + wsum[1][q]) + (wsum[2][q] + wsum[3][q]); };
-  const int a = threadIdx.x;
-  if (a < n_u) u_nom[i * n_u + a] = (Real)((double)u_nom[i * n_u + a] + total(1 + a) / total(0));
-  if (a == 0) {
-    norm[2 * i] = mn;
-    norm[2 * i + 1] = total(0);
+    for (int q = 0; q <= kMaxU; ++q) {
+      const double w = q <= n_u ? wave_sum(v[q] * f) : 0.0;
+      if (lane == 0) wsum[wave][q] = w;
+    }
+    __syncthreads();
+    auto total = [&](int q) { return (wsum[0][q] + wsum[1][q]) + (wsum[2][q] + wsum[3][q]); };
+    const int a = threadIdx.x;
+    if (a < n_u) u_nom[i * n_u + a] = (Real)((double)u_nom[i * n_u + a] + total(1 + a) / total(0));
+    if (a == 0) {
+      norm[2 * i] = mn;
+      norm[2 * i + 1] = total(0);
+    }
+    if (i + gridDim.x < T) __syncthreads();   // the sums have been read
   }
 }
 
@@ -1026,8 +1032,8 @@ static void update_part(const ProbDev<Real> &p, const Real *cost, const uint32_t
   const int nseg = (T + seg_len - 1) / seg_len;
   const int vec = T % 4 == 0 && (uintptr_t)cost % 16 == 0;
   *part = (double *)((char *)ws + align_up((size_t)K * nseg * 8, 256));
-  hipLaunchKernelGGL(update_bound_kernel<Real>, dim3((K + kUpdRows - 1) / kUpdRows), dim3(256), 0, s, cost, K, T,
-                     seg_len, nseg, vec, ws);
+  hipLaunchKernelGGL(update_bound_kernel<Real>, dim3(std::min((K - 1) / kUpdRows + 1, kUpdMaxGrid)), dim3(256), 0, s,
+                     cost, K, T, seg_len, nseg, vec, ws);
   if (single)
     hipLaunchKernelGGL((update_part_kernel<Real, NU, 1, 1>), dim3((C + 3) / 4, T), dim3(256), 0, s, p, lambda, inv,
                        weighting, iter, cost, (const double *)ws, seg_len, nseg, vec, C, *part);
@@ -1049,7 +1055,7 @@ static hipError_t update_t(const ProbDev<Real> &p, const Real *cost, const uint3
     update_part<Real, 2>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
   else
     update_part<Real, 4>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
-  hipLaunchKernelGGL(update_apply_kernel<Real>, dim3(T), dim3(256), 0, s, C, p.n_u, lambda,
+  hipLaunchKernelGGL(update_apply_kernel<Real>, dim3(std::min(T, kUpdMaxGrid)), dim3(256), 0, s, T, C, p.n_u, lambda,
                      (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
   if (W) {
     const unsigned nb = (unsigned)((K + kWgtK - 1) / kWgtK);

@@ -44,3 +44,18 @@ def test_more_rollouts_than_a_quarter_of_the_threads():
         goal, w = (torch.as_tensor(np.asarray(a[:2]), device="cuda") for a in (prob.goal, prob.w_pos))
         ref = prob.dt * ((w * (p - goal) ** 2).sum(1) + (v ** 2).sum(1))
         assert (cost[k0:k0 + 70, 0] - ref).abs().max() <= 1e-12 * ref.abs().max()
+
+
+# updates with 2^24 steps and more (a block per step), and with 2^29 rollouts and more
+# (eight threads each).  One rollout is free and the others' weights vanish: the plan
+# moves by that rollout's draws
+@pytest.mark.parametrize("K,T", [(3, (1 << 24) + 16), ((1 << 29) + 40, 9)])
+def test_more_steps_or_rollouts_than_blocks(K, T):
+    prob, _ = _problem(np.float32, K, 4)
+    prob.T, prob.u_nom = T, np.zeros((T, 2), np.float32)
+    dp = pi.DeviceProblem(prob)
+    cost = torch.full((K, T), 2000.0, device="cuda")
+    cost[K - 1] = 0.0
+    eps = pi.noise(dp, pi.PI_TAG_CTRL, K - 1, 1)[0]
+    u, _ = pi.update(dp, cost)
+    assert torch.equal(u, eps) and int(dp.iter) == 1
