@@ -354,7 +354,10 @@ RolloutPlan rollout_plan(const pi_problem *p, const pi_lwpr *m) {
     r.spw = n >= 256 * 16 ? 16 : 8;
   }
   r.groups = (n + r.spw - 1) / r.spw;
-  r.pair_ok = split_allowed && r.spw <= 16 && r.groups <= kMaxPairGroups;
+  // a pieces form left to choose its tile: no pairs (and no slots for them, which the
+  // allocation-free entry point has no room for) from kMaxPairGroups full tiles on
+  const bool many = r.bf && p->tile_samples == 0 && n >= 16 * kMaxPairGroups;
+  r.pair_ok = split_allowed && r.spw <= 16 && r.groups <= kMaxPairGroups && !many;
   return r;
 }
 
