@@ -165,7 +165,9 @@ typedef struct {
                                     * each runs half and they exchange partial
                                     * sums every step); 0 = library's choice:
                                     * 2 when the device has a compute unit for
-                                    * each workgroup of the pairs.  Float32
+                                    * each workgroup of the pairs (for the point
+                                    * mass and the hybrid model with many local
+                                    * models: for each pair).  Float32
                                     * matrix-core rollouts with tile_samples
                                     * <= 16 (4 waves, or 8 for the quadrotor)
                                     * only; otherwise 1.                       */

@@ -386,10 +386,20 @@ int device_cus(int *dev_out = nullptr) {
 }
 
 // Pairing at launch: requested (tile_split 2) or, by default, when the pairs
-// still find a compute unit each (past that the units that hold two workgroups
-// set the pace: 3000 rollouts of 6 x 256 models, 61 steps, 1.46 ms in pairs,
-// 1.31 ms without); in both cases only if the whole grid is resident.
-bool use_pair(const pi_problem *p, const RolloutPlan &pl) {
+// still find a compute unit each; in both cases only if the whole grid is resident.
+// Past that the units that hold two workgroups set the pace, and a step in pairs
+// costs the same from 129 to 256 tiles of rollouts (microseconds for 40 steps of 2100
+// and of 4000 rollouts, in pairs and without):
+//   quadrotor  6 x 64     float32 392, 349; 402, 352    fp16 318, 298; 324, 305
+//              6 x 1024   float32 3035, 2872; 2970, 2887    fp16 2066, 1930; 1982, 1939
+//   hybrid     3 x 400    286, 277; 290, 277    3 x 600   342, 356; 357, 360
+//              3 x 1500   616, 684; 637, 689
+//   point mass 2 x 800    368, 363; 380, 364    2 x 1000  423, 434; 440, 438
+//              2 x 1500   565, 595; 583, 596
+// so models of the small dynamics go in pairs up to the unit count from kPairTiles model
+// tiles on.
+constexpr int kPairTiles = 112;
+bool use_pair(const pi_problem *p, const pi_lwpr *m, const RolloutPlan &pl) {
   if (!pl.pair_ok) return false;
   int dev = 0;
   const int n_cu = device_cus(&dev);
@@ -409,7 +419,8 @@ bool use_pair(const pi_problem *p, const RolloutPlan &pl) {
   }
   const bool resident = (int64_t)pair_grid(pl.groups) <= (int64_t)cap * n_cu;
   if (!resident) return false;
-  return p->tile_split == 2 || 2 * pl.groups <= n_cu;
+  if (p->tile_split == 2 || 2 * pl.groups <= n_cu) return true;
+  return p->dyn != PI_DYN_QUAD12 && pl.groups < n_cu && mfma_layout(m->d, m->n_out, m->L_off).n_tiles >= kPairTiles;
 }
 
 // The rollout launch on the current device: the plan, whether its tiles are
@@ -425,7 +436,7 @@ struct RolloutLaunch {
 
 RolloutLaunch rollout_launch(const pi_problem *p, const pi_lwpr *m) {
   RolloutLaunch r{rollout_plan(p, m), false};
-  r.pair = use_pair(p, r.pl);
+  r.pair = use_pair(p, m, r.pl);
   if (p->tile_waves == 0 && r.pl.mfma && p->dyn == PI_DYN_QUAD12 && r.pl.spw <= 16) {
     const int n_cu = device_cus();
     const int64_t wgs = r.pair ? 2 * r.pl.groups : r.pl.groups;
@@ -433,7 +444,7 @@ RolloutLaunch rollout_launch(const pi_problem *p, const pi_lwpr *m) {
       RolloutPlan p8 = r.pl;
       p8.waves = 8;
       // a pair keeps four waves if its 8-wave grid would not be resident
-      if (!r.pair || use_pair(p, p8)) r.pl = p8;
+      if (!r.pair || use_pair(p, m, p8)) r.pl = p8;
     }
   }
   return r;

@@ -1,0 +1,46 @@
+"""The launches that the library picks, either side of each of its limits."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import DYN_POINTMASS2D, DYN_QUAD12, DYN_QUAD_HYBRID, OBS_SMOOTH
+
+torch = pytest.importorskip("torch")
+pi = pytest.importorskip("paper_1503_00330_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    yield
+    torch.cuda.synchronize()
+
+
+def _problem(K, L, dyn=DYN_QUAD12, T=3, **kw):
+    prob, model = synth.tiny_problem(74, dyn=dyn, L=L, R=2, K=K, T=T, M=1, dtype=np.float32, n_obs=2,
+                                     obs_kind=OBS_SMOOTH)
+    return prob, model, pi.DeviceProblem(prob, **kw), pi.DeviceModel(model)
+
+
+def _parity(prob, model, dp, dm):
+    got = pi.rollout_cost(dp, dm).cpu().numpy().astype(np.float64)
+    ref = oracle.rollout_cost(prob, model)
+    # three float32 steps: well inside the 1e-4 that trajectory costs are held to
+    assert np.all(np.abs(got.sum(1) - ref.sum(1)) <= 1e-5 * np.abs(ref.sum(1)))
+
+
+# pairs of workgroups: up to half the compute units' tiles, and for many local models
+# of the small dynamics up to all of them (128 and 255 tiles of 16 on 256 units)
+@pytest.mark.parametrize("dyn,L,K,split", [
+    (DYN_QUAD_HYBRID, [590, 600, 590], 2048, 2), (DYN_QUAD_HYBRID, [590, 600, 590], 2049, 2),
+    (DYN_QUAD_HYBRID, [590, 600, 590], 4080, 2), (DYN_QUAD_HYBRID, [590, 600, 590], 4081, 1),
+    (DYN_QUAD_HYBRID, [400, 400, 400], 2048, 2), (DYN_QUAD_HYBRID, [400, 400, 400], 2049, 1),
+    (DYN_POINTMASS2D, [900, 892], 4080, 2), (DYN_POINTMASS2D, [700, 700], 2049, 1)])
+def test_pairs_of_the_small_dynamics(dyn, L, K, split):
+    prob, model, dp, dm = _problem(K, L, dyn)
+    assert pi.rollout_describe(dp, dm)["tile_split"] == split
+    _parity(prob, model, dp, dm)
