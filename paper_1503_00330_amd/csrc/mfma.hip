@@ -1449,9 +1449,12 @@ struct SampleArgs {
   float *trace = nullptr;
   int64_t trace_stride = 0;
   int trace_off = 0, trace_rows = 0;
-  // optional moments (prediction): mean[row * n_out + o], var[...] of rows < moment_rows
+  // optional moments (prediction): mean[row * n_out + o], var[...] of rows < moment_rows;
+  // full: the pass takes every piece (mprev of a row and output then holds whether its
+  // sums were usable)
   float *mean = nullptr, *var = nullptr;
   int moment_rows = 0, n_out = 0;
+  bool full = true;
 };
 
 // Eq. (1) moments of one (row, output) from its complete sums, the sampled
@@ -1480,10 +1483,18 @@ __device__ __forceinline__ void finish_sums(MixSmem<D, MT, NW, PF> &sm, int row,
   }
   sm.accel(row, o) = sa.xi ? mu + sqrtf(var) * sa.xi[row * MixSmem<D, MT, NW, PF>::XIS + o] : mu;
   const bool valid = isfinite(s.Z) && isfinite(s.S1) && isfinite(s.S2) && isfinite(s.S3) && s.mx >= kAnchorLo;
-  // a prediction's reference far from its mean (a coarse pass, far inputs) costs
-  // the variance its digits: 2^-24 d1^2 beside var
-  const bool off = sa.mean && !(d1 * d1 <= 4.0f * var) && row < sa.moment_rows;
-  if (!valid || off) sm.redo[ev & 1] = 1;
+  if (sa.mean) {
+    // a prediction's reference far from its mean (a coarse pass, far inputs) costs
+    // the variance its digits: 2^-24 d1^2 beside var.  A reference that is the mean of
+    // a full pass is as near as rounding lets it (the variance may be 0), and sums that
+    // no anchor or reference makes finite stay what they are.
+    const bool off = d1 * d1 > 4.0f * var && sm.mprev[row][o] == 0.0f;
+    const bool lost = isnan(s.Z) || (isfinite(s.Z) && s.mx >= kAnchorLo && !isfinite(mu));
+    if ((!valid || off) && !lost && row < sa.moment_rows) sm.redo[ev & 1] = 1;
+    sm.mprev[row][o] = sa.full && valid ? 1.0f : 0.0f;
+  } else if (!valid) {
+    sm.redo[ev & 1] = 1;
+  }
   sm.mref[row][o] += s.mx;
   if (isfinite(mu)) sm.yref[row][o] = mu;
 }
@@ -1664,8 +1675,8 @@ __device__ __forceinline__ void reset_anchors(MixSmem<D, MT, NW, PF> &sm) {
 // bf16 pieces (d = 16): the first pass takes the leading piece alone, a sixth of
 // the products -- an anchor within 100 units of the largest activation and a
 // reference within two standard deviations of the mean are all it has to give --
-// and the second all three; a third, and a fourth, follow only where those were
-// out of that range (inputs far from every model).  Bound: the matrix pipe (42 bf16 products per 16 x 16
+// and the second all three; a third follows where the reference was out of that
+// range, a fourth where the anchor was (inputs far from every model).  Bound: the matrix pipe (42 bf16 products per 16 x 16
 // block against 88 float32 ones of twice the length); 100003 inputs, 6 x 256
 // models: 0.36 ms, 0.94 ms in two float32 passes of 16-row workgroups.
 template <int D, int MT, int NW, int PF>
@@ -1709,6 +1720,7 @@ __global__ void __launch_bounds__(NW * 64) predict_mfma_kernel(MfmaModel md, con
           mixture_tiles_bf<D, MT, NW, PF, SM::NPC, true>(md, sm, 0, md.n_tiles);
       }
       __syncthreads();
+      sa.full = pass > 0;
       merge_waves(sm, md.n_out, 0u, sa);
       __syncthreads();
       if (pass > 0 && sm.redo[0] == 0) break;
