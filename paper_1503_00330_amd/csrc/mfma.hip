@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
   __shared__ double cs[16][kMaxD];
   __shared__ float val[16][kFoldVals + 1];
   __shared__ unsigned char pa[kMaxD * (kMaxD + 1) / 2], pb[kMaxD * (kMaxD + 1) / 2];
-  __shared__ int eq[16], ey[16];
+  __shared__ int eq[16], ey[16], big[16];
   const int tile = blockIdx.x, d = m.d, R = m.R, tid = threadIdx.x;
   const MfmaGeom g = MfmaGeom::make(d);
   int o = 0;
@@ -264,7 +264,14 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
   // m then hold 22 bits, and every smaller value of the set is kept to
   // within 2^-25 absolute, 2^-23 of m, the lo piece's subnormal step); any
   // other set is scaled by the power of two 2^-e that brings m to [2^13,
-  // 2^14) (fp16 holds up to 65504; the padded models' -1e30 included).
+  // 2^14) (fp16 holds up to 65504).
+  // A padded slot beside models of the first kind, all below 2^13, is one of them:
+  // -2 x 65504 (1 + sum_a z_a^2), in both pieces, lies below every such model's
+  // activation at any z, which is at least -2^13 (9 + 9 sum_a z_a^2) -- by far
+  // enough that it has no weight and is never the largest.  So outputs whose models
+  // do not fill their last tile need no scales (a rollout with some runs the slower
+  // loop of mixture_tiles_sh: 32768 rollouts, 6 x 61 models, 27.3 us per step against
+  // 24.5).  Beside any other model the slot holds kPadAct, scaled.
   {
     float mq = 0.0f, my = 0.0f;
     for (int f = a; f < g.KQ; f += 16) mq = fmaxf(mq, fabsf(val[col][f]));
@@ -277,29 +284,40 @@ __global__ void __launch_bounds__(kFoldThreads) fold_mfma_kernel(ModelArgs m, Mf
       int ex = 0;
       if (mm > 0.0f) frexpf(mm, &ex);   // mm < 2^ex
       (a == 0 ? eq : ey)[col] = (ex > 14 || ex < -1) ? ex - 14 : 0;
+      if (a == 0) big[col] = ex > 13;
     }
     if (a == 2) hmeta[(size_t)tile * kHfMeta + col] = s2;
   }
   __syncthreads();
+  int any = 0, any_big = 0;   // over the tile's models
+  for (int c = 0; c < nvalid; ++c) {
+    any |= eq[c] | ey[c];
+    any_big |= big[c];
+  }
+  const bool pad16 = any == 0 && any_big == 0;   // padded slots in fp16's own range
   if (tid >= 16 && tid < 64) {
     const int slot = tid & 15, part = tid >> 4;
     float v = 0.0f;
-    if (part < 3) {
-      v = ldexpf(1.0f, part == 1 ? eq[slot] : ey[slot]);
-    } else if (slot == kHfPlain - 48) {
-      int any = 0;
-      for (int c = 0; c < 16; ++c) any |= eq[c] | ey[c];
-      v = any == 0 ? 1.0f : 0.0f;
-    }
+    if (part < 3)
+      v = slot >= nvalid && pad16 ? 1.0f : ldexpf(1.0f, part == 1 ? eq[slot] : ey[slot]);
+    else if (slot == kHfPlain - 48)
+      v = any == 0 && (nvalid == 16 || pad16) ? 1.0f : 0.0f;
     hmeta[(size_t)tile * kHfMeta + tid] = v;
   }
   u32x4 *dsth = (u32x4 *)(Wh + (size_t)tile * kHfTileU32);
   for (int e = tid; e < kBfNKB * 64; e += kFoldThreads) {
     const int lane = e & 63, kb = e >> 6, k0 = 32 * (kb < kBfNKQ ? kb : 0) + 8 * (lane / 16);
-    const int sc = kb < kBfNKQ ? eq[lane & 15] : ey[lane & 15];
+    const bool pad = (lane & 15) >= nvalid && pad16;
+    const int sc = pad ? 0 : kb < kBfNKQ ? eq[lane & 15] : ey[lane & 15];
     uint16_t pc[8][2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) f16_split2(ldexpf(piece_value(kb, k0 + i, lane & 15), -sc), pc[i]);
+    for (int i = 0; i < 8; ++i) {
+      const int k = k0 + i;
+      if (pad && kb < kBfNKQ && ((k < g.NP && pa[k] == pb[k]) || k == g.NP + d))
+        pc[i][0] = pc[i][1] = 0xFBFF;   // -65504
+      else
+        f16_split2(ldexpf(piece_value(kb, k, lane & 15), -sc), pc[i]);
+    }
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       u32x4 w;
