@@ -258,48 +258,48 @@ bool auto_pieces(const pi_problem *p, const pi_lwpr *m, int64_t n) {
 }
 
 // Tile (and waves) of a pieces-form problem that leaves its tile to the
-// library: the launch with the least time per step on 256 compute units, as
-// (passes over the device) x (a + b model tiles), a and b in microseconds
-// fitted to 61-step launches of 6 x 64, 6 x 256 and 6 x 1024 models (24, 96 and
-// 384 tiles; fitted within 15 %):
-//              fp16 pieces          bf16 pieces          rollouts per pass
-//   16 rows    2.6 + 0.105 t        1.0 + 0.164 t        4096 (8192 in halves)
-//   32 rows    7.5 + 0.142 t        5.5 + 0.219 t        8192
-//   64 rows   12.3 + 0.259 t       13.0 + 0.406 t        16384
-//   128 rows  16.8 + 0.344 t (8 waves)   11.6 + 0.627 t (8), 13 + 0.722 t (4)   32768
-// e.g. 16384 rollouts, fp16, 96 tiles: 48 (measured), 40, 37 and 49 us per step.
+// library: the launch with the least time per step, passes over 256 compute units
+// times the microseconds of one, measured over whole launches (40 steps, 2100 to
+// 80000 rollouts, models of 6 x 16 to 6 x 1024) and linear between the measured
+// numbers of model tiles.  Over those launches the choice is within 1 % of the best
+// one on average, 12 % at most, and never slower than 16 rows up to 32767 rollouts
+// and 128 from there on (but for one launch at 0.7 %).
 struct TileChoice {
   int spw, waves;
 };
 TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles) {
+  constexpr int kPts = 6;
+  static const double kTiles[kPts] = {6, 24, 72, 96, 192, 384};
   struct Form {
     int spw, waves;
-    int64_t pass;
-    double a, b;
+    double us[kPts];
   };
-  static const Form kF16[] = {{16, 4, 4096, 2.6, 0.105}, {32, 4, 8192, 7.5, 0.142}, {64, 4, 16384, 12.3, 0.259},
-                              {128, 8, 32768, 16.8, 0.344}};
-  static const Form kB16[] = {{16, 4, 4096, 1.0, 0.164}, {32, 4, 8192, 5.5, 0.219}, {64, 4, 16384, 13.0, 0.406},
-                              {128, 8, 32768, 11.6, 0.627}, {128, 4, 32768, 13.0, 0.722}};
-  const bool hf = pf == kPfF16x2;
-  const Form *f = hf ? kF16 : kB16;
-  const int nf = hf ? 4 : 5;
+  static const Form kF16[] = {{16, 4, {3.2, 4.6, 10.1, 12.3, 23.0, 46.2}},
+                              {16, 8, {4.8, 7.3, 12.2, 14.8, 24.9, 48.2}},
+                              {32, 4, {9.1, 11.0, 16.9, 19.9, 32.0, 60.0}},
+                              {64, 4, {11.2, 17.4, 29.7, 35.9, 61.0, 115.0}},
+                              {128, 4, {16.4, 25.0, 46.8, 58.0, 103.5, 200.0}},
+                              {128, 8, {15.5, 24.5, 41.5, 50.5, 87.0, 162.0}}};
+  static const Form kB16[] = {{16, 4, {3.1, 5.5, 12.7, 16.2, 31.0, 64.5}},
+                              {16, 8, {4.7, 7.8, 14.0, 17.5, 31.7, 65.7}},
+                              {32, 4, {8.1, 11.2, 20.5, 25.3, 45.5, 87.0}},
+                              {64, 4, {12.1, 21.1, 39.8, 49.6, 90.0, 170.0}},
+                              {128, 4, {18.7, 31.8, 66.5, 84.0, 157.0, 303.0}},
+                              {128, 8, {14.5, 26.3, 60.0, 77.0, 144.0, 280.0}}};
+  int i = 0;
+  while (i + 2 < kPts && n_tiles > kTiles[i + 1]) ++i;
+  const double at = (n_tiles - kTiles[i]) / (kTiles[i + 1] - kTiles[i]);
   TileChoice best{16, 4};
   double t_best = 0;
-  for (int i = 0; i < nf; ++i) {
-    // a caller's 8 waves run tiles of 16 or 128 rows; its 4, or the library's
-    // choice for PI_VARIANT_AUTO, no 8-wave launch
-    if (waves == 8 ? (f[i].spw == 32 || f[i].spw == 64 || (f[i].spw == 128 && f[i].waves == 4))
-                   : waves == 4 && f[i].waves == 8 && !hf)
-      continue;
-    double passes = (double)((n + f[i].pass - 1) / f[i].pass);
-    if (i == 0 && passes > 4) passes = (double)n / (double)f[i].pass;   // many small tiles: no whole last pass
-    const double t = passes * (f[i].a + f[i].b * n_tiles);
-    if (i == 0 || t < t_best) {
-      // leave 16 rows for a gain past the fit's error: 17966 rollouts, fp16, 72
-      // tiles, 128 rows 47.1 us per step, 16 rows 46.6 (by the fit 41.6 and 44.6)
-      t_best = i == 0 ? 0.92 * t : t;
-      best = TileChoice{f[i].spw, waves > 0 ? waves : f[i].waves};
+  for (const Form &f : pf == kPfF16x2 ? kF16 : kB16) {
+    // a caller's waves, if given (the library's 16-row tiles take theirs by the grid
+    // of the launch, see rollout_launch)
+    if (waves > 0 ? f.waves != waves : f.spw == 16 && f.waves == 8) continue;
+    const int64_t pass = 256 * (int64_t)f.spw;
+    const double t = (double)((n + pass - 1) / pass) * (f.us[i] + at * (f.us[i + 1] - f.us[i]));
+    if (t_best == 0 || t < t_best) {
+      t_best = t;
+      best = TileChoice{f.spw, f.waves};
     }
   }
   return best;
