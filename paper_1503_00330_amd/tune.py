@@ -5,8 +5,11 @@ launch (samples per tile, waves per workgroup, workgroups per tile, and the
 contraction: float32 matrix-core products, their three-piece bf16 form or
 their two-piece fp16 form)
 with HIP events and caches the fastest in a JSON file keyed by the device
-architecture, the shape and the requested variant; for a batch of problems it
-times the batched launch for every uniform tile shape and contraction.  A
+architecture, the shape, the requested variant and the version of the launch
+set; ensure() also times the launches that the library picks by itself (its
+cost model has tiles that no candidate names), and keeps one that wins.  For a
+batch of problems it times the batched launch for every uniform tile shape and
+contraction.  A
 missing, unreadable or corrupt cache simply means "not tuned": the library's
 defaults apply.  The cache path is $PI2RH_AUTOTUNE_CACHE or
 ~/.cache/pi2rh/tune.json.
@@ -36,7 +39,11 @@ CANDIDATES: Tuple[Tuple[int, int, int, int], ...] = (tuple(s + (v,) for v in (_M
 # uniform launches of a batch: (samples per tile, waves per workgroup, contraction)
 BATCH_CANDIDATES: Tuple[Tuple[int, int, int], ...] = (tuple(s + (v,) for v in (_MF, _BF, _HF)
                                                             for s in _BATCH_SHAPES)
-                                                      + tuple((128, w, v) for v in (_BF, _HF) for w in (4, 8)))
+                                                      + tuple((128, w, v) for v in (_BF, _HF) for w in (4, 8))
+                                                      + tuple((64, 4, v) for v in (_BF, _HF)))
+# part of every cache key: raised when the kernels behind a launch or the launches
+# change, so that entries timed on others are tuned again
+LAUNCH_SET = 2
 
 
 def cache_path() -> str:
@@ -48,13 +55,16 @@ def shape_key(arch: str, dtype_code: int, d: int, n_out: int, L_off, R: int, K: 
               dyn: int = 1, variant: int = 0) -> str:
     Ls = [int(L_off[i + 1]) - int(L_off[i]) for i in range(n_out)]
     kb = 1 << max(0, int(K * max(M, 1) - 1).bit_length())  # power-of-two bucket of samples
-    return "%s|dyn%d|dt%d|d%d|o%d|L%s|R%d|S%d|T%d|v%d" % (arch, dyn, dtype_code, d, n_out,
-                                                          "-".join(map(str, Ls)), R, kb, T, variant)
+    return "%s|dyn%d|dt%d|d%d|o%d|L%s|R%d|S%d|T%d|v%d|set%d" % (arch, dyn, dtype_code, d, n_out,
+                                                                "-".join(map(str, Ls)), R, kb, T, variant,
+                                                                LAUNCH_SET)
 
 
 def _valid(v) -> bool:
     if not isinstance(v, list) or not all(isinstance(x, int) for x in v):
         return False
+    if len(v) == 4 and v[:3] == [0, 0, 0]:        # the library's choice of tile, waves and pairing
+        return v[3] in (0, _MF, _BF, _HF)
     return tuple(v) in CANDIDATES or tuple(v) in BATCH_CANDIDATES
 
 
@@ -140,6 +150,13 @@ def candidates_for(prob, model=None) -> Tuple[Tuple[int, int, int, int], ...]:
     return tuple(out)
 
 
+def library_launches(prob, model) -> Tuple[Tuple[int, int, int, int], ...]:
+    """The launches left to the library: the requested variant's, and with
+    PI_VARIANT_AUTO those of each contraction that the tuner searches."""
+    req = _requested(prob)
+    return tuple((0, 0, 0, v) for v in dict.fromkeys((req,) + _variants_for(prob, [model])))
+
+
 def _launch(prob):
     return (prob.tile_samples, prob.tile_waves, prob.tile_split, prob.variant)
 
@@ -178,11 +195,19 @@ def tune_rollout(prob, model, candidates: Optional[Iterable[Tuple[int, int, int,
                  path: Optional[str] = None, save: bool = True):
     """Times every candidate launch; stores and returns the fastest
     ((samples, waves, split, variant), {candidate: ms})."""
-    import torch
-    from . import rollout_cost
     if _requested(prob) not in (0, _MF, _BF, _HF):
         raise ValueError("launch shapes apply to the matrix-core rollout kernels")
     cands = tuple(candidates) if candidates is not None else candidates_for(prob, model)
+    times = _time_launches(prob, model, cands, reps)
+    best = min(times, key=times.get)
+    if save:
+        _save(prob, model, best, path)
+    return best, times
+
+
+def _time_launches(prob, model, cands, reps: int) -> Dict[Tuple[int, int, int, int], float]:
+    import torch
+    from . import rollout_cost
     saved = _launch(prob)
     cost = torch.empty((prob.K, prob.T), dtype=prob.dtype, device=prob.device)
     times = {}
@@ -192,24 +217,29 @@ def tune_rollout(prob, model, candidates: Optional[Iterable[Tuple[int, int, int,
             times[tuple(c)] = _time(lambda: rollout_cost(prob, model, out=cost), reps)
     finally:
         prob.tile_samples, prob.tile_waves, prob.tile_split, prob.variant = saved
-    best = min(times, key=times.get)
-    if save:
-        data = load_cache(path)
-        data[key_for(prob, model)] = list(best)
-        save_cache(data, path)
-    return best, times
+    return times
+
+
+def _save(prob, model, best, path) -> None:
+    data = load_cache(path)
+    data[key_for(prob, model)] = list(best)
+    save_cache(data, path)
 
 
 def ensure(prob, model, path: Optional[str] = None, reps: int = 3):
     """Applies the cached launch for this shape, tuning (and caching) it first
-    if there is none.  A problem that the library runs on its small-model kernel,
-    which has no launch shape, is left to it.  Returns the (samples, waves, split,
-    variant) in use."""
+    if there is none; the library's own launches take part.  A problem that the
+    library runs on its small-model kernel, which has no launch shape, is left to
+    it.  Returns the (samples, waves, split, variant) in use, zeros for what the
+    library picks."""
     from . import rollout_describe
     if _requested(prob) == 0 and rollout_describe(prob, model)["variant"] == "direct":
         return _launch(prob)
     if not apply(prob, model, path):
-        best, _ = tune_rollout(prob, model, reps=reps, path=path)
+        _, times = tune_rollout(prob, model, reps=reps, save=False)
+        times.update(_time_launches(prob, model, library_launches(prob, model), reps))
+        best = min(times, key=times.get)
+        _save(prob, model, best, path)
         _set_launch(prob, best)
     return _launch(prob)
 
