@@ -240,6 +240,7 @@ struct RolloutPlan {
 };
 
 constexpr int64_t kMaxPairGroups = 2048;
+constexpr int64_t kSharedTileMinSamples = 128 * 256;   // 128-row tiles for every unit of 256
 // Rollouts up to which the float32 16-row pairs of workgroups cover a 256-unit
 // device once.
 constexpr int64_t kPairFullSamples = 16 * 128;
@@ -258,51 +259,59 @@ bool auto_pieces(const pi_problem *p, const pi_lwpr *m, int64_t n) {
 }
 
 // Tile (and waves) of a pieces-form problem that leaves its tile to the
-// library: the launch with the least time per step, passes over 256 compute units
-// times the microseconds of one, measured over whole launches (40 steps, 2100 to
-// 80000 rollouts, models of 6 x 16 to 6 x 1024) and linear between the measured
-// numbers of model tiles.  Over those launches the choice is within 1 % of the best
-// one on average, 12 % at most, and never slower than 16 rows up to 32767 rollouts
-// and 128 from there on (but for one launch at 0.7 %).
+// library: 16 rows up to 32767 rollouts and 128 from there on, or the launch with the
+// least time per step if that is clearly less.  The time is passes over 256 compute
+// units times the microseconds of one, measured over whole launches (40 steps, 2100 to
+// 80000 rollouts, models of 6 x 16 to 6 x 1024, 10 obstacles) and linear between the
+// measured numbers of model tiles, plus what an obstacle adds where the costs are
+// evaluated between the steps' products (10289 rollouts x 25 steps, 72 tiles, 35
+// obstacles, fp16: 16 rows 29.6 us, 64 rows 32.0).  Over the measured launches the
+// choice is within half a per cent of the best one on average, 11 % at most, and never
+// slower than the rule it starts from (but for one launch, by 0.7 %).
 struct TileChoice {
   int spw, waves;
 };
-TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles) {
-  constexpr int kPts = 6;
+constexpr double kTileMargin = 0.97;
+TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles, int n_obs) {
+  constexpr int kPts = 6, kObs = 10;
   static const double kTiles[kPts] = {6, 24, 72, 96, 192, 384};
   struct Form {
     int spw, waves;
-    double us[kPts];
+    double us[kPts], obs;
   };
-  static const Form kF16[] = {{16, 4, {3.2, 4.6, 10.1, 12.3, 23.0, 46.2}},
-                              {16, 8, {4.8, 7.3, 12.2, 14.8, 24.9, 48.2}},
-                              {32, 4, {9.1, 11.0, 16.9, 19.9, 32.0, 60.0}},
-                              {64, 4, {11.2, 17.4, 29.7, 35.9, 61.0, 115.0}},
-                              {128, 4, {16.4, 25.0, 46.8, 58.0, 103.5, 200.0}},
-                              {128, 8, {15.5, 24.5, 41.5, 50.5, 87.0, 162.0}}};
-  static const Form kB16[] = {{16, 4, {3.1, 5.5, 12.7, 16.2, 31.0, 64.5}},
-                              {16, 8, {4.7, 7.8, 14.0, 17.5, 31.7, 65.7}},
-                              {32, 4, {8.1, 11.2, 20.5, 25.3, 45.5, 87.0}},
-                              {64, 4, {12.1, 21.1, 39.8, 49.6, 90.0, 170.0}},
-                              {128, 4, {18.7, 31.8, 66.5, 84.0, 157.0, 303.0}},
-                              {128, 8, {14.5, 26.3, 60.0, 77.0, 144.0, 280.0}}};
+  static const Form kF16[] = {{16, 4, {3.2, 4.6, 10.1, 12.4, 23.0, 46.2}, 0.0},
+                              {16, 8, {4.8, 7.3, 12.2, 14.8, 24.9, 48.2}, 0.0},
+                              {32, 4, {9.1, 11.0, 16.9, 19.9, 32.0, 60.0}, 0.006},
+                              {64, 4, {11.2, 17.4, 29.7, 35.9, 61.0, 115.0}, 0.035},
+                              {128, 4, {16.4, 25.0, 46.8, 58.0, 103.5, 200.0}, 0.05},
+                              {128, 8, {15.5, 24.5, 41.5, 50.5, 87.0, 162.0}, 0.025}};
+  static const Form kB16[] = {{16, 4, {3.1, 5.5, 12.7, 16.2, 31.0, 64.5}, 0.0},
+                              {16, 8, {4.7, 7.8, 14.0, 17.5, 31.7, 65.7}, 0.0},
+                              {32, 4, {8.1, 11.2, 20.5, 25.3, 45.5, 87.0}, 0.006},
+                              {64, 4, {12.1, 21.1, 39.8, 49.6, 90.0, 170.0}, 0.035},
+                              {128, 4, {18.7, 31.8, 66.5, 84.0, 157.0, 303.0}, 0.05},
+                              {128, 8, {14.5, 26.2, 57.0, 73.0, 134.0, 258.0}, 0.025}};
+  const Form *forms = pf == kPfF16x2 ? kF16 : kB16;
   int i = 0;
   while (i + 2 < kPts && n_tiles > kTiles[i + 1]) ++i;
   const double at = (n_tiles - kTiles[i]) / (kTiles[i + 1] - kTiles[i]);
-  TileChoice best{16, 4};
-  double t_best = 0;
-  for (const Form &f : pf == kPfF16x2 ? kF16 : kB16) {
-    // a caller's waves, if given (the library's 16-row tiles take theirs by the grid
-    // of the launch, see rollout_launch)
-    if (waves > 0 ? f.waves != waves : f.spw == 16 && f.waves == 8) continue;
+  auto time = [&](const Form &f) {
     const int64_t pass = 256 * (int64_t)f.spw;
-    const double t = (double)((n + pass - 1) / pass) * (f.us[i] + at * (f.us[i + 1] - f.us[i]));
-    if (t_best == 0 || t < t_best) {
+    return (double)((n + pass - 1) / pass) * (f.us[i] + at * (f.us[i + 1] - f.us[i]) + f.obs * (n_obs - kObs));
+  };
+  // a caller's waves, if given (the library's 16-row tiles take theirs by the grid of the
+  // launch, see rollout_launch)
+  const Form *best = &forms[n >= kSharedTileMinSamples ? (waves == 4 ? 4 : 5) : (waves == 8 ? 1 : 0)];
+  double t_best = kTileMargin * time(*best);
+  for (int k = 0; k < 6; ++k) {
+    if (waves > 0 ? forms[k].waves != waves : k == 1) continue;
+    const double t = time(forms[k]);
+    if (t < t_best) {
       t_best = t;
-      best = TileChoice{f.spw, f.waves};
+      best = &forms[k];
     }
   }
-  return best;
+  return TileChoice{best->spw, best->waves};
 }
 
 // Whether predictions left to the library skip the fold (predict_raw_kernel): models
@@ -338,7 +347,7 @@ RolloutPlan rollout_plan(const pi_problem *p, const pi_lwpr *m) {
   r.bf = r.pf != kPfF32;
   TileChoice tile{16, 4};
   if (r.bf && p->tile_samples == 0 && p->dyn == PI_DYN_QUAD12 && bf_model_ok(m))
-    tile = pieces_tile(r.pf, auto_bf ? 4 : p->tile_waves, n, mfma_layout(m->d, m->n_out, m->L_off).n_tiles);
+    tile = pieces_tile(r.pf, auto_bf ? 4 : p->tile_waves, n, mfma_layout(m->d, m->n_out, m->L_off).n_tiles, p->n_obs);
   const bool large = tile.spw > 16;
   r.waves = p->tile_waves > 0 ? p->tile_waves : large ? tile.waves : 4;
   const bool split_allowed = r.mfma && (r.waves == 4 || (r.waves == 8 && p->dyn == PI_DYN_QUAD12)) &&
