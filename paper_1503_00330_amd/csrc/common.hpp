@@ -195,6 +195,15 @@ __device__ __forceinline__ void lwpr_input(const Real *x, const Real *u, Real *z
   }
 }
 
+// Component a of that input.
+template <int DYN, typename Real>
+__device__ __forceinline__ Real lwpr_input_at(const Real *x, const Real *u, int a) {
+  if constexpr (DYN == kDynQuadHybrid)
+    return a < 3 ? x[6 + a] : u[3];
+  else
+    return a < (DYN == kDynPointMass2D ? 4 : 12) ? x[a] : u[a - (DYN == kDynPointMass2D ? 4 : 12)];
+}
+
 // Explicit Euler: positions integrate velocities, velocities the linear
 // accelerations; for the 12-state quadrotor euler angles integrate the body
 // rates and rates integrate the angular accelerations; for the hybrid
@@ -269,6 +278,24 @@ __device__ __forceinline__ void euler_step_comp(int dyn, float dt, const float *
       add(9 + a, acc[3 + a]);
     }
   }
+}
+
+// The same step by a lane per component: component a of the state, x and u of a row in
+// LDS, acc(o) its accelerations.
+template <int DYN, class Acc>
+__device__ __forceinline__ void euler_lane_comp(int a, float dt, const float *x, const float *u, Acc acc, float &xa,
+                                                float &lo) {
+  float rate;
+  if constexpr (DYN == kDynPointMass2D)
+    rate = a < 2 ? x[2 + a] : acc(a - 2);
+  else if constexpr (DYN == kDynQuadHybrid)
+    rate = a < 3 ? x[3 + a] : a < 6 ? acc(a - 3) : (float)kRateGain * (u[a - 6] - x[a]);
+  else
+    rate = a < 3 || (a >= 6 && a < 9) ? x[3 + a] : acc(a < 6 ? a - 3 : a - 6);
+  const float y = dt * rate + lo, xn = xa + y;
+  lo = y - (xn - xa);
+  if (DYN == kDynQuadHybrid && a < 6) lo = __builtin_amdgcn_fmed3f(lo, -kLargestUlp, kLargestUlp);
+  xa = xn;
 }
 
 // State cost q(x) (Sec. 5): weighted squared goal error, |euler|^2 and |v|^2

@@ -1988,30 +1988,51 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
 #pragma unroll
       for (int a = 0; a < NU; ++a) u[a] = rs.us_s[tc][row][a];
     };
-    if (row < ROWS) {
-      if (active) {
-        float u[NU], x[NX], z[D];
-        applied(u);
+    if constexpr (SH) {
+      if (row < ROWS) {
+        if (active) {
+          float u[NU], x[NX], z[D];
+          applied(u);
 #pragma unroll
-        for (int a = 0; a < NX; ++a) x[a] = rs.xs[row][a];
-        if (trace) {
+          for (int a = 0; a < NX; ++a) x[a] = rs.xs[row][a];
+          if (trace) {
 #pragma unroll
-          for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(t - tb) * SEGW + a] = x[a];
+            for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(t - tb) * SEGW + a] = x[a];
+          }
+          if (ckpt_out && t % ck == 0) {
+            float *dst = ckpt_out + (s * nck + t / ck) * (2 * NX);
+#pragma unroll
+            for (int a = 0; a < NX; ++a) {
+              dst[a] = x[a];
+              dst[NX + a] = rs.xlo[row][a];
+            }
+          }
+          lwpr_input<DYN>(x, u, z);
+#pragma unroll
+          for (int a = 0; a < D; ++a) sm.z[row][a] = z[a];
+        } else {
+#pragma unroll
+          for (int a = 0; a < D; ++a) sm.z[row][a] = 0.0f;
         }
-        if (ckpt_out && t % ck == 0) {
-          float *dst = ckpt_out + (s * nck + t / ck) * (2 * NX);
-#pragma unroll
-          for (int a = 0; a < NX; ++a) {
-            dst[a] = x[a];
-            dst[NX + a] = rs.xlo[row][a];
+      }
+    } else {
+      // 16 lanes to a row, one component each
+      for (int i = threadIdx.x; i < ROWS * 16; i += NW * 64) {
+        const int rr = i >> 4, l = i & 15;
+        const int64_t ss = s_base + rr;
+        const bool act = rr < spw && ss < (int64_t)p.K * p.Ms;
+        if (l < D) {
+          const float z = lwpr_input_at<DYN>(rs.xs[rr], rs.us_s[tc][rr], l);
+          sm.z[rr][l] = act ? z : 0.0f;
+        }
+        if (act && l < NX) {
+          if (trace) trace[rr * tstride + (int64_t)(t - tb) * SEGW + l] = rs.xs[rr][l];
+          if (ckpt_out && t % ck == 0) {
+            float *dst = ckpt_out + (ss * nck + t / ck) * (2 * NX);
+            dst[l] = rs.xs[rr][l];
+            dst[NX + l] = rs.xlo[rr][l];
           }
         }
-        lwpr_input<DYN>(x, u, z);
-#pragma unroll
-        for (int a = 0; a < D; ++a) sm.z[row][a] = z[a];
-      } else {
-#pragma unroll
-        for (int a = 0; a < D; ++a) sm.z[row][a] = 0.0f;
       }
     }
     __syncthreads();
@@ -2023,25 +2044,47 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
       sa.trace_rows = trows;
     }
     mixture_step(md, sm, t == tb, T0, T1, pc, seq, sa);
-    if (active) {
-      float acc[NO], xn[NX], x[NX], lo[NX], u[NU];
+    if constexpr (SH) {
+      if (active) {
+        float acc[NO], xn[NX], x[NX], lo[NX], u[NU];
 #pragma unroll
-      for (int o = 0; o < NO; ++o) acc[o] = sm.accel(row, o);
+        for (int o = 0; o < NO; ++o) acc[o] = sm.accel(row, o);
 #pragma unroll
-      for (int a = 0; a < NX; ++a) {
-        x[a] = rs.xs[row][a];
-        lo[a] = rs.xlo[row][a];
+        for (int a = 0; a < NX; ++a) {
+          x[a] = rs.xs[row][a];
+          lo[a] = rs.xlo[row][a];
+        }
+        applied(u);
+        euler_step_comp(DYN, p.dt, x, acc, u, xn, lo);
+#pragma unroll
+        for (int a = 0; a < NX; ++a) {
+          rs.xs[row][a] = xn[a];
+          rs.xlo[row][a] = lo[a];
+          if constexpr (!SH) rs.xc[tc][row][a] = xn[a];
+        }
       }
-      applied(u);
-      euler_step_comp(DYN, p.dt, x, acc, u, xn, lo);
-#pragma unroll
-      for (int a = 0; a < NX; ++a) {
-        rs.xs[row][a] = xn[a];
-        rs.xlo[row][a] = lo[a];
-        if constexpr (!SH) rs.xc[tc][row][a] = xn[a];
+    } else {
+      for (int i = threadIdx.x; i < ROWS * 16; i += NW * 64) {
+        const int rr = i >> 4, l = i & 15;
+        const bool on = l < NX && rr < spw && s_base + rr < (int64_t)p.K * p.Ms;
+        float x = 0.0f, lo = 0.0f;
+        if (on) {
+          x = rs.xs[rr][l];
+          lo = rs.xlo[rr][l];
+          euler_lane_comp<DYN>(l, p.dt, rs.xs[rr], rs.us_s[tc][rr], [&](int o) { return sm.accel(rr, o); }, x, lo);
+        }
+        // a row's lanes are one wave's: their reads are done before their writes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (on) {
+          rs.xs[rr][l] = x;
+          rs.xlo[rr][l] = lo;
+          rs.xc[tc][rr][l] = x;
+        }
       }
     }
   }
+  if constexpr (!SH) __syncthreads();   // the last states, of other lanes
   if (trace && active) {
 #pragma unroll
     for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(te - tb) * SEGW + a] = rs.xs[row][a];
