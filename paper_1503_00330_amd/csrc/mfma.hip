@@ -1871,6 +1871,11 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
   constexpr bool SH = RollSmem<DYN, MT, NW, PF>::SH;
   MixSmem<D, MT, NW, PF> &sm = rs.sm;
   constexpr int SEGW = NX + 5 * NO;   // trace row: x_t, then 5 values per output (SampleArgs)
+  // the shared tile runs whole horizons from x0 and keeps nothing besides the costs
+  if constexpr (SH) {
+    sg = nullptr;
+    tr = nullptr;
+  }
   const int tb = sg ? sg->tb : 0, te = sg ? sg->te : p.T;
   const int ck = sg ? sg->ckpt : 0;
   const int nck = ck > 0 ? (p.T + ck - 1) / ck : 0;
@@ -1995,18 +2000,6 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
           applied(u);
 #pragma unroll
           for (int a = 0; a < NX; ++a) x[a] = rs.xs[row][a];
-          if (trace) {
-#pragma unroll
-            for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(t - tb) * SEGW + a] = x[a];
-          }
-          if (ckpt_out && t % ck == 0) {
-            float *dst = ckpt_out + (s * nck + t / ck) * (2 * NX);
-#pragma unroll
-            for (int a = 0; a < NX; ++a) {
-              dst[a] = x[a];
-              dst[NX + a] = rs.xlo[row][a];
-            }
-          }
           lwpr_input<DYN>(x, u, z);
 #pragma unroll
           for (int a = 0; a < D; ++a) sm.z[row][a] = z[a];
@@ -2060,7 +2053,6 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
         for (int a = 0; a < NX; ++a) {
           rs.xs[row][a] = xn[a];
           rs.xlo[row][a] = lo[a];
-          if constexpr (!SH) rs.xc[tc][row][a] = xn[a];
         }
       }
     } else {
@@ -2200,6 +2192,7 @@ hipError_t launch_rollout_mfma(const RolloutArgs<float> &ra, const ModelArgs &m,
                                const void *base, int tile_samples, int waves, int pf, hipStream_t s) {
   const MfmaModel md = mfma_view(l, base);
   const int spw = tile_samples;
+  if (spw > 32 && (ra.trace || ra.ckpt_out || ra.xstart || ra.t_begin != 0 || ra.t_end >= 0)) return hipErrorInvalidValue;
   if (pf != kPfF32) {
     if (ra.p.dyn != kDynQuad12 || (pf == kPfF16x2 ? md.Wh : md.Wb) == nullptr ||
         (waves == 8 && spw > 16 && spw <= 32) || spw > 128)
