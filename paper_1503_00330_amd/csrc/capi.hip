@@ -437,7 +437,11 @@ bool use_pair(const pi_problem *p, const pi_lwpr *m, const RolloutPlan &pl) {
 // library.  With at most one workgroup per compute unit, eight waves (two per
 // SIMD) keep the matrix cores busier than four; once workgroups share a unit
 // they already do, and four waves are faster (12-state quadrotor, 16-row
-// tiles; the other families have 4-wave kernels only).
+// tiles; the other families have 4-wave kernels only).  The pieces forms without
+// pairs take eight where that leaves a wave one model tile of two, or for very many
+// (eight waves' time over four's, 512..4096 rollouts, fp16 and bf16: 6 tiles 0.91 and
+// 0.94, 12 1.11 and 1.15, 96 1.03 and 1.03, 288 1.01 and 1.00, 384 0.96 and 1.00;
+// float32 12 tiles 1.14, 24 1.02, 48 0.98, 384 0.90).
 struct RolloutLaunch {
   RolloutPlan pl;
   bool pair;
@@ -449,7 +453,9 @@ RolloutLaunch rollout_launch(const pi_problem *p, const pi_lwpr *m) {
   if (p->tile_waves == 0 && r.pl.mfma && p->dyn == PI_DYN_QUAD12 && r.pl.spw <= 16) {
     const int n_cu = device_cus();
     const int64_t wgs = r.pair ? 2 * r.pl.groups : r.pl.groups;
-    if (n_cu > 0 && wgs <= n_cu) {
+    const int t = mfma_layout(m->d, m->n_out, m->L_off).n_tiles;
+    const bool four = r.pl.bf && !r.pair && t > 8 && t < 384;
+    if (n_cu > 0 && wgs <= n_cu && !four) {
       RolloutPlan p8 = r.pl;
       p8.waves = 8;
       // a pair keeps four waves if its 8-wave grid would not be resident

@@ -65,3 +65,17 @@ def test_tiles_of_the_pieces(variant, waves, L, K, spw):
         assert d["variant"] == ("mfma" if K <= 2048 else "mfma-bf16x3")
     if L < 16:
         _parity(prob, model, dp, dm)
+
+
+# waves of 16-row tiles, at most one workgroup to a unit: eight, but four for the pieces
+# forms without pairs, except with very few or very many model tiles
+@pytest.mark.parametrize("variant,L,K,split,waves", [
+    (2, 5, 4096, 1, 8), (2, 256, 4096, 1, 8), (2, 256, 1024, 2, 8), (3, 5, 2100, 1, 8), (3, 20, 2100, 1, 4),
+    (3, 256, 2100, 1, 4), (3, 256, 1024, 2, 8), (4, 5, 2100, 1, 8), (4, 20, 2100, 1, 4), (4, 256, 4096, 1, 4),
+    (4, 256, 1024, 2, 8), (4, 1024, 2100, 1, 8), (0, 256, 2100, 1, 4)])
+def test_waves(variant, L, K, split, waves):
+    prob, model, dp, dm = _problem(K, L, variant=variant)
+    d = pi.rollout_describe(dp, dm)
+    assert (d["tile_samples"], d["tile_split"], d["tile_waves"]) == (16, split, waves)
+    if L < 64:
+        _parity(prob, model, dp, dm)
