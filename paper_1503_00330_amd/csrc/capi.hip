@@ -266,8 +266,8 @@ bool auto_pieces(const pi_problem *p, const pi_lwpr *m, int64_t n) {
 // measured numbers of model tiles, plus what an obstacle adds where the costs are
 // evaluated between the steps' products (10289 rollouts x 25 steps, 72 tiles, 35
 // obstacles, fp16: 16 rows 29.6 us, 64 rows 32.0).  Over the measured launches the
-// choice is within half a per cent of the best one on average, 11 % at most, and never
-// slower than the rule it starts from (but for one launch, by 0.7 %).
+// choice is within 1 % of the best one on average, 12 % at most, and never slower than
+// the rule it starts from.
 struct TileChoice {
   int spw, waves;
 };
@@ -279,15 +279,15 @@ TileChoice pieces_tile(int pf, int waves, int64_t n, int n_tiles, int n_obs) {
     int spw, waves;
     double us[kPts], obs;
   };
-  static const Form kF16[] = {{16, 4, {3.2, 4.6, 10.1, 12.4, 23.0, 46.2}, 0.0},
-                              {16, 8, {4.8, 7.3, 12.2, 14.8, 24.9, 48.2}, 0.0},
-                              {32, 4, {9.1, 11.0, 16.9, 19.9, 32.0, 60.0}, 0.006},
+  static const Form kF16[] = {{16, 4, {3.0, 4.4, 9.7, 11.9, 22.4, 45.6}, 0.0},
+                              {16, 8, {4.6, 7.1, 12.0, 14.6, 24.6, 48.2}, 0.0},
+                              {32, 4, {9.1, 11.0, 16.9, 19.9, 32.0, 60.5}, 0.006},
                               {64, 4, {11.2, 17.4, 29.7, 35.9, 61.0, 115.0}, 0.035},
                               {128, 4, {16.4, 25.0, 46.8, 58.0, 103.5, 200.0}, 0.05},
                               {128, 8, {15.5, 24.5, 41.5, 50.5, 87.0, 162.0}, 0.025}};
-  static const Form kB16[] = {{16, 4, {3.1, 5.5, 12.7, 16.2, 31.0, 64.5}, 0.0},
-                              {16, 8, {4.7, 7.8, 14.0, 17.5, 31.7, 65.7}, 0.0},
-                              {32, 4, {8.1, 11.2, 20.5, 25.3, 45.5, 87.0}, 0.006},
+  static const Form kB16[] = {{16, 4, {3.0, 5.3, 12.4, 15.9, 30.5, 64.8}, 0.0},
+                              {16, 8, {4.5, 7.4, 13.8, 17.3, 31.3, 65.2}, 0.0},
+                              {32, 4, {8.1, 11.2, 20.5, 25.3, 46.0, 90.0}, 0.006},
                               {64, 4, {12.1, 21.1, 39.8, 49.6, 90.0, 170.0}, 0.035},
                               {128, 4, {18.7, 31.8, 66.5, 84.0, 157.0, 303.0}, 0.05},
                               {128, 8, {14.5, 26.2, 57.0, 73.0, 134.0, 258.0}, 0.025}};

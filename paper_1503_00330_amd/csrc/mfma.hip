@@ -1993,13 +1993,25 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
 #pragma unroll
       for (int a = 0; a < NU; ++a) u[a] = rs.us_s[tc][row][a];
     };
-    if constexpr (SH) {
+    if constexpr (MT > 1) {
       if (row < ROWS) {
         if (active) {
           float u[NU], x[NX], z[D];
           applied(u);
 #pragma unroll
           for (int a = 0; a < NX; ++a) x[a] = rs.xs[row][a];
+          if (trace) {
+#pragma unroll
+            for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(t - tb) * SEGW + a] = x[a];
+          }
+          if (ckpt_out && t % ck == 0) {
+            float *dst = ckpt_out + (s * nck + t / ck) * (2 * NX);
+#pragma unroll
+            for (int a = 0; a < NX; ++a) {
+              dst[a] = x[a];
+              dst[NX + a] = rs.xlo[row][a];
+            }
+          }
           lwpr_input<DYN>(x, u, z);
 #pragma unroll
           for (int a = 0; a < D; ++a) sm.z[row][a] = z[a];
@@ -2009,7 +2021,9 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
         }
       }
     } else {
-      // 16 lanes to a row, one component each
+      // 16 rows: 16 lanes to each, one component a lane (2048 rollouts x 100 steps of
+      // 6 x 256 models 1037 us with a lane per row, 1024 so; 32 rows take two rounds
+      // and 1 to 3 % longer)
       for (int i = threadIdx.x; i < ROWS * 16; i += NW * 64) {
         const int rr = i >> 4, l = i & 15;
         const int64_t ss = s_base + rr;
@@ -2037,7 +2051,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
       sa.trace_rows = trows;
     }
     mixture_step(md, sm, t == tb, T0, T1, pc, seq, sa);
-    if constexpr (SH) {
+    if constexpr (MT > 1) {
       if (active) {
         float acc[NO], xn[NX], x[NX], lo[NX], u[NU];
 #pragma unroll
@@ -2053,6 +2067,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
         for (int a = 0; a < NX; ++a) {
           rs.xs[row][a] = xn[a];
           rs.xlo[row][a] = lo[a];
+          if constexpr (!SH) rs.xc[tc][row][a] = xn[a];
         }
       }
     } else {
@@ -2076,7 +2091,7 @@ __device__ void rollout_tile(RollSmem<DYN, MT, NW, PF> &rs, const ProbDev<float>
       }
     }
   }
-  if constexpr (!SH) __syncthreads();   // the last states, of other lanes
+  if constexpr (MT == 1) __syncthreads();   // the last states, of other lanes
   if (trace && active) {
 #pragma unroll
     for (int a = 0; a < NX; ++a) trace[row * tstride + (int64_t)(te - tb) * SEGW + a] = rs.xs[row][a];
