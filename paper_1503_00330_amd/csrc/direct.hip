@@ -774,14 +774,16 @@ __device__ __forceinline__ void load_cost4(const Real *__restrict__ row, int t, 
 // Stage 1: lanes take (row, segment) pairs in memory order, the segment sums meet
 // in LDS, one lane per row walks them backwards, and the boundaries go out
 // transposed, 32 rows at a time.  Bound by reading the costs.
-template <typename Real>
+// kLoop: more rows than kUpdMaxGrid blocks take.
+template <typename Real, bool kLoop>
 __global__ void __launch_bounds__(256) update_bound_kernel(const Real *__restrict__ cost, int K, int T, int seg_len,
                                                            int nseg, int vec, double *__restrict__ Sb) {
   __shared__ double tot[kUpdRows][kUpdMaxSeg + 1];
-  for (int64_t k0 = (int64_t)blockIdx.x * kUpdRows; k0 < K; k0 += (int64_t)gridDim.x * kUpdRows) {
+  // (k0 stays below 2^31 + 2^25)
+  for (uint32_t k0 = blockIdx.x * kUpdRows; k0 < (uint32_t)K; k0 += gridDim.x * kUpdRows) {
     for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
       const int r = e / nseg, j = e - r * nseg;
-      const Real *row = cost + min(k0 + r, (int64_t)K - 1) * T;
+      const Real *row = cost + (int64_t)min(k0 + r, (uint32_t)K - 1) * T;
       const int te = min(T, (j + 1) * seg_len);
       double sum = 0.0;
       for (int t = j * seg_len; t < te; t += 8) {
@@ -804,9 +806,10 @@ __global__ void __launch_bounds__(256) update_bound_kernel(const Real *__restric
     __syncthreads();
     for (int e = threadIdx.x; e < kUpdRows * nseg; e += 256) {
       const int r = e % kUpdRows, j = e / kUpdRows;
-      if (k0 + r < K) Sb[(int64_t)j * K + k0 + r] = tot[r][j];
+      if (k0 + r < (uint32_t)K) Sb[(int64_t)j * K + k0 + r] = tot[r][j];
     }
-    __syncthreads();
+    if (!kLoop) return;
+    __syncthreads();   // the sums have been read
   }
 }
 
@@ -966,7 +969,8 @@ __global__ void __launch_bounds__(256) update_part_kernel(ProbDev<Real> p, doubl
 
 // Stage 3, one block per step: every lane reads its chunks' partials at once, so the
 // block waits for memory once; then minima and sums over the waves and through LDS.
-template <typename Real>
+// kLoop: more steps than kUpdMaxGrid.
+template <typename Real, bool kLoop>
 __global__ void __launch_bounds__(256) update_apply_kernel(int T, int C, int n_u, double lambda,
                                                            const double *__restrict__ part,
                                                            Real *__restrict__ u_nom, double *__restrict__ norm,
@@ -975,8 +979,8 @@ __global__ void __launch_bounds__(256) update_apply_kernel(int T, int C, int n_u
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // the iteration's draws have all been consumed: advance the iteration word
   if (blockIdx.x == 0 && threadIdx.x == 0) *iter += 1u;
-  for (int64_t i = blockIdx.x; i < T; i += gridDim.x) {
-    const double *pi_ = part + i * kUpdQ * C;
+  for (uint32_t i = blockIdx.x; i < (uint32_t)T; i += gridDim.x) {
+    const double *pi_ = part + (int64_t)i * kUpdQ * C;
     double m = 1.0 / 0.0, v[1 + kMaxU] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int c = threadIdx.x; c < C; c += 256) {
       const double mc = pi_[c], mn = fmin(m, mc);
@@ -999,12 +1003,13 @@ __global__ void __launch_bounds__(256) update_apply_kernel(int T, int C, int n_u
     __syncthreads();
     auto total = [&](int q) { return (wsum[0][q] + wsum[1][q]) + (wsum[2][q] + wsum[3][q]); };
     const int a = threadIdx.x;
-    if (a < n_u) u_nom[i * n_u + a] = (Real)((double)u_nom[i * n_u + a] + total(1 + a) / total(0));
+    if (a < n_u) u_nom[(int64_t)i * n_u + a] = (Real)((double)u_nom[(int64_t)i * n_u + a] + total(1 + a) / total(0));
     if (a == 0) {
-      norm[2 * i] = mn;
-      norm[2 * i + 1] = total(0);
+      norm[2 * (int64_t)i] = mn;
+      norm[2 * (int64_t)i + 1] = total(0);
     }
-    if (i + gridDim.x < T) __syncthreads();   // the sums have been read
+    if (!kLoop) return;
+    __syncthreads();   // the sums have been read
   }
 }
 
@@ -1032,8 +1037,12 @@ static void update_part(const ProbDev<Real> &p, const Real *cost, const uint32_t
   const int nseg = (T + seg_len - 1) / seg_len;
   const int vec = T % 4 == 0 && (uintptr_t)cost % 16 == 0;
   *part = (double *)((char *)ws + align_up((size_t)K * nseg * 8, 256));
-  hipLaunchKernelGGL(update_bound_kernel<Real>, dim3(std::min((K - 1) / kUpdRows + 1, kUpdMaxGrid)), dim3(256), 0, s,
-                     cost, K, T, seg_len, nseg, vec, ws);
+  const int nb = (K - 1) / kUpdRows + 1;
+  if (nb > kUpdMaxGrid)
+    hipLaunchKernelGGL((update_bound_kernel<Real, true>), dim3(kUpdMaxGrid), dim3(256), 0, s, cost, K, T, seg_len, nseg,
+                       vec, ws);
+  else
+    hipLaunchKernelGGL((update_bound_kernel<Real, false>), dim3(nb), dim3(256), 0, s, cost, K, T, seg_len, nseg, vec, ws);
   if (single)
     hipLaunchKernelGGL((update_part_kernel<Real, NU, 1, 1>), dim3((C + 3) / 4, T), dim3(256), 0, s, p, lambda, inv,
                        weighting, iter, cost, (const double *)ws, seg_len, nseg, vec, C, *part);
@@ -1055,8 +1064,12 @@ static hipError_t update_t(const ProbDev<Real> &p, const Real *cost, const uint3
     update_part<Real, 2>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
   else
     update_part<Real, 4>(p, cost, iter, (double *)ws, &part, &C, lambda, weighting, s);
-  hipLaunchKernelGGL(update_apply_kernel<Real>, dim3(std::min(T, kUpdMaxGrid)), dim3(256), 0, s, T, C, p.n_u, lambda,
-                     (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
+  if (T > kUpdMaxGrid)
+    hipLaunchKernelGGL((update_apply_kernel<Real, true>), dim3(kUpdMaxGrid), dim3(256), 0, s, T, C, p.n_u, lambda,
+                       (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
+  else
+    hipLaunchKernelGGL((update_apply_kernel<Real, false>), dim3(T), dim3(256), 0, s, T, C, p.n_u, lambda,
+                       (const double *)part, u_nom, norm, const_cast<uint32_t *>(iter));
   if (W) {
     const unsigned nb = (unsigned)((K + kWgtK - 1) / kWgtK);
     if (nb >= 256)   // enough blocks to cover the compute units: read through LDS
