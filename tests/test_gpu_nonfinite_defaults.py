@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import synth
-from synth import DYN_QUAD12, DYN_QUAD_HYBRID, OBS_SMOOTH
+from synth import DYN_POINTMASS2D, DYN_QUAD12, DYN_QUAD_HYBRID, OBS_SMOOTH
 
 torch = pytest.importorskip("torch")
 pi = pytest.importorskip("paper_1503_00330_amd")
@@ -128,3 +128,46 @@ def test_infinite_coefficient_folds_to_infinity(d, n_out, variant):
     mean, _ = pi.lwpr_predict(pi.DeviceModel(model), torch.from_numpy(Z).cuda(), variant=variant)
     mean = mean.cpu().numpy()
     assert np.isposinf(mean[:, 0]).all() and np.isfinite(mean[:, 1:]).all()
+
+
+# few inputs of a model of the small dynamics, given unfolded (no fold) and folded
+@pytest.mark.parametrize("folded", [False, True])
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("d,n_out", [(4, 3), (6, 2)])
+def test_nan_inputs_of_small_predictions(d, n_out, dtype, folded):
+    rng = np.random.Generator(np.random.PCG64(9))
+    model = synth.make_lwpr(rng, d, [70, 16, 5][:n_out], 3).astype(dtype)
+    Z = rng.uniform(-1, 1, (40, d)).astype(dtype)
+    Z[3, 1], Z[17, 0], Z[39, d - 1] = np.nan, np.inf, -np.inf
+    dm = pi.DeviceModel(model)
+    mean, var = pi.lwpr_predict(dm.fold() if folded else dm, torch.from_numpy(Z).cuda())
+    om, ov = oracle.lwpr_predict(model, Z)
+    tol = 1e-10 if dtype == F64 else 1e-5
+    _same_nonfinite(mean.cpu().numpy(), om, tol)
+    _same_nonfinite(var.cpu().numpy(), ov, tol)
+
+
+# the small-model rollouts: a start state, a control and a model's parameter
+@pytest.mark.parametrize("where", ["x0", "u_nom", "u_inf", "centre", "sigma2"])
+@pytest.mark.parametrize("K", [40, 25000])
+@pytest.mark.parametrize("dyn", [DYN_POINTMASS2D, DYN_QUAD_HYBRID])
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_nan_reaches_the_costs_of_small_models(dtype, dyn, K, where):
+    L = [17, 9] if dyn == DYN_POINTMASS2D else [15, 15, 24]
+    prob, model = synth.tiny_problem(32, dyn=dyn, L=L, R=2, K=K, T=7, M=1, dtype=dtype, n_obs=3, obs_kind=OBS_SMOOTH)
+    nan = _nan(0xFFFFFFFF)
+    if where == "x0":
+        prob.x0[1] = nan
+    elif where == "u_nom":
+        prob.u_nom[2, -1] = nan
+    elif where == "u_inf":
+        prob.u_nom[2, 0] = np.inf
+    elif where == "centre":
+        model.centre[3, 0] = nan
+    else:
+        model.sigma2[int(model.L_off[1])] = nan
+    dp, dm = pi.DeviceProblem(prob), pi.DeviceModel(model)
+    assert pi.rollout_describe(dp, dm)["variant"] == "direct"
+    ref = oracle.rollout_cost(prob, model)
+    assert not np.isfinite(ref).all()
+    _same_nonfinite(pi.rollout_cost(dp, dm).cpu().numpy(), ref, 1e-10 if dtype == F64 else 1e-4)
