@@ -156,8 +156,10 @@ typedef struct {
                                     * library's choice) */
   int32_t tile_waves;              /* waves per workgroup, 4 or 8 (8: 12-state
                                     * quadrotor only); 0 = library's choice:
-                                    * 8 for the quadrotor when the launch has
-                                    * at most one workgroup per compute unit,
+                                    * for the quadrotor's tiles of <= 16 samples
+                                    * 8 when the launch has at most one workgroup
+                                    * per compute unit (the pieces forms: in
+                                    * pairs, or with few or very many models),
                                     * else 4                                  */
   int32_t tile_split;              /* workgroups per tile of 16 samples: 1 (one
                                     * workgroup runs every local model) or 2 (a
@@ -206,9 +208,10 @@ size_t pi_model_fold_bytes(const pi_lwpr *m);
 pi_status pi_model_fold(const pi_lwpr *m, void *folded, size_t folded_bytes, void *stream);
 
 /* The launch pi_rollout_cost would make for this problem and model on the
- * current device (no work is done): out[0] = PI_VARIANT_DIRECT or
- * PI_VARIANT_MFMA, out[1] = samples per tile, out[2] = waves per workgroup,
- * out[3] = workgroups per tile (1 or 2, see tile_split).  out is a host array
+ * current device (no work is done): out[0] = the kernel variant that runs
+ * (PI_VARIANT_DIRECT, _MFMA, _MFMA_BF16X3 or _MFMA_F16X2; never AUTO), out[1] =
+ * samples per tile, out[2] = waves per workgroup, out[3] = workgroups per tile
+ * (1 or 2, see tile_split).  out is a host array
  * of 4.  Returns PI_ERR_* for invalid arguments as pi_rollout_cost would.   */
 pi_status pi_rollout_describe(const pi_problem *p, const pi_lwpr *m, int32_t *out);
 
@@ -294,7 +297,8 @@ pi_status pi_rh_shift(const pi_problem *p, const pi_lwpr *m, void *x0, void *u_n
  * centres g_centre dev [Ltot][d] and every entry of the metrics g_metric dev
  * [Ltot][d][d] (problem dtype; the metric gradient is symmetric).  gJ (dev,
  * one double) seeds the reverse pass; NULL means 1.  States are checkpointed
- * every `ckpt_every` steps (0: ceil(sqrt(T))) and each segment is recomputed
+ * every `ckpt_every` steps (0: ceil(sqrt(T))), on the matrix cores with their
+ * carried rounding errors, and each segment is recomputed
  * from its checkpoints before its reverse sweep, so the workspace holds the
  * checkpoints and one segment: pi_adjoint_workspace_bytes(p, m, ckpt_every)
  * (or pi_workspace_bytes(PI_OP_ADJOINT), for ckpt_every 0).  Float32
@@ -325,9 +329,11 @@ pi_status pi_rollout_adjoint(const pi_problem *p, const pi_lwpr *m, const void *
  * [T_b][n_u], iter[b] (one uint32), cost[b] [K_b][T_b].  All problems must be
  * PI_F32 and PI_DYN_QUAD12 with matrix-core models (PI_ERR_UNSUPPORTED
  * otherwise).  A problem's tile_samples (<= 32, or <= 128 when the batch
- * runs the bf16x3 or f16x2 form; 0 = 16, or 128 in the f16x2 form of a batch
- * of at least 16384 rollouts) sets its tile; the variant and tile_waves of problem 0 apply to the batch (8
- * waves need every tile <= 16, or the largest above 32 in the pieces forms).
+ * runs the bf16x3 or f16x2 form; 0 = 16, or in the f16x2 form 128 for a batch
+ * of at least 16384 rollouts and beside tiles of 17..32 on 8 waves) sets its
+ * tile; the variant and tile_waves of problem 0 apply to the batch (8
+ * waves need every tile <= 16, or the largest above 32 in the pieces forms, where
+ * a tile that an f16x2 problem leaves to the library counts as 128).
  * Models given pre-folded (pi_lwpr.folded) are read in place; the others are
  * folded into the workspace on every call.  The launch plan (descriptors and
  * work list) is written into the workspace by kernels on `stream`, so these

@@ -252,7 +252,10 @@ constexpr int64_t kPairFullSamples = 16 * 128;
 // the nearer ones (2100..3000 rollouts x 30..100 steps against float64: 0.9e-7..
 // 1.7e-7 of the costs, the float32 products' 1.2e-7..6.3e-7), and it is faster
 // (61 steps, 6 x 256 models, best launch of each: 1.06 against 1.30 ms at 2100
-// rollouts, 3.07 against 4.7 ms at 16384).
+// rollouts, 3.07 against 4.7 ms at 16384; 40 steps of 2100 rollouts: 6 x 16 models
+// 199 and 199 us, 6 x 64 314 against 349, 6 x 1024 2524 against 2872).  Of the tiles
+// below it takes those of four waves: the 128-row tile on eight is the faster one by
+// its line of the table, but has not been measured as this default.
 bool auto_pieces(const pi_problem *p, const pi_lwpr *m, int64_t n) {
   return p->variant == PI_VARIANT_AUTO && p->tile_samples == 0 && p->tile_waves == 0 && p->tile_split == 0 &&
          p->dyn == PI_DYN_QUAD12 && n > kPairFullSamples && bf_model_ok(m);
@@ -604,7 +607,8 @@ struct BatchLayout {
 // the 16-row tiles, whose workgroups are eight times as many (single problems
 // of 6 x 256 models and 40 steps, shared tile on 8 waves against 16 rows on 4
 // or 8: 2.07 against 1.12 or 1.30 ms at 8192 rollouts, 2.07 against 1.99 or
-// 2.39 ms at 16384, 2.08 against 2.87 or 3.59 ms at 24576).
+// 2.39 ms at 16384, 2.08 against 2.87 or 3.59 ms at 24576; on 4 waves 2.29 ms at
+// all three).
 constexpr int64_t kBatchSharedMinSamples = 16384;
 
 // What a problem may ask for: its own tile, or the form's default, whichever the

@@ -39,7 +39,8 @@ inline size_t direct_bytes(int dtype, int d, int Ltot) {
 // Small-model rollouts (rollout_wave_kernel): the records of the whole model in a
 // block's LDS (padded to 16 bytes), at most kWaveModels models per output.  Up to 40
 // (32 in double) at any size; beyond, while a sub-rollout's 16 lanes find idle vector
-// units, and in double where a lane per sub-rollout leaves most of them idle.
+// units, and in double where a lane per sub-rollout leaves most of them idle.  (A record
+// of zeros per output goes beside them.)
 // 50 steps, against the next best form: 30/40/35 models, float, 1000 rollouts 113 us
 // (matrix cores 166), 30400 394 (452), 60/64/50 1000 123 (181), 30400 585 (510);
 // double, 30/25 1000 84 (16 lanes and LDS exchange 257), 30400 574 (lane per

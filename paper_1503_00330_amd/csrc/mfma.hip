@@ -1821,8 +1821,9 @@ struct RollSmem {
   static constexpr bool SH = MixSmem<Dims<DYN>::D, MT, NW, PF>::SH;
   static constexpr int CH = !SH ? kNoiseChunk : PF == kPfBf16x3 && MT == 8 ? 1 : 4;
   MixSmem<Dims<DYN>::D, MT, NW, PF> sm;
-  // the state and its compensation (euler_step_comp): below 1 % of a step in every
-  // form, and an eighth of the float32 batch's error after an update
+  // the state and its compensation (euler_step_comp): up to 0.8 % of a step with a lane
+  // per row, nothing measurable with 16, and an eighth of the float32 batch's error
+  // after an update
   float xs[ROWS][Dims<DYN>::NX], xlo[ROWS][Dims<DYN>::NX];
   float us_s[CH][ROWS][4];           // applied controls u_nom + sigma eps of the chunk
   float xi_s[CH][ROWS][MixSmem<Dims<DYN>::D, MT, NW, PF>::XIS];
@@ -1836,13 +1837,14 @@ struct RollSmem {
 };
 
 // Rollouts s_base .. s_base + spw - 1 of one problem for its whole horizon.
-// Every CH steps (kNoiseChunk, or 1) all lanes draw the chunk's eps and xi, store the
+// Every CH steps (RollSmem::CH) all lanes draw the chunk's eps and xi, store the
 // applied controls u_nom + sigma eps in LDS (no global read is left on the
 // per-step critical section) and evaluate the previous chunk's step costs
 // dt*q(x_{t+1}) from the states kept in LDS (the cost feeds nothing on the
-// path, so it leaves the per-step critical section too).  Per step: rows form z, the waves run the model tiles,
-// partial sums are merged, and each row samples its accelerations and steps
-// Euler.  Block-synchronous; rs.sm must have been set up.  With a pair
+// path, so it leaves the per-step critical section too; the shared tile, which
+// has no room for them, evaluates each step's).  Per step: rows form z, the waves
+// run the model tiles, partial sums are merged and the accelerations sampled, and
+// the rows step Euler.  Block-synchronous; rs.sm must have been set up.  With a pair
 // context (pc->half = 0 or 1) the workgroup runs its half of the model tiles,
 // exchanges sums with its partner, and only half 0 writes costs.
 // The steps a rollout tile runs and what it keeps besides the costs (see
